@@ -14,8 +14,9 @@
 //   cooperatively dequantize a tile ONCE into LDS as bf16 (K row-major [token][channel], V
 //   transposed [channel][token], the layout the packed cache already has), so the unpack/convert
 //   cost is shared by NW*QB*32 queries (half of the threads stage K, the other half V, with the
-//   same code on mirrored layouts).  LDS is double buffered; the next tile's packed codes and
-//   group parameters are fetched into registers before the current tile's MFMAs are issued.
+//   same code on mirrored layouts).  LDS is double buffered; the next tile's packed codes are fetched into
+//   registers before the current tile's MFMAs are issued, the group parameters of the tile after that on their way
+//   to LDS (one float per thread).
 //   Partition.  A unit is one (layer, head, block of NW*QB*32 query rows); its work is its key tiles.
 //   Two forms, chosen by the host.  (a) Every unit is cut into the same number R of key ranges
 //   (gridDim.x = units * R): the host passes where each range begins, placed so that the ranges cost
@@ -28,10 +29,17 @@
 //   next, and the workgroup handles them one after the other.  In both forms a unit covered by one
 //   workgroup is normalized and written directly; otherwise each workgroup writes an unnormalized
 //   partial that combine_kernel merges.
-//   Softmax.  No row maximum on the common path: the reference of the exponent only moves when a
-//   row sum leaves [0, 2^64] (which also catches the very first tile, whose reference is a
-//   sentinel that sends every probability to +infinity); then, and only then, the maximum is
-//   taken, the accumulators are rescaled and the block's probabilities are recomputed.
+//   Softmax.  No row maximum and no rescaling on the common path: the reference of the exponent is the row maximum
+//   of a range's first 32 tokens plus a headroom of 60 powers of two, probabilities are clamped to 1 (a modifier of the
+//   exponential, so nothing can overflow), and only when a row sum reaches 1 - looked at once per tile - the tile is taken
+//   out again, the reference raised and the tile added anew (raise_references).  The loop over full tiles is straight-line
+//   code: a ragged last tile (cache or frame) has its own, simpler, code behind it.
+//   What bounds the loop: vector issue.  Per wave and tile 64 fma + 64 exp + 32 conversions, 56 instructions of dequantizing,
+//   and about 8 cycles of issue for each of 40 MFMAs come to some 1350 cycles, against 1170 of the matrix pipe; two waves
+//   share a SIMD.  v_dot2c_f32_bf16 must stay out of this loop: it executes on the matrix pipe (beside a wave that issues
+//   MFMAs back to back it makes no progress at all), so row sums taken with it serialize MFMAs and softmax; they are MFMAs of
+//   their own here (row_sum).  At 16 heads, 1374 rows, 5470 keys, one key range per 512 rows: 1.88 -> 1.66 us per tile of a
+//   workgroup on the 4-bit cache; a bf16 cache grown by 16 frames of 1374 tokens, four layers: 7190 -> 5760 us.
 #include <cstddef>
 #include <type_traits>
 
@@ -42,16 +50,18 @@ namespace xsv {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kLdsStride = 72;  // bf16 elements per LDS row: 64 + 8 pad (144 B, keeps 16 B alignment)
 constexpr int kLdsTile = 64 * kLdsStride;  // elements of one K (or V) tile in LDS
+// the kernel's local functions are called from several places and are large: without this some of them become calls whose
+// captured registers go through memory
+#define XSV_INLINE __attribute__((always_inline))
 constexpr float kNegBig = -1.0e30f;
-// "no reference yet": with this in place of -reference every finite logit exponentiates to +infinity, which the
-// row-sum check catches, and the first real reference then scales the (empty) sums by 2^-huge = 0
-constexpr float kNoReference = 1.0e30f;
-// row sums may grow to this before the reference of the exponent is moved: 2^64 leaves the fp32 accumulators
-// (sums of probability x value over thousands of tokens) far from overflow
-constexpr float kSumLimit = 0x1p64f;
+// A row's reference is put this many powers of two above its largest logit so far: probabilities start at 2^-60 and are
+// clamped to 1 by the exponential's own output modifier, so nothing overflows while the reference stands; it has to move only
+// when a row's sum reaches 1.  Probabilities down to 2^-66 of the row's largest stay normal numbers.
+constexpr float kHeadroom = 60.0f;
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
@@ -119,10 +129,30 @@ struct Stage {
   static constexpr int kSets = (G >= 64 || kIter == 1) ? 1 : 2;
   static_assert(kItems % NH == 0 && NH % kRI == 0, "thread count must tile the items");
   static_assert(kSets == 1 || (kIter % 2 == 0 && kRowStep * (kIter / 2) == 32), "two groups need an even split");
+  // A tile has kPrm scales and kPrm zero points per role, consecutive in memory (K: [group][channel], V: [token][channel
+  // group]).  Only the first tile of a range takes them from there; for the others they come through LDS, where they are
+  // put a tile ahead (see PrmStage): held in registers across a tile's MFMAs, as the codes are, they would cost a
+  // thread up to 64 registers.
+  static constexpr int kPrm = kTile * kD / G;
+};
 
-  uint32_t code[kQuant ? kIter : 1];
-  float ps[kQuant ? kSets : 1][kPer], pz[kQuant ? kSets : 1][kPer];
-  uint4 row[kQuant ? 1 : kIter];  // bf16 cache
+// A tile on its way to LDS: packed codes or bf16 rows of the cache, or rows of the frame.  (Two types, held by two
+// loops: one array for both costs register copies right behind the loads, which then wait for them.)
+template <int BITS, int G, int NH>
+struct CacheRegs {
+  uint32_t w[Stage<BITS, G, NH>::kIter * (BITS == 16 ? 4 : 1)];
+};
+template <int NH>
+struct FrameRegs {
+  uint32_t w[512 / NH * 4];
+};
+
+// The parameters of one tile and role on their way to LDS: scales, then zero points, one float per thread and step.
+template <int BITS, int G, int NH>
+struct PrmStage {
+  static constexpr int kFloats = 2 * Stage<BITS, G, NH>::kPrm;
+  static constexpr int kIter = (kFloats + NH - 1) / NH;
+  float x[kIter];
 };
 
 struct RolePtrs {      // what distinguishes the K half from the V half
@@ -130,82 +160,96 @@ struct RolePtrs {      // what distinguishes the K half from the V half
   const float* ps;        // parameter arrays of (layer, head)
   const float* pz;
   uint16_t* lds;          // first of the two LDS tiles of this role (the second follows it)
+  float* prm;             // first of the two LDS parameter blocks of this role (the second follows it)
   bool is_v;
 };
 
 template <int BITS, int G, int NH>
-__device__ __forceinline__ void fetch_cache_tile(Stage<BITS, G, NH>& st, const RolePtrs& rp, int Tcap, int tile, int u) {
+__device__ __forceinline__ void fetch_cache_tile(CacheRegs<BITS, G, NH>& st, const RolePtrs& rp, int tile, int u) {
   using S = Stage<BITS, G, NH>;
   constexpr int kRowDw = kD * BITS / 32;  // dwords per K row == dwords per V block row
   const uint32_t* base = rp.codes + (size_t)tile * kTile * kRowDw;
   if constexpr (!S::kQuant) {
 #pragma unroll
-    for (int it = 0; it < S::kIter; ++it) st.row[it] = reinterpret_cast<const uint4*>(base)[u + it * NH];
+    for (int it = 0; it < S::kIter; ++it) {
+      const u32x4 v = reinterpret_cast<const u32x4*>(base)[u + it * NH];
+      st.w[4 * it] = v[0]; st.w[4 * it + 1] = v[1]; st.w[4 * it + 2] = v[2]; st.w[4 * it + 3] = v[3];
+    }
   } else {
 #pragma unroll
-    for (int it = 0; it < S::kIter; ++it) st.code[it] = base[u + it * NH];
-    const int o = u % S::kRI;
-#pragma unroll
-    for (int set0 = 0; set0 < S::kSets; ++set0) {
-      // 32-row half of the tile this set belongs to (a thread with a single item has a single row)
-      const int set = (G >= 64) ? 0 : (S::kIter == 1 ? (u / S::kRI) / 32 : set0);
-      // K: parameters [group][channel], the item's channels are o*kPer.. of group (tile, set)
-      // V: parameters [token][channel group], the item's tokens are o*kPer.. of channel group `set`
-      const float *ps, *pz;
-      size_t stride;
-      if (!rp.is_v) {
-        const size_t g = (G >= kTile) ? (size_t)tile / (G / kTile) : (size_t)tile * (kTile / G) + set;
-        ps = rp.ps + g * kD + o * S::kPer;
-        pz = rp.pz + g * kD + o * S::kPer;
-        stride = 1;
-      } else {
-        const size_t t0 = (size_t)tile * kTile + o * S::kPer;
-        ps = rp.ps + t0 * (kD / G) + set;
-        pz = rp.pz + t0 * (kD / G) + set;
-        stride = kD / G;
-      }
-      if (!rp.is_v || kD / G == 1) {  // consecutive parameters: 16-byte loads (t0 and o * kPer are multiples of 8)
-#pragma unroll
-        for (int e = 0; e < S::kPer; e += 4) {
-          const float4 a4 = *reinterpret_cast<const float4*>(ps + e), b4 = *reinterpret_cast<const float4*>(pz + e);
-          st.ps[set0][e] = a4.x; st.ps[set0][e + 1] = a4.y; st.ps[set0][e + 2] = a4.z; st.ps[set0][e + 3] = a4.w;
-          st.pz[set0][e] = b4.x; st.pz[set0][e + 1] = b4.y; st.pz[set0][e + 2] = b4.z; st.pz[set0][e + 3] = b4.w;
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < S::kPer; ++e) {
-          st.ps[set0][e] = ps[e * stride];
-          st.pz[set0][e] = pz[e * stride];
-        }
-      }
-    }
+    for (int it = 0; it < S::kIter; ++it) st.w[it] = base[u + it * NH];
   }
 }
 
 template <int BITS, int G, int NH>
-__device__ __forceinline__ void store_cache_tile(const Stage<BITS, G, NH>& st, uint16_t* lds, int u) {
+__device__ __forceinline__ void fetch_params(PrmStage<BITS, G, NH>& st, const RolePtrs& rp, int tile, int u) {
+  using P = PrmStage<BITS, G, NH>;
+  constexpr int kPrm = Stage<BITS, G, NH>::kPrm;
+#pragma unroll
+  for (int it = 0; it < P::kIter; ++it) {
+    const int i = u + it * NH;
+    if (P::kFloats % NH == 0 || i < P::kFloats) st.x[it] = (i < kPrm ? rp.ps : rp.pz - kPrm)[(size_t)tile * kPrm + i];
+  }
+}
+
+template <int BITS, int G, int NH>
+__device__ __forceinline__ void store_params(const PrmStage<BITS, G, NH>& st, float* prm, int u) {
+  using P = PrmStage<BITS, G, NH>;
+#pragma unroll
+  for (int it = 0; it < P::kIter; ++it) {
+    const int i = u + it * NH;
+    if (P::kFloats % NH == 0 || i < P::kFloats) prm[i] = st.x[it];
+  }
+}
+
+// ps, pz: the tile's kPrm scales and zero points of this role, in LDS or in global memory
+template <int BITS, int G, int NH>
+__device__ __forceinline__ void store_cache_tile(const CacheRegs<BITS, G, NH>& st, uint16_t* lds, const float* ps, const float* pz, bool is_v,
+                                                 int u) {
   using S = Stage<BITS, G, NH>;
   const int r0 = u / S::kRI, o = u % S::kRI;
-  // The cache's canonical view: (code - zero) exactly, ONE fp32 multiply by the scale, then bf16.
-  // (A fused code * scale + (-zero * scale) would save an instruction per element, but it rounds
-  // zero * scale first and so breaks ties differently: products of a small integer with
-  // scale = range / levels land on bf16 midpoints often enough to move a dominant key's logit.)
+  if constexpr (!S::kQuant) {
 #pragma unroll
-  for (int it = 0; it < S::kIter; ++it) {
-    uint16_t* dst = lds + (r0 + it * S::kRowStep) * kLdsStride + o * S::kPer;
-    if constexpr (!S::kQuant) {
-      *reinterpret_cast<uint4*>(dst) = st.row[it];
-    } else {
-      const int set = (S::kSets == 1) ? 0 : (it >= S::kIter / 2);
-      float f[S::kPer];
-      unpack_codes<BITS>(st.code[it], f);
-      uint32_t pk[S::kPer / 2];
+    for (int it = 0; it < S::kIter; ++it)
+      *reinterpret_cast<u32x4*>(lds + (r0 + it * S::kRowStep) * kLdsStride + o * S::kPer) =
+          u32x4{st.w[4 * it], st.w[4 * it + 1], st.w[4 * it + 2], st.w[4 * it + 3]};
+  } else {
+    // The cache's canonical view: (code - zero) exactly, ONE fp32 multiply by the scale, then bf16.
+    // (A fused code * scale + (-zero * scale) would save an instruction per element, but it rounds
+    // zero * scale first and so breaks ties differently: products of a small integer with
+    // scale = range / levels land on bf16 midpoints often enough to move a dominant key's logit.)
 #pragma unroll
-      for (int e = 0; e < S::kPer; e += 2)
-        pk[e / 2] = pack_bf16((f[e] - st.pz[set][e]) * st.ps[set][e], (f[e + 1] - st.pz[set][e + 1]) * st.ps[set][e + 1]);
+    for (int set0 = 0; set0 < S::kSets; ++set0) {
+      // 32-row half of the tile this set belongs to (a thread with a single item has a single row)
+      const int set = (G >= 64) ? 0 : (S::kIter == 1 ? r0 / 32 : set0);
+      float s[S::kPer], z[S::kPer];
+      if (!is_v || kD / G == 1) {  // K: group `set`, channels o*kPer..;  V with one channel group: tokens o*kPer..
+        const int off = (is_v ? 0 : set * kD) + o * S::kPer;
 #pragma unroll
-      for (int w = 0; w < S::kPer / 8; ++w)
-        *reinterpret_cast<uint4*>(dst + w * 8) = make_uint4(pk[4 * w], pk[4 * w + 1], pk[4 * w + 2], pk[4 * w + 3]);
+        for (int e = 0; e < S::kPer; e += 4) {
+          const float4 a4 = *reinterpret_cast<const float4*>(ps + off + e), b4 = *reinterpret_cast<const float4*>(pz + off + e);
+          s[e] = a4.x; s[e + 1] = a4.y; s[e + 2] = a4.z; s[e + 3] = a4.w;
+          z[e] = b4.x; z[e + 1] = b4.y; z[e + 2] = b4.z; z[e + 3] = b4.w;
+        }
+      } else {  // V: tokens o*kPer.., channel group `set`
+#pragma unroll
+        for (int e = 0; e < S::kPer; ++e) {
+          s[e] = ps[(o * S::kPer + e) * (kD / G) + set];
+          z[e] = pz[(o * S::kPer + e) * (kD / G) + set];
+        }
+      }
+#pragma unroll
+      for (int it = set0 * (S::kIter / S::kSets); it < (set0 + 1) * (S::kIter / S::kSets); ++it) {
+        float f[S::kPer];
+        unpack_codes<BITS>(st.w[it], f);
+        uint32_t pk[S::kPer / 2];
+#pragma unroll
+        for (int e = 0; e < S::kPer; e += 2) pk[e / 2] = pack_bf16((f[e] - z[e]) * s[e], (f[e + 1] - z[e + 1]) * s[e + 1]);
+        uint16_t* dst = lds + (r0 + it * S::kRowStep) * kLdsStride + o * S::kPer;
+#pragma unroll
+        for (int w = 0; w < S::kPer / 8; ++w)
+          *reinterpret_cast<u32x4*>(dst + w * 8) = u32x4{pk[4 * w], pk[4 * w + 1], pk[4 * w + 2], pk[4 * w + 3]};
+      }
     }
   }
 }
@@ -219,7 +263,6 @@ struct FrameStage {
   static constexpr int kIterK = 512 / NH;  // 16-byte items per K thread
   static constexpr int kIterV = 256 / NH;  // 8-dword items per V thread
   static_assert(kIterK * 4 == kIterV * 8, "both roles stage the same number of registers");
-  uint32_t w[kIterK * 4];
 };
 
 // Frame tile, V half: which (channel pair c2 = 0..31, token octet tq) thread u of the V half stages first (its
@@ -255,7 +298,7 @@ __device__ __forceinline__ FrameRows frame_rows(const uint16_t* xh, int64_t x_st
 }
 
 template <int NH>
-__device__ __forceinline__ void fetch_frame_tile(FrameStage<NH>& st, const FrameRows& f, bool is_v, int tile) {
+__device__ __forceinline__ void fetch_frame_tile(FrameRegs<NH>& st, const FrameRows& f, bool is_v, int tile) {
   using F = FrameStage<NH>;
   const uint32_t tile_off = (uint32_t)tile * kTile * f.row_bytes;  // scalar
   if (!is_v) {
@@ -275,7 +318,7 @@ __device__ __forceinline__ void fetch_frame_tile(FrameStage<NH>& st, const Frame
 }
 
 template <int NH>
-__device__ __forceinline__ void store_frame_tile(const FrameStage<NH>& st, uint16_t* lds, bool is_v, int u) {
+__device__ __forceinline__ void store_frame_tile(const FrameRegs<NH>& st, uint16_t* lds, bool is_v, int u) {
   using F = FrameStage<NH>;
   if (!is_v) {
 #pragma unroll
@@ -317,14 +360,15 @@ __device__ __forceinline__ float xhalf_max(float x) {
 }
 
 // A callable that issues `N` MFMAs per call (the softmax block uses N to lay out its issue order).
-template <int N, typename F>
+template <int N, bool SUMS, typename F>
 struct MfmaHook {
   static constexpr int kMfma = N;
+  static constexpr bool kSums = SUMS;
   F f;
   __device__ __forceinline__ void operator()(int i) const { f(i); }
 };
-template <int N, typename F>
-__device__ __forceinline__ MfmaHook<N, F> with_mfma(F f) { return MfmaHook<N, F>{f}; }
+template <int N, bool SUMS, typename F>
+__device__ __forceinline__ MfmaHook<N, SUMS, F> with_mfma(F f) { return MfmaHook<N, SUMS, F>{f}; }
 
 // ---- partition of the (unit, tile) line over the workgroups -----------------------------------------
 struct Partition {
@@ -371,6 +415,8 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   }
   __shared__ __attribute__((aligned(16))) uint16_t lds_k[2][kLdsTile];
   __shared__ __attribute__((aligned(16))) uint16_t lds_v[2][kLdsTile];
+  constexpr int kPrmBlock = BITS == 16 ? 1 : 2 * Stage<BITS, G, NH>::kPrm;  // one tile's scales and zero points of one role
+  __shared__ __attribute__((aligned(16))) float lds_prm[2][2][kPrmBlock];    // [role][buffer]
 
   const int H = a.H, n = a.n, Tc = a.Tc;
   const int nqb = (n + kRowsWG - 1) / kRowsWG;
@@ -458,6 +504,7 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   rp.ps = is_v ? ly.vs + (size_t)h * a.vparam_head : ly.ks + (size_t)h * a.kparam_head;
   rp.pz = is_v ? ly.vz + (size_t)h * a.vparam_head : ly.kz + (size_t)h * a.kparam_head;
   rp.lds = is_v ? lds_v[0] : lds_k[0];
+  rp.prm = lds_prm[is_v][0];
   const uint16_t* xh = is_v ? ly.v + (size_t)h * a.v_sh : ly.k + (size_t)h * a.k_sh;
   const int64_t x_st = is_v ? a.v_st : a.k_st;
 
@@ -478,230 +525,337 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
 
   f32x16 o0[QB], o1[QB];
   // softmax state per query block: mc = -(reference of the exponent, log2 domain) so that a probability is
-  // 2^(c2 * logit + mc), and this lane's share of the row sum
-  float mc[QB], l[QB];
+  // 2^(c2 * logit + mc), and the row sums (layout: see row_sum)
+  float mc[QB];
+  f32x4 l[QB];
 #pragma unroll
   for (int cb = 0; cb < QB; ++cb) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) { o0[cb][r] = 0.f; o1[cb][r] = 0.f; }
-    mc[cb] = kNoReference;
-    l[cb] = 0.f;
+    l[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  // softmax of one query block over the 32 tokens of a half-step: masks tokens >= valid, exponentiates into
-  // packed bf16 and adds the row sums.  `hook(i)`, i = 0..3, is called before each quarter of the
-  // exponentials: the caller issues MFMAs there, so that the matrix pipe works underneath this arithmetic.
-  // The reference of the exponent is NOT the running row maximum: it stays where it is while the row sums
-  // stay below 2^kSumLog2 - probabilities above 1 are as exact as those below, in bf16 as in fp32 - and no
-  // maximum is computed at all on that path (half an instruction per logit saved).  Only when some row's sum
-  // passes the limit (or, the first time, when there is no reference yet: every finite logit then
-  // exponentiates to infinity) the block is redone the classical way: row maximum, new reference, sums and
-  // accumulators rescaled, probabilities recomputed.  The MFMAs of the hook belong to other blocks and are
-  // not repeated; this block's own PV product is issued by the caller after this function returns.
-  auto softmax_half = [&](f32x16& sv, u32x4 (&pb)[2], float& mcr, float& lsum, f32x16& oa, f32x16& ob, int tok0,
-                          int valid, auto&& hook) {
-    if (valid < tok0 + 32) {  // tokens past the end of the cache / of the frame
-      // (the limit passes through an opaque move so that the 16 compares stay inside this rarely
-      // taken branch instead of being hoisted into every tile)
-      int lim = valid - tok0;
-      asm volatile("" : "+s"(lim));
-      lim -= 8 * hh;
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  // Row sums on the matrix pipe: MFMA 16x16x32 of a 0/1 matrix with the packed probabilities - the ROUNDED ones, which
+  // the PV product sees.  Read as the B operand of that shape, lane group g = lane / 16 holds query 16 * (g & 1) + lane % 16;
+  // row i of the 0/1 matrix takes the groups of i's parity, so result rows of even (odd) index - registers 0, 2 (1, 3) of
+  // every lane - are the sums of query lane % 16 (16 + lane % 16) over both halves' tokens.
+  const uint32_t ones = (((lane & 15) ^ (lane >> 4)) & 1) ? 0u : 0x3f803f80u;
+  const u32x4 sum_rows = {ones, ones, ones, ones};
+  auto row_sum = [&](int cb) XSV_INLINE { return (lane & 16) ? l[cb][1] : l[cb][0]; };
+  // step i (0..3) of O^T += V^T P^T for one query block: token step i/2, channel half i%2
+  auto pv_step = [&](int cb, const bf16x8 (&vf)[2][2], const u32x4 (&pb)[2], int i) XSV_INLINE {
+    const int k2 = i >> 1;
+    const bf16x8 p = __builtin_bit_cast(bf16x8, pb[k2]);
+    if (!(i & 1)) l[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, sum_rows), p, l[cb], 0, 0, 0);
+    if (i & 1) o1[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[k2][1], p, o1[cb], 0, 0, 0);
+    else o0[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[k2][0], p, o0[cb], 0, 0, 0);
+  };
+  // logits of tokens past the end of the cache / of the frame
+  auto mask_tail = [&](f32x16& sv, int tok0, int valid) XSV_INLINE {
+    // (the limit passes through an opaque move so that the 16 compares stay where they are)
+    int lim = __builtin_amdgcn_readfirstlane(valid - tok0);
+    asm volatile("" : "+s"(lim));
+    lim -= 8 * hh;
 #pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (16 * (r >> 3) + (r & 7) >= lim) sv[r] = -INFINITY;
+    for (int r = 0; r < 16; ++r)
+      if (16 * (r >> 3) + (r & 7) >= lim) sv[r] = -INFINITY;
+  };
+  auto load_k = [&](bf16x8 (&kf)[4], int buf, int half) XSV_INLINE {
+    const uint16_t* lk = lds_k[buf] + krow * kLdsStride + 8 * hh;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) kf[ks] = *reinterpret_cast<const bf16x8*>(lk + 32 * half * kLdsStride + 16 * ks);
+  };
+  auto load_v = [&](bf16x8 (&vf)[2][2], int buf, int half) XSV_INLINE {
+    const uint16_t* lv = lds_v[buf] + j * kLdsStride + 8 * hh;
+#pragma unroll
+    for (int k2 = 0; k2 < 2; ++k2) {
+      vf[k2][0] = *reinterpret_cast<const bf16x8*>(lv + 32 * half + 16 * k2);
+      vf[k2][1] = *reinterpret_cast<const bf16x8*>(lv + 32 * kLdsStride + 32 * half + 16 * k2);
     }
-    float psum = lsum;
+  };
+  // step i (0..3) of S^T = K Q^T for one query block (contraction over 16 channels per step)
+  auto qk_step = [&](f32x16& sv, const bf16x8 (&kf)[4], int cb, int i) XSV_INLINE {
+    sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i], qf[cb][i], i == 0 ? zero : sv, 0, 0, 0);
+  };
+  auto row_max = [&](const f32x16& sv) XSV_INLINE {
+    float mx = fmaxf(fmaxf(sv[0], sv[1]), sv[2]);  // v_max3 chain
+#pragma unroll
+    for (int r = 3; r < 15; r += 2) mx = fmaxf(fmaxf(mx, sv[r]), sv[r + 1]);
+    return xhalf_max(fmaxf(mx, sv[15]));  // both lane halves of a row agree on it
+  };
+  // Probabilities of one query block over the 32 tokens of a half-step: registers r = 8*k2 .. 8*k2+7 of the logits become
+  // the packed B operand of token step k2.  `hook(i)`, i = 0..3, is called before each quarter: the caller issues MFMAs
+  // there, so that the matrix pipe works underneath this arithmetic.
+  auto softmax_half = [&](f32x16& sv, u32x4 (&pb)[2], float mcr, auto&& hook) XSV_INLINE {
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
       hook(q4);
 #pragma unroll
       for (int r = 4 * q4; r < 4 * q4 + 4; r += 2) {
-        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[r], c2, mcr));
-        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[r + 1], c2, mcr));
-        const uint32_t w = pack_bf16(p0, p1);
-        pb[r >> 3][(r >> 1) & 3] = w;  // registers r = 8*k2 .. 8*k2+7 are the B operand of token step k2
-        // row sum of the ROUNDED probabilities (what the PV product sees): v_dot2c_f32_bf16
-        psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), __builtin_bit_cast(bf16x2, 0x3f803f80u),
-                                               psum, false);
+        const float p0 = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(__builtin_fmaf(sv[r], c2, mcr)), 0.f, 1.f);
+        const float p1 = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(__builtin_fmaf(sv[r + 1], c2, mcr)), 0.f, 1.f);
+        pb[r >> 3][(r >> 1) & 3] = pack_bf16(p0, p1);
       }
     }
-    // prescribed issue order of this block, per quarter: its MFMAs spread between its 12 vector
-    // instructions (4 fma, 4 exp, 2 convert, 2 dot) - the MFMAs execute while the VALU works
-    constexpr int kMfmaPerQuarter = std::remove_reference_t<decltype(hook)>::kMfma;
-    if constexpr (kMfmaPerQuarter > 0) {
+    // prescribed issue order of this block, per quarter: its MFMAs spread between its 10 vector instructions (4 fma,
+    // 4 exp, 2 convert) - the MFMAs execute while the VALU works
+    using Hook = std::remove_reference_t<decltype(hook)>;
+    if constexpr (Hook::kMfma > 0) {
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
         // masks: 0x008 MFMA, 0x002 VALU (without transcendentals), 0x400 transcendental
-        if constexpr (kMfmaPerQuarter == 2) {
+        const int m = Hook::kMfma + (Hook::kSums && q4 % 2 == 0 ? 1 : 0);
+        if (m == 3) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+        } else if (m == 2) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
           __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
           __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
           __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);
-          __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
         } else {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
           __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
           __builtin_amdgcn_sched_group_barrier(0x400, 4, 0);
-          __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
         }
-      }
-    }
-    if (__builtin_expect(__any(!(psum <= kSumLimit)), 0)) {  // some row sum passed the limit (or is not finite): redo with a new reference
-      float mx = fmaxf(fmaxf(sv[0], sv[1]), sv[2]);  // v_max3 chain
-#pragma unroll
-      for (int r = 3; r < 15; r += 2) mx = fmaxf(fmaxf(mx, sv[r]), sv[r + 1]);
-      mx = xhalf_max(fmaxf(mx, sv[15]));  // both lane halves of a row agree on it
-      // new reference = max(old, row maximum of this half-step) in the log2 domain; rows whose tokens are all
-      // masked here keep theirs
-      const float ref_old = -mcr;
-      const float ref_new = fmaxf(ref_old, mx * c2);
-      const float alpha = __builtin_amdgcn_exp2f(ref_old - ref_new);  // 0 the first time (no reference yet)
-      lsum *= alpha;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) { oa[r] *= alpha; ob[r] *= alpha; }
-      mcr = -ref_new;
-      psum = lsum;
-#pragma unroll
-      for (int r = 0; r < 16; r += 2) {
-        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[r], c2, mcr));
-        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[r + 1], c2, mcr));
-        const uint32_t w = pack_bf16(p0, p1);
-        pb[r >> 3][(r >> 1) & 3] = w;
-        psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), __builtin_bit_cast(bf16x2, 0x3f803f80u),
-                                               psum, false);
       }
     }
     // keep this block's probabilities in this block (the compiler would otherwise sink the
     // exponentials down to their consumer, next to the MFMAs they are meant to overlap with)
     asm volatile("" : "+v"(pb[0]), "+v"(pb[1]));
-    lsum = psum;
   };
 
-  // one tile of 64 tokens held in LDS buffer `buf`, of which the first `valid` are real
-  auto compute = [&](int buf, int valid) {
-    if (n_cb == 0) return;
-    const uint16_t* lk = lds_k[buf] + krow * kLdsStride + 8 * hh;
-    const uint16_t* lv = lds_v[buf] + j * kLdsStride + 8 * hh;
-    auto load_k = [&](bf16x8 (&kf)[4], int half) {
+  // The references: row maxima over the first half-step of the range, which is in LDS buffer `buf`.
+  auto first_reference = [&](int buf, int valid) XSV_INLINE {
+    bf16x8 kf[4];
+    load_k(kf, buf, 0);
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) kf[ks] = *reinterpret_cast<const bf16x8*>(lk + 32 * half * kLdsStride + 16 * ks);
-    };
-    auto load_v = [&](bf16x8 (&vf)[2][2], int half) {
+    for (int cb = 0; cb < QB; ++cb) {
+      f32x16 sv;
 #pragma unroll
-      for (int k2 = 0; k2 < 2; ++k2) {
-        vf[k2][0] = *reinterpret_cast<const bf16x8*>(lv + 32 * half + 16 * k2);
-        vf[k2][1] = *reinterpret_cast<const bf16x8*>(lv + 32 * kLdsStride + 32 * half + 16 * k2);
-      }
-    };
-    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    // step i (0..3) of S^T = K Q^T for one query block (contraction over 16 channels per step)
-    auto qk_step = [&](f32x16& sv, const bf16x8 (&kf)[4], int cb, int i) {
-      sv = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i], qf[cb][i], i == 0 ? zero : sv, 0, 0, 0);
-    };
-    // step i (0..3) of O^T += V^T P^T for one query block: token step i/2, channel half i%2
-    auto pv_step = [&](int cb, const bf16x8 (&vf)[2][2], const u32x4 (&pb)[2], int i) {
-      const int k2 = i >> 1;
-      const bf16x8 p = __builtin_bit_cast(bf16x8, pb[k2]);
-      if (i & 1) o1[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[k2][1], p, o1[cb], 0, 0, 0);
-      else o0[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[k2][0], p, o0[cb], 0, 0, 0);
-    };
+      for (int i = 0; i < 4; ++i) qk_step(sv, kf, cb, i);
+      if (valid < 32) mask_tail(sv, 0, valid);
+      mc[cb] = -__builtin_fmaf(row_max(sv), c2, kHeadroom);
+    }
+  };
 
+  // One whole tile of 64 tokens held in LDS buffer `buf`, the references standing: straight-line code.
+  auto compute_tile = [&](int buf) XSV_INLINE {
+    bf16x8 kf[4], vf[2][2];
     if constexpr (QB == 2) {
       // Software pipeline over the two half-steps and the two query blocks A, B of the wave: every
       // block of softmax arithmetic has independent MFMAs issued inside it —
       //   SM(A,h):  S(B,h) [and O(B,h-1)]      SM(B,h):  O(A,h) [and S(A,h+1)]
       // Blocks past the end of the frame are computed on clamped rows and never stored.
-      bf16x8 kf[4], vf[2][2];
       f32x16 sA, sB;
       u32x4 pA[2], pB[2];
-      load_k(kf, 0);
+      load_k(kf, buf, 0);
 #pragma unroll
       for (int i = 0; i < 4; ++i) qk_step(sA, kf, 0, i);
-      load_v(vf, 0);
+      load_v(vf, buf, 0);
       // ---- half 0 ----
       // (wave priority falls as a wave advances through a tile: of the two waves that share a SIMD the one that is
       // behind is served first, so they stay within a block of each other and each one's MFMAs run under the
       // other's softmax arithmetic, instead of the older wave finishing its tile first and the younger one
       // then working through its own alone; measured 2.7 % on the kernel)
       __builtin_amdgcn_s_setprio(3);
-      softmax_half(sA, pA, mc[0], l[0], o0[0], o1[0], 0, valid, with_mfma<1>([&](int i) { qk_step(sB, kf, 1, i); }));
-      load_k(kf, 1);
+      softmax_half(sA, pA, mc[0], with_mfma<1, false>([&](int i) XSV_INLINE { qk_step(sB, kf, 1, i); }));
+      load_k(kf, buf, 1);
       __builtin_amdgcn_s_setprio(2);
-      softmax_half(sB, pB, mc[1], l[1], o0[1], o1[1], 0, valid, with_mfma<2>([&](int i) {
+      softmax_half(sB, pB, mc[1], with_mfma<2, true>([&](int i) XSV_INLINE {
         pv_step(0, vf, pA, i);
         qk_step(sA, kf, 0, i);
       }));
       // ---- half 1 ----
       __builtin_amdgcn_s_setprio(1);
-      softmax_half(sA, pA, mc[0], l[0], o0[0], o1[0], 32, valid, with_mfma<2>([&](int i) {
+      softmax_half(sA, pA, mc[0], with_mfma<2, true>([&](int i) XSV_INLINE {
         pv_step(1, vf, pB, i);
         qk_step(sB, kf, 1, i);
       }));
-      load_v(vf, 1);
+      load_v(vf, buf, 1);
       __builtin_amdgcn_s_setprio(0);
-      softmax_half(sB, pB, mc[1], l[1], o0[1], o1[1], 32, valid, with_mfma<1>([&](int i) { pv_step(0, vf, pA, i); }));
+      softmax_half(sB, pB, mc[1], with_mfma<1, true>([&](int i) XSV_INLINE { pv_step(0, vf, pA, i); }));
 #pragma unroll
       for (int i = 0; i < 4; ++i) pv_step(1, vf, pB, i);
     } else {
-      bf16x8 kf[4], vf[2][2];
-      load_k(kf, 0);
+      load_k(kf, buf, 0);
 #pragma unroll
       for (int half = 0; half < 2; ++half) {
-        if (32 * half >= valid) break;
         f32x16 sv;
 #pragma unroll
         for (int i = 0; i < 4; ++i) qk_step(sv, kf, 0, i);
-        load_v(vf, half);
-        if (half == 0 && valid > 32) load_k(kf, 1);
+        load_v(vf, buf, half);
+        if (half == 0) load_k(kf, buf, 1);
         u32x4 pw[2];
-        softmax_half(sv, pw, mc[0], l[0], o0[0], o1[0], 32 * half, valid, with_mfma<0>([](int) {}));
+          softmax_half(sv, pw, mc[0], with_mfma<0, false>([](int) XSV_INLINE {}));
 #pragma unroll
         for (int i = 0; i < 4; ++i) pv_step(0, vf, pw, i);
       }
     }
   };
-  // Phase 1: this range's tiles of the packed cache; phase 2: its tiles of the frame.  Each phase is
-  // software pipelined on its own: a tile is fetched into registers while an earlier one is
-  // computed, then converted into a free LDS buffer.
+
+  // references of one block raised from -mc[cb] to `ref`: its accumulators and sums rescaled
+  auto rescale = [&](int cb, float ref) XSV_INLINE {
+    const float alpha = __builtin_amdgcn_exp2f(-mc[cb] - ref);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { o0[cb][r] *= alpha; o1[cb][r] *= alpha; }
+    const float a0 = __shfl(alpha, lane & 15), a1 = __shfl(alpha, (lane & 15) + 16);  // (layout of the row sums)
+    l[cb][0] *= a0; l[cb][1] *= a1; l[cb][2] *= a0; l[cb][3] *= a1;
+    mc[cb] = -ref;
+  };
+  // A tile of which the first `valid` tokens are real (a ragged last tile), one block after the other, with references that
+  // follow the running row maxima.
+  auto compute_tile_ragged = [&](int buf, int valid) XSV_INLINE {
+    for (int half = 0; half < 2 && 32 * half < valid; ++half) {
+      bf16x8 kf[4], vf[2][2];
+      load_k(kf, buf, half);
+      load_v(vf, buf, half);
+#pragma unroll
+      for (int cb = 0; cb < QB; ++cb) {
+        f32x16 sv;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) qk_step(sv, kf, cb, i);
+        mask_tail(sv, 32 * half, valid);
+        rescale(cb, fmaxf(-mc[cb], __builtin_fmaf(row_max(sv), c2, kHeadroom)));
+        u32x4 pw[2];
+        softmax_half(sv, pw, mc[cb], with_mfma<0, false>([](int) XSV_INLINE {}));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) pv_step(cb, vf, pw, i);
+      }
+    }
+  };
+  // After a full tile: rows whose sum has reached 1 - probabilities of this tile may have been clamped - get a new reference.
+  // The tile's contribution is taken out again (the same products with the sign of P turned; not needed where the tile's
+  // largest logit makes everything before it vanish below fp32), accumulators and sums are rescaled, and the tile is added
+  // with the new reference.  Rare: a logit 60 powers of two above everything before it.
+  auto raise_references = [&](int buf) XSV_INLINE {
+#pragma unroll
+    for (int cb = 0; cb < QB; ++cb) {
+      const bool over = row_sum(cb) >= 1.0f;
+      if (!__any(over)) continue;
+      f32x16 s0, s1;
+      {
+        bf16x8 kf[4];
+        load_k(kf, buf, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) qk_step(s0, kf, cb, i);
+        load_k(kf, buf, 1);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) qk_step(s1, kf, cb, i);
+      }
+      const float top = fmaxf(row_max(s0), row_max(s1)) * c2;  // log2 domain
+      auto add_tile = [&](float mcr, uint32_t sign) XSV_INLINE {
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          bf16x8 vf[2][2];
+          load_v(vf, buf, half);
+          u32x4 pw[2];
+          softmax_half(half == 0 ? s0 : s1, pw, over ? mcr : -INFINITY, with_mfma<0, false>([](int) XSV_INLINE {}));
+#pragma unroll
+          for (int i = 0; i < 8; ++i) pw[i >> 2][i & 3] ^= sign;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) pv_step(cb, vf, pw, i);
+        }
+      };
+      if (__any(over && top + mc[cb] < 40.0f)) add_tile(mc[cb], 0x80008000u);
+      rescale(cb, over ? fmaxf(top, -mc[cb]) + kHeadroom : -mc[cb]);
+      add_tile(mc[cb], 0u);
+    }
+  };
+  auto some_row_over = [&]() XSV_INLINE {
+    float top = fmaxf(l[0][0], l[0][1]);
+    if constexpr (QB == 2) top = fmaxf(top, fmaxf(l[1][0], l[1][1]));
+    return __any(top >= 1.0f);
+  };
+
+  // This range's tiles: first its tiles of the packed cache, then its tiles of the frame.  In either phase a tile is
+  // fetched into registers while the one before it is computed, then converted into the free one of the two LDS buffers:
+  // one barrier per tile.  A ragged last tile (cache or frame) is computed outside of the loop over the full ones, which
+  // is straight-line code.  `first(buf, valid)`: before the first tile; `full(buf)`, `ragged(buf, valid)`: the tiles.
+  auto walk = [&](auto&& first, auto&& full, auto&& ragged) XSV_INLINE {
+    int cur = 0;
+    if (c_begin < c_end) {
+      constexpr bool kQuant = BITS != 16;
+      constexpr int kPrm = Stage<BITS, G, NH>::kPrm;
+      CacheRegs<BITS, G, NH> st;
+      PrmStage<BITS, G, NH> pst;
+      fetch_cache_tile<BITS, G, NH>(st, rp, c_begin, u);
+      if (kQuant && c_begin + 1 < c_end) fetch_params<BITS, G, NH>(pst, rp, c_begin + 1, u);
+      store_cache_tile<BITS, G, NH>(st, rp.lds, rp.ps + (size_t)c_begin * kPrm, rp.pz + (size_t)c_begin * kPrm, is_v, u);
+      if (kQuant && c_begin + 1 < c_end) store_params<BITS, G, NH>(pst, rp.prm + kPrmBlock, u);
+      no_loads_in_flight();
+      __syncthreads();
+      first(0, Tc - c_begin * kTile);
+      const int full_end = min(c_end, Tc / kTile);
+      for (int t = c_begin; t < full_end; ++t) {
+        // tile t is in lds[cur], the parameters of tile t + 1 in prm[cur^1]; everybody is done reading lds[cur^1] and prm[cur]
+        __syncthreads();
+        if (t + 1 < c_end) fetch_cache_tile<BITS, G, NH>(st, rp, t + 1, u);
+        if (kQuant && t + 2 < c_end) fetch_params<BITS, G, NH>(pst, rp, t + 2, u);
+        full(cur);
+        if (t + 1 < c_end) {
+          const float* prm = rp.prm + (cur ^ 1) * kPrmBlock;
+          store_cache_tile<BITS, G, NH>(st, rp.lds + (cur ^ 1) * kLdsTile, prm, prm + kPrm, is_v, u);
+        }
+        if (kQuant && t + 2 < c_end) store_params<BITS, G, NH>(pst, rp.prm + cur * kPrmBlock, u);
+        no_loads_in_flight();
+        cur ^= 1;
+      }
+      if (full_end < c_end) {
+        __syncthreads();
+        ragged(cur, Tc - full_end * kTile);
+        cur ^= 1;
+      }
+    }
+    if (f_begin < f_end) {
+      FrameRegs<NH> st;
+      const FrameRows fr = frame_rows(xh, x_st, n, is_v, u);
+      fetch_frame_tile<NH>(st, fr, is_v, f_begin);
+      store_frame_tile<NH>(st, rp.lds + cur * kLdsTile, is_v, u);  // lds[cur] was last read two barriers ago
+      no_loads_in_flight();
+      if (c_begin >= c_end) {
+        __syncthreads();
+        first(cur, n - f_begin * kTile);
+      }
+      const int full_end = min(f_end, n / kTile);
+      for (int t = f_begin; t < full_end; ++t) {
+        __syncthreads();
+        if (t + 1 < f_end) fetch_frame_tile<NH>(st, fr, is_v, t + 1);
+        full(cur);
+        if (t + 1 < f_end) store_frame_tile<NH>(st, rp.lds + (cur ^ 1) * kLdsTile, is_v, u);
+        no_loads_in_flight();
+        cur ^= 1;
+      }
+      if (full_end < f_end) {
+        __syncthreads();
+        ragged(cur, n - full_end * kTile);
+      }
+    }
+  };
   // the previous unit's last tile has been read by everybody (a workgroup's first unit has nothing to wait for, and a
   // barrier there would only make its waves wait for the last of them to be started)
   if (pos - (t_end - t_begin) != piece_first) __syncthreads();
-  int cur = 0;      // two LDS buffers, one barrier per tile
-  if (c_begin < c_end) {
-    Stage<BITS, G, NH> st;
-    fetch_cache_tile<BITS, G, NH>(st, rp, a.Tcap, c_begin, u);
-    store_cache_tile<BITS, G, NH>(st, rp.lds + cur * kLdsTile, u);
-    no_loads_in_flight();
-    for (int t = c_begin; t < c_end; ++t) {
-      __syncthreads();  // tile t is in lds[cur]; everybody is done reading lds[cur^1]
-      if (t + 1 < c_end) fetch_cache_tile<BITS, G, NH>(st, rp, a.Tcap, t + 1, u);
-      compute(cur, min(kTile, Tc - t * kTile));
-      if (t + 1 < c_end) store_cache_tile<BITS, G, NH>(st, rp.lds + (cur ^ 1) * kLdsTile, u);
-      no_loads_in_flight();
-      cur ^= 1;
-    }
-  }
-  if (f_begin < f_end) {
-    FrameStage<NH> st;
-    const FrameRows fr = frame_rows(xh, x_st, n, is_v, u);
-    fetch_frame_tile<NH>(st, fr, is_v, f_begin);
-    store_frame_tile<NH>(st, rp.lds + cur * kLdsTile, is_v, u);  // lds[cur] was last read two barriers ago
-    no_loads_in_flight();
-    for (int t = f_begin; t < f_end; ++t) {
-      __syncthreads();
-      if (t + 1 < f_end) fetch_frame_tile<NH>(st, fr, is_v, t + 1);
-      compute(cur, min(kTile, n - t * kTile));
-      if (t + 1 < f_end) store_frame_tile<NH>(st, rp.lds + (cur ^ 1) * kLdsTile, is_v, u);
-      no_loads_in_flight();
-      cur ^= 1;
-    }
-  }
+  walk([&](int buf, int valid) XSV_INLINE { if (n_cb > 0) first_reference(buf, valid); },
+       [&](int buf) XSV_INLINE {
+         if (n_cb == 0) return;
+         compute_tile(buf);
+         if (__builtin_expect(some_row_over(), 0)) raise_references(buf);
+       },
+       [&](int buf, int valid) XSV_INLINE { if (n_cb > 0) compute_tile_ragged(buf, valid); });
 
   // accumulator register r of o0 (o1) is channel 8*(r/4) + 4*hh + r%4 (+32) of the lane's query row
 #pragma unroll
   for (int cb = 0; cb < QB; ++cb) {
     const int q_row = q_row0 + 32 * cb + j;
-    const float lsum = l[cb] + __shfl_xor(l[cb], 32);  // the two lane halves saw disjoint tokens
+    const float lsum = row_sum(cb);
     if (q_row >= n) continue;  // (both lanes of a row leave together, so the lane exchange below stays paired)
     if (whole) {
       const float inv = 1.0f / lsum;

@@ -156,6 +156,37 @@ def test_frame_attention_matches_oracle(H, n, splits):
     ctx.destroy()
 
 
+@pytest.mark.parametrize("variant", [0, 1, 2, 3])
+@pytest.mark.parametrize("jump", [30.0, 59.0, 61.0, 140.0])
+def test_frame_attention_when_the_softmax_reference_has_to_move(variant, jump):
+    """A key `jump` powers of two above all keys before it, for every other query row (the rest of the wave's rows keep
+    their reference): inside the first tile, in a later one, twice in a row, and in a ragged last tile - below and above
+    the 60 powers of two of headroom the kernel starts a range with."""
+    n, H = 64 * 4 + 17, 3
+    g = torch.Generator().manual_seed(int(jump))
+    q = torch.zeros((H, n, 64))
+    q[:, ::2, 0] = 8.0
+    q[:, :, 1:] = 0.25 * torch.randn((H, n, 63), generator=g)
+    k = 0.5 * torch.randn((H, n, 64), generator=g)
+    step = jump / (8.0 * 0.125 * 1.4426950408889634)            # q.k / 8 * log2(e) of channel 0 = jump
+    k[:, :, 0] = 0.0
+    for h, places in enumerate(([40], [70, 199], [130, n - 3])):
+        for i, t in enumerate(places):
+            k[h, t, 0] = step * (i + 1)
+    v = torch.randn((H, n, 64), generator=g)
+    q, k, v = (x.to(torch.bfloat16).to(DEV) for x in (q, k, v))
+    ctx = xsv.Context(1, H, 64, n, 5, 4 * n, 4, 64)
+    ctx.set_attend_variant(variant)
+    ctx.set_attend_splits(1, 1)
+    out = ctx.frame_attend(q, k, v).double()
+    ctx.destroy()
+    qd, kd, vd = q.double(), k.double(), v.double()
+    want = torch.matmul(torch.softmax(torch.matmul(qd, kd.transpose(1, 2).contiguous()) / 8.0, -1), vd)
+    err = out - want
+    # bf16 probabilities and outputs: each 2^-9 relative, so a value of magnitude <= 4.5 is off by at most 2 * 2^-9 * 4.5
+    assert err.abs().max() <= 2e-2 and err.norm() <= 1e-2 * want.norm()
+
+
 def test_measured_peaks_are_plausible():
     """The library's two yardsticks: an MFMA-only loop and a streaming copy, against the published peaks."""
     mfma, copy = xsv.measure_peaks()
