@@ -185,7 +185,7 @@ int xsv_cache_import(xsv_ctx* ctx, int layer, int32_t T, int32_t frames_seen, co
  * length each, [H][n_scores] and [H][n_keep]). */
 int xsv_last_selection(xsv_ctx* ctx, int layer, int32_t* n_scores, float* scores, int32_t* n_keep, int32_t* keep);
 
-/* ---- stateless kernels (DEVICE pointers; synchronous: they allocate temporaries and wait) ------- */
+/* ---- stateless kernels (DEVICE pointers; synchronous: they wait; xsv_score allocates a temporary) - */
 
 /* Sec. 3.3 quantizers on a plain bf16 tensor [H][T][64] (contiguous).  Outputs canonical:
  * codes uint8 [H][T][64]; keys: scale, zero float [H][ceil(T/G)][64]; values: [H][T][64/G]. */

@@ -1,6 +1,6 @@
 // Gather by the keep list + dimension-adaptive quantization of the whole retained cache
 // (paper Sec. 3.3: keys per channel over groups of G kept tokens, values per token over groups of G
-// channels), and the canonical unpack used by export and by the stateless entry points.  gfx950.
+// channels), the stateless quantizers, and the canonical unpack used by export.  gfx950.
 //
 // requant_kernel: one workgroup per (block of 64 new cache positions, head, layer), 256 threads,
 // thread = (token tid/4 of the block, channel quarter tid%4 = 16 channels).
@@ -387,6 +387,149 @@ hipError_t launch_requant(const RequantArgs& a, hipStream_t stream) {
   else if (bits == 2 && G == 32) hipLaunchKernelGGL((requant_kernel<2, 32, true>), grid, dim3(256), 0, stream, a);
   else return hipErrorInvalidValue;
   return hipGetLastError();
+}
+
+// ---- the stateless quantizers ------------------------------------------------------------------------
+// A plain bf16 tensor [H][T][64] straight to canonical codes (a byte each), scales and zero points: one workgroup per
+// (block of 64 tokens, head), thread = (token tid/4, 16 channels), one read of the tensor and one write of the result.
+// The arithmetic, the order of every min / max included (a group of zeros of both signs keeps the sign that the
+// re-quantization gives it), is requant_kernel's.  Bound: memory, in principle - at 16 heads x 4096 tokens a launch moves
+// 13 MB and takes less time than launching it and waiting for it (the calls are synchronous).  Keys and values of that
+// size took 5.2 ms as a throw-away context that was filled, re-quantized and unpacked (its allocations and its first fill).
+// `wide`: the codes' address allows 16-byte stores (any address is accepted).
+__device__ __forceinline__ void load_row16(const uint16_t* p, float* x) {
+  const uint4* p4 = reinterpret_cast<const uint4*>(p);
+  const uint4 v0 = p4[0], v1 = p4[1];
+  const uint32_t ww[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+#pragma unroll
+  for (int e = 0; e < 8; ++e) { x[2 * e] = bf16_lo(ww[e]); x[2 * e + 1] = bf16_hi(ww[e]); }
+}
+
+__device__ __forceinline__ void store_codes16(uint8_t* out, const uint32_t* code, bool wide) {
+  if (wide) {
+    uint32_t w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = code[4 * i] | (code[4 * i + 1] << 8) | (code[4 * i + 2] << 16) | (code[4 * i + 3] << 24);
+    *reinterpret_cast<uint4*>(out) = make_uint4(w[0], w[1], w[2], w[3]);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) out[e] = (uint8_t)code[e];
+  }
+}
+
+template <int BITS, int G>
+__global__ __launch_bounds__(256) void quantize_keys_kernel(const QuantizeArgs a) {
+  constexpr int kKGroups = kTile / G;
+  __shared__ float xk[kTile][kD + 1];
+  __shared__ float red_lo[4][kD], red_hi[4][kD];
+  __shared__ float gs[kKGroups][kD], gz[kKGroups][kD], gy[kKGroups][kD];
+  __shared__ int k_unsafe;
+  const int u = blockIdx.x, h = blockIdx.y, tid = threadIdx.x, r = tid >> 2, cq = tid & 3;
+  const int nv = min(kTile, a.T - u * kTile);
+  const size_t row = (size_t)h * a.T + (size_t)u * kTile + r;
+  if (tid == 0) k_unsafe = 0;
+  float x[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) x[e] = 0.f;
+  if (r < nv) load_row16(a.x + row * kD + cq * 16, x);
+#pragma unroll
+  for (int e = 0; e < 16; ++e) xk[r][cq * 16 + e] = x[e];
+  __syncthreads();
+  {
+    const int c = tid & 63, part = tid >> 6;
+    float lo = INFINITY, hi = -INFINITY;
+    for (int i = part * 16; i < min(nv, part * 16 + 16); ++i) {
+      lo = fminf(lo, xk[i][c]);
+      hi = fmaxf(hi, xk[i][c]);
+    }
+    red_lo[part][c] = lo;
+    red_hi[part][c] = hi;
+  }
+  __syncthreads();
+  if (tid < kKGroups * kD) {
+    const int c = tid & 63, gi = tid >> 6;
+    constexpr int parts = 4 / kKGroups;
+    if (gi * G < nv) {
+      float lo = red_lo[gi * parts][c], hi = red_hi[gi * parts][c];
+#pragma unroll
+      for (int p = 1; p < parts; ++p) {
+        lo = fminf(lo, red_lo[gi * parts + p][c]);
+        hi = fmaxf(hi, red_hi[gi * parts + p][c]);
+      }
+      const QParam q = group_param(lo, hi, BITS);
+      gs[gi][c] = q.s;
+      gz[gi][c] = q.z;
+      gy[gi][c] = q.y;
+      if (!q.safe) k_unsafe = 1;
+      const size_t gidx = ((size_t)h * ((a.T + G - 1) / G) + (size_t)u * kKGroups + gi) * kD + c;
+      a.scale[gidx] = q.s;
+      a.zero[gidx] = q.z;
+    }
+  }
+  __syncthreads();
+  if (r >= nv) return;
+  const int gi = r / G;
+  uint32_t code[16];
+  if (!k_unsafe) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) code[e] = quant_code_fast(x[e], gs[gi][cq * 16 + e], gy[gi][cq * 16 + e], gz[gi][cq * 16 + e], BITS);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) code[e] = quant_code(x[e], gs[gi][cq * 16 + e], gz[gi][cq * 16 + e], BITS);
+  }
+  store_codes16(a.codes + row * kD + cq * 16, code, a.wide);
+}
+
+template <int BITS, int G>
+__global__ __launch_bounds__(256) void quantize_values_kernel(const QuantizeArgs a) {
+  const int h = blockIdx.y, tid = threadIdx.x, r = tid >> 2, cq = tid & 3;
+  const bool valid = (long long)blockIdx.x * kTile + r < a.T;
+  const size_t row = (size_t)h * a.T + (size_t)blockIdx.x * kTile + r;
+  float x[16];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) x[e] = 0.f;
+  if (valid) load_row16(a.x + row * kD + cq * 16, x);
+  float lo = x[0], hi = x[0];
+#pragma unroll
+  for (int e = 1; e < 16; ++e) { lo = fminf(lo, x[e]); hi = fmaxf(hi, x[e]); }
+  lo = fminf(lo, __shfl_xor(lo, 1));
+  hi = fmaxf(hi, __shfl_xor(hi, 1));
+  if (G == 64) {
+    lo = fminf(lo, __shfl_xor(lo, 2));
+    hi = fmaxf(hi, __shfl_xor(hi, 2));
+  }
+  const QParam q = group_param(lo, hi, BITS);
+  uint32_t code[16];
+  if (__all(q.safe)) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) code[e] = quant_code_fast(x[e], q.s, q.y, q.z, BITS);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) code[e] = quant_code(x[e], q.s, q.z, BITS);
+  }
+  if (!valid) return;
+  if ((cq * 16) % G == 0) {
+    const size_t gidx = row * (kD / G) + (cq * 16) / G;
+    a.scale[gidx] = q.s;
+    a.zero[gidx] = q.z;
+  }
+  store_codes16(a.codes + row * kD + cq * 16, code, a.wide);
+}
+
+template <int BITS, int G>
+static hipError_t launch_quantize_t(const QuantizeArgs& a, bool keys, hipStream_t stream) {
+  const dim3 grid((a.T + kTile - 1) / kTile, a.H);
+  if (keys) hipLaunchKernelGGL((quantize_keys_kernel<BITS, G>), grid, dim3(256), 0, stream, a);
+  else hipLaunchKernelGGL((quantize_values_kernel<BITS, G>), grid, dim3(256), 0, stream, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_quantize_plain(const QuantizeArgs& a, int bits, int G, bool keys, hipStream_t stream) {
+  if (bits == 4 && G == 64) return launch_quantize_t<4, 64>(a, keys, stream);
+  if (bits == 4 && G == 32) return launch_quantize_t<4, 32>(a, keys, stream);
+  if (bits == 2 && G == 64) return launch_quantize_t<2, 64>(a, keys, stream);
+  if (bits == 2 && G == 32) return launch_quantize_t<2, 32>(a, keys, stream);
+  return hipErrorInvalidValue;
 }
 
 // ---- canonical unpack: thread per (head, token, channel) -------------------------------------------

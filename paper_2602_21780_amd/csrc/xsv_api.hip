@@ -1026,7 +1026,7 @@ int xsv_last_selection(xsv_ctx* ctx, int layer, int32_t* n_scores, float* scores
   return XSV_OK;
 }
 
-// ---- stateless entry points: a throw-away one-layer context around the same kernels ----------------
+// ---- stateless entry points ---------------------------------------------------------------------------
 
 static int quantize_plain(void* hip_stream, const void* x, int H, int T, int d, int bits, int G, void* codes, float* scale,
                           float* zero, bool keys) {
@@ -1034,26 +1034,19 @@ static int quantize_plain(void* hip_stream, const void* x, int H, int T, int d, 
   if (d != kD) return XSV_ERR_UNSUPPORTED;
   if (bits != 2 && bits != 4) return XSV_ERR_ARG;
   if (G != 32 && G != 64) return XSV_ERR_UNSUPPORTED;
-  xsv_config c{};
-  c.n_layers = 1; c.n_heads = H; c.head_dim = d; c.tokens_per_frame = T; c.n_special = 0; c.budget = 0;
-  c.kv_bits = bits; c.group_size = G; c.pool_size = 1; c.max_frames = 1;
-  xsv_ctx* ctx = nullptr;
-  int rc = xsv_create(&c, hip_stream, &ctx);
-  if (rc != XSV_OK) return rc;
-  // the whole tensor is "the current frame" of an empty cache: keep everything, quantize
-  const xsv_tensor t{x, (int64_t)T * d, d};
-  ctx->layers[0].phase = kAttended;
-  rc = do_score_prune(ctx, 0, 1, nullptr);
-  if (rc == XSV_OK) rc = do_quantize(ctx, 0, 1, &t, &t);
-  if (rc == XSV_OK) {
-    UnpackArgs u{};
-    u.pool = ctx->pool; u.buf = ctx->layers[0].buf; u.layer = 0; u.T = T;
-    if (keys) { u.k_codes = static_cast<uint8_t*>(codes); u.k_scale = scale; u.k_zero = zero; }
-    else { u.v_codes = static_cast<uint8_t*>(codes); u.v_scale = scale; u.v_zero = zero; }
-    if (launch_unpack(u, ctx->stream) != hipSuccess) rc = XSV_ERR_HIP;
-  }
-  xsv_destroy(ctx);  // synchronizes
-  return rc;
+  if (T > (1 << 24) || H > (1 << 16)) return XSV_ERR_UNSUPPORTED;  // the limits of a one-layer cache of this size
+  if (reinterpret_cast<uintptr_t>(x) % 16 != 0) return XSV_ERR_ARG;
+  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  QuantizeArgs a{};
+  a.x = static_cast<const uint16_t*>(x);
+  a.codes = static_cast<uint8_t*>(codes);
+  a.scale = scale;
+  a.zero = zero;
+  a.H = H;
+  a.T = T;
+  a.wide = reinterpret_cast<uintptr_t>(codes) % 16 == 0;
+  if (launch_quantize_plain(a, bits, G, keys, stream) != hipSuccess) return XSV_ERR_HIP;
+  return hipStreamSynchronize(stream) == hipSuccess ? XSV_OK : XSV_ERR_HIP;
 }
 
 int xsv_quantize_k(void* hip_stream, const void* k_bf16, int H, int T, int d, int bits, int G, void* codes_u8,

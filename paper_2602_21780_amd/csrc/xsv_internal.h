@@ -202,6 +202,18 @@ struct RequantArgs {
 hipError_t launch_requant(const RequantArgs& a, hipStream_t stream);
 hipError_t launch_zero_bytes(uint8_t* p, size_t n, hipStream_t stream);  // a fill kernel (no memset node)
 
+// A plain tensor [H][T][64] quantized to canonical codes, scales and zero points (keys: groups of G tokens per channel;
+// values: groups of G channels per token).  H <= 65536 (grid.y), x 16-byte aligned.
+struct QuantizeArgs {
+  const uint16_t* x;
+  uint8_t* codes;  // [H][T][64]
+  float* scale;    // keys [H][ceil(T/G)][64], values [H][T][64/G]
+  float* zero;
+  int H, T;
+  bool wide;  // codes is 16-byte aligned
+};
+hipError_t launch_quantize_plain(const QuantizeArgs& a, int bits, int G, bool keys, hipStream_t stream);
+
 // Canonical (one code per byte, untransposed) copies of one layer buffer → device arrays.
 struct UnpackArgs {
   CachePool pool;

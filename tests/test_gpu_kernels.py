@@ -98,6 +98,33 @@ def test_quantize_extreme_magnitudes_next_to_ordinary_groups(bits):
             assert np.array_equal(codes.cpu().numpy(), rc)
 
 
+@pytest.mark.parametrize("bits,G,T", [(4, 64, 130), (4, 32, 95), (2, 64, 64), (2, 32, 33)])
+def test_cache_of_one_frame_equals_the_stateless_quantizers(bits, G, T):
+    """The re-quantization of a context's cache and the stateless quantizers are two kernels: same codes, scales and zero
+    points, over ordinary groups, groups that need the division (extreme magnitudes) and constant ones, ragged last groups
+    - and into a codes buffer of odd address, which takes no wide stores."""
+    H = 3
+    x = randn_bf16((H, T, 64), 5 * T + bits, 1.5, outliers=(3, 40)).float()
+    x[0, :, 7] *= 1e30
+    x[1, 3, :] *= 1e-30
+    x[2, :, 9] = -2.5
+    x[2, 5, :] = 0.0
+    x = x.to(torch.bfloat16)
+    ctx = xsv.Context(1, H, 64, T, 0, 4 * T, bits, G)
+    ctx.step(0, x, x, x)
+    dump = ctx.cache_export(0)
+    ctx.destroy()
+    for name, fn, got in (("xsv_quantize_k", xsv.quantize_k, (dump.k_codes, dump.k_scale, dump.k_zero)),
+                          ("xsv_quantize_v", xsv.quantize_v, (dump.v_codes, dump.v_scale, dump.v_zero))):
+        codes, scale, zero = fn(x, bits, G)
+        for a, b in zip((codes, scale, zero), got):
+            assert np.array_equal(a.cpu().numpy(), b)
+        odd = torch.zeros(codes.numel() + 3, dtype=torch.uint8, device=DEV)
+        rc = getattr(xsv.lib(), name)(None, x.data_ptr(), H, T, 64, bits, G, odd.data_ptr() + 1, scale.data_ptr(), zero.data_ptr())
+        assert rc == xsv.XSV_OK
+        assert torch.equal(odd[1:1 + codes.numel()], codes.reshape(-1)) and odd[0] == 0 and not odd[1 + codes.numel():].any()
+
+
 @pytest.mark.parametrize("H,n,n_s,P,g", [(2, 64, 5, 192, 16), (16, 1374, 5, 2722, 16), (3, 37, 5, 70, 4), (1, 21, 0, 1, 1),
                                          (20, 150, 5, 333, 16), (37, 90, 3, 100, 7)])
 def test_score_matches_oracle(H, n, n_s, P, g):
