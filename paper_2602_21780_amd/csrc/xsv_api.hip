@@ -69,7 +69,7 @@ struct xsv_ctx {
   std::vector<hipEvent_t> chain_events;  // triples on the chain's stream: before score, after select, after re-quantize
   size_t chain_used = 0;
   int frame_tile_cost = 95;  // cost of a key tile of the frame's own rows in percent of a cache tile's (attention range cut)
-  int short_pct = -1; // xsv_step: length of one extra, short key range per unit, in percent of a long one (0 = none, -1 = by overlap mode)
+  int short_pct = -1; // xsv_step: length of one extra, short key range per unit, in percent of a long one (0 = none, -1 = default)
   int side_cus = -1;  // compute units xsv_step leaves to the prune chain while attention runs (-1: by launch size)
   size_t part_rows = 0;  // rows the partial-output workspace holds
   int n_cu = 256;
@@ -296,9 +296,9 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
   AttendPlan plan = choose_grid(ctx, n_layers, a.Tc, splits_req, spare_cus);
   const int n_ct = (a.Tc + kTile - 1) / kTile, n_ft = (a.n + kTile - 1) / kTile, n_tiles = n_ct + n_ft;
   bool short_last = false;
-  // with deferred joins the chain only has to keep up, so the short range can be longer (the long ones shorter) than
-  // when every step waits for its chain before it returns
-  const int short_pct = ctx->short_pct >= 0 ? ctx->short_pct : (ctx->overlap == 2 ? 50 : 35);
+  // (24 layers of 16 heads x 1374 tokens, 4-bit budget 4096, us per frame at 0 / 20 / 35 / 50 / 65 %: deferred joins
+  // 1315 / 1319 / 1282 / 1300 / 1343, a join per step 1498 / 1497 / 1487 / 1605 / 1638)
+  const int short_pct = ctx->short_pct >= 0 ? ctx->short_pct : 35;
   if (splits_req <= 0 && spare_cus > 0 && short_pct > 0) {
     // beside the overlapped chain: the equal cut that leaves spare units, plus one short range per unit
     const int rows = attend_rows_per_workgroup(ctx->attend_variant);

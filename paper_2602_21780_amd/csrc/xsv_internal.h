@@ -66,15 +66,17 @@ struct LayerCache {
   int32_t* tok_index;
 };
 
+// (A 16-bit cache has no parameters: those four pointers are then meaningless, and nobody reads them.  No test for it here -
+// a kernel's first loads wait behind this.)
 __host__ __device__ inline LayerCache layer_cache(const CachePool& p, int buf, int layer) {
   const size_t i = p.slab_index(buf, layer);
   LayerCache c;
   c.kc = p.kc + i * p.code_slab();
   c.vc = p.vc + i * p.code_slab();
-  c.ks = p.ks ? p.ks + i * p.kparam_slab() : nullptr;
-  c.kz = p.kz ? p.kz + i * p.kparam_slab() : nullptr;
-  c.vs = p.vs ? p.vs + i * p.vparam_slab() : nullptr;
-  c.vz = p.vz ? p.vz + i * p.vparam_slab() : nullptr;
+  c.ks = p.ks + i * p.kparam_slab();
+  c.kz = p.kz + i * p.kparam_slab();
+  c.vs = p.vs + i * p.vparam_slab();
+  c.vz = p.vz + i * p.vparam_slab();
   c.tok_frame = p.tok_frame + i * p.tok_slab();
   c.tok_index = p.tok_index + i * p.tok_slab();
   return c;

@@ -677,3 +677,28 @@ def test_attention_timing_series():
     ctx.step(0, q[0], k[0], v[0])
     assert ctx.attend_times()[0] == 0                      # nothing is recorded while it is off
     ctx.destroy()
+
+
+@pytest.mark.parametrize("bits,G,value_mode", [(4, 64, 0), (4, 32, 1), (2, 64, 1), (2, 32, 0)])
+@pytest.mark.parametrize("n,budget", [(37, 90), (16, 50), (64, 200)])
+def test_requantized_cache_with_groups_that_need_the_division(bits, G, value_mode, n, budget):
+    """Rows of cache and frame inside one wave of 16 positions (n = 37: no wave begins where a frame does), ragged last
+    groups, and among the ordinary groups some whose quotients are too large for the fast rounding: a key channel and value
+    rows that are constant and huge (scale 1, quotients beyond 2^21), and a channel of tiny values.  The cache, bit for bit."""
+    H = 2
+    spec = CONFIGS[0].with_(name=f"div-n{n}", n_heads=H, tokens_per_frame=n, n_special=2, budget=budget, kv_bits=bits, group_size=G,
+                            n_layers=1, seed=61 + n)
+    ctx, st = parity.make_pair(spec, value_mode=value_mode)
+    src = FrameSource(spec, DEV)
+    for f in range(7):
+        q, k, v = (t[0].clone() for t in src.frame(f))
+        k[0, :, 7], q[:, :, 7] = 3.0e7, 0.0          # (no part in the logits or the scores)
+        k[1, :, 9] *= 2.0 ** -90
+        v[:, 3::5] = -5.0e6
+        keep, scores = parity.oracle_keep_preview(st, 0, to_u16(q), n, 2, spec.pool_size, budget)
+        ctx.step(0, q, k, v)
+        _, keep_gpu = ctx.last_selection(0)
+        parity.check_keep(keep_gpu, keep, scores, keep.shape[-1] - 2 * n, n)
+        st.step(0, to_u16(q), to_u16(k), to_u16(v), rows=np.array([0], np.int32), forced_keep=keep_gpu)
+        parity.compare_cache(ctx.cache_export(0), st.export(0), True)
+    ctx.destroy()
