@@ -22,8 +22,9 @@
 //   (gridDim.x = units * R): the host passes where each range begins, placed so that the ranges cost
 //   the same (a tile of the frame's own rows costs a little less than a cache tile, and the last
 //   range may be made short on purpose so that its compute units are free early for the kernels
-//   that run beside this one); the grid is permuted so that the query blocks of one (layer, head,
-//   range), which read the same tiles, run on one XCD and share its L2.  (b) Otherwise all units'
+//   that run beside this one); the grid is permuted so that a head's workgroups run on one XCD
+//   and share its L2: the query blocks of a range read the same tiles, the ranges of a query block the same
+//   queries, and the merge, permuted alike, finds the partials there.  (b) Otherwise all units'
 //   tiles form one line of n_units * n_tiles items cut into gridDim.x equal pieces, so that any
 //   number of workgroups gets the same amount of work; a piece may end one unit and begin the
 //   next, and the workgroup handles them one after the other.  In both forms a unit covered by one
@@ -444,9 +445,20 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   int f_unit = 0, f_range = 0, f_qb = 0, f_head = 0;
   if (a.xcd_ranges > 0) {
     const int xcd = wg & 7, slot = wg >> 3;
-    const int sq = slot / nqb, sr = slot - sq * nqb;
-    const int g = sq * 8 + xcd;  // (layer, head, key range) triple
-    const int gq = g / a.xcd_ranges, gr = g - gq * a.xcd_ranges;
+    int gq, gr, sr;  // (layer, head), key range, query block
+    if (a.xcd_heads) {  // all workgroups of a head on one XCD
+      const int per_head = a.xcd_ranges * nqb;
+      const int sq = slot / per_head, rest = slot - sq * per_head;
+      gq = sq * 8 + xcd;
+      gr = rest / nqb;
+      sr = rest - gr * nqb;
+    } else {
+      const int sq = slot / nqb;
+      sr = slot - sq * nqb;
+      const int g = sq * 8 + xcd;  // (layer, head, key range) triple
+      gq = g / a.xcd_ranges;
+      gr = g - gq * a.xcd_ranges;
+    }
     wg = (gq * nqb + sr) * a.xcd_ranges + gr;
     if (a.equal_ranges == a.xcd_ranges) {  // unit = wg / ranges, range = wg % ranges
       fast = true;
@@ -919,6 +931,10 @@ __global__ __launch_bounds__(256) void combine_kernel(const AttendArgs a) {
   int unit, S;
   if (a.equal_ranges > 0) {  // every unit is cut into the same number of ranges: x = unit
     unit = blockIdx.x;
+    if (a.xcd_heads) {  // the chunks of a head on the XCD that its partials were written on
+      const int slot = unit >> 3, sq = slot / nqb;
+      unit = (sq * 8 + (unit & 7)) * nqb + slot - sq * nqb;
+    }
     S = a.equal_ranges;
   } else {
     const int w = blockIdx.x + 1;

@@ -320,6 +320,10 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
     const int ranges = plan.n_wgs % n_units == 0 ? plan.n_wgs / n_units : 0;
     a.equal_ranges = (ranges > 1 && ranges <= kMaxPieces && ranges <= n_tiles) ? ranges : 0;
     a.xcd_ranges = (ranges > 0 && (ctx->cfg.n_heads * n_layers * ranges) % 8 == 0) ? ranges : 0;
+    // Whole heads to an XCD where they divide evenly; otherwise (head, range) pairs, so that at least the query blocks that
+    // read the same tiles meet.  (16 heads x 1374 tokens, budget 4096: pairs 1337 us per frame of 24 layers, heads 1320;
+    // frame-wise attention 23.6 and 23.1.)
+    a.xcd_heads = a.xcd_ranges > 0 && a.equal_ranges > 0 && (ctx->cfg.n_heads * n_layers) % 8 == 0;
     if (a.equal_ranges > 0) range_starts(n_ct, n_ft, a.equal_ranges, short_last ? short_pct : 100, ctx->frame_tile_cost, a.range_begin);
   }
   ctx->last_attend_wgs = plan.n_wgs;

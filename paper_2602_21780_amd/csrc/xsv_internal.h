@@ -146,6 +146,7 @@ struct AttendArgs {
   // so that the last one is deliberately short (see xsv_set_short_range)
   int32_t range_begin[17];
   int xcd_ranges;  // > 0: every unit is cut into this many key ranges and the grid is permuted for L2 sharing
+  int xcd_heads;   // with xcd_ranges: (layer, head) pairs rather than (layer, head, range) triples are dealt to the XCDs
   float qscale;  // softmax scale * log2(e)
 };
 struct AttendPlan {
