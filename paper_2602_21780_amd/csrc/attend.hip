@@ -59,6 +59,7 @@ constexpr int kLdsTile = 64 * kLdsStride;  // elements of one K (or V) tile in L
 // captured registers go through memory
 #define XSV_INLINE __attribute__((always_inline))
 constexpr float kNegBig = -1.0e30f;
+constexpr float kFar = 3.0e38f;  // above every finite logit in the log2 domain (their scale is below 0.2): references end here
 // A row's reference is put this many powers of two above its largest logit so far: probabilities start at 2^-60 and are
 // clamped to 1 by the exponential's own output modifier, so nothing overflows while the reference stands; it has to move only
 // when a row's sum reaches 1.  Probabilities down to 2^-66 of the row's largest stay normal numbers.
@@ -400,6 +401,10 @@ template <int BITS, int G, int NW, int QB, bool ONE_LAYER>
 __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   constexpr int NT = NW * 64, NH = NT / 2;
   constexpr int kRowsWG = 32 * QB * NW;  // query rows per workgroup
+  // The probabilities' clamp passes a NaN through (MODE.DX10_CLAMP, on by default, makes it 0: a NaN key would drop out of
+  // the softmax instead of showing in every row that attends to it).
+  constexpr int kModeReg = 1, kDx10ClampBit = 8;
+  __builtin_amdgcn_s_setreg(kModeReg | (kDx10ClampBit << 6), 0);
   {
     // The argument block is read field by field further down, each read a scalar load the next instructions wait
     // for, and at the start of a launch every one of them misses the scalar cache: several memory round trips in a
@@ -540,11 +545,16 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   // 2^(c2 * logit + mc), and the row sums (layout: see row_sum)
   float mc[QB];
   f32x4 l[QB];
+  // Rows whose output is NaN without a NaN key: a query with a NaN or an infinity, or a logit of +inf (bit = lane).  They go
+  // through the loop with finite probabilities and get their NaN at the end: a NaN probability would also reach the sum of
+  // the row 16 further (row_sum multiplies it by 0).
+  unsigned long long nan_rows[QB];
 #pragma unroll
   for (int cb = 0; cb < QB; ++cb) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) { o0[cb][r] = 0.f; o1[cb][r] = 0.f; }
     l[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    nan_rows[cb] = 0;
   }
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   // Row sums on the matrix pipe: MFMA 16x16x32 of a 0/1 matrix with the packed probabilities - the ROUNDED ones, which
@@ -654,8 +664,30 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
       f32x16 sv;
 #pragma unroll
       for (int i = 0; i < 4; ++i) qk_step(sv, kf, cb, i);
+      // (a query that is not finite has no finite logit: one of them tells whether to look at the queries themselves)
+      if (__builtin_expect(__any((__float_as_uint(sv[0]) & 0x7f800000u) == 0x7f800000u), 0)) {
+        bool bad = false;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          const u32x4 w = __builtin_bit_cast(u32x4, qf[cb][ks]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) bad = bad || (w[e] & 0x7f80u) == 0x7f80u || (w[e] & 0x7f800000u) == 0x7f800000u;
+        }
+        unsigned long long rows = __ballot(bad);
+        rows |= (rows >> 32) | (rows << 32);  // both halves of a row
+        nan_rows[cb] = rows;
+        const uint32_t keep = (rows >> lane) & 1 ? 0u : ~0u;
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          const u32x4 w = __builtin_bit_cast(u32x4, qf[cb][ks]);
+          qf[cb][ks] = __builtin_bit_cast(bf16x8, u32x4{w[0] & keep, w[1] & keep, w[2] & keep, w[3] & keep});
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) qk_step(sv, kf, cb, i);
+      }
       if (valid < 32) mask_tail(sv, 0, valid);
-      mc[cb] = -__builtin_fmaf(row_max(sv), c2, kHeadroom);
+      // (a row of which every logit here is -inf gets a reference below all others: the first one that is not raises it)
+      mc[cb] = -fminf(fmaxf(__builtin_fmaf(row_max(sv), c2, kHeadroom), kNegBig), kFar);
     }
   };
 
@@ -736,7 +768,9 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) qk_step(sv, kf, cb, i);
         mask_tail(sv, 32 * half, valid);
-        rescale(cb, fmaxf(-mc[cb], __builtin_fmaf(row_max(sv), c2, kHeadroom)));
+        const float top = __builtin_fmaf(row_max(sv), c2, kHeadroom);
+        nan_rows[cb] |= __ballot(top > kFar);
+        rescale(cb, fminf(fmaxf(-mc[cb], top), kFar));
         u32x4 pw[2];
         softmax_half(sv, pw, mc[cb], with_mfma<0, false>([](int) XSV_INLINE {}));
 #pragma unroll
@@ -764,6 +798,7 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
         for (int i = 0; i < 4; ++i) qk_step(s1, kf, cb, i);
       }
       const float top = fmaxf(row_max(s0), row_max(s1)) * c2;  // log2 domain
+      nan_rows[cb] |= __ballot(top > kFar);
       auto add_tile = [&](float mcr, uint32_t sign) XSV_INLINE {
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
@@ -778,7 +813,7 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
         }
       };
       if (__any(over && top + mc[cb] < 40.0f)) add_tile(mc[cb], 0x80008000u);
-      rescale(cb, over ? fmaxf(top, -mc[cb]) + kHeadroom : -mc[cb]);
+      rescale(cb, over ? fminf(fmaxf(top, -mc[cb]) + kHeadroom, kFar) : -mc[cb]);
       add_tile(mc[cb], 0u);
     }
   };
@@ -867,7 +902,7 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
 #pragma unroll
   for (int cb = 0; cb < QB; ++cb) {
     const int q_row = q_row0 + 32 * cb + j;
-    const float lsum = row_sum(cb);
+    const float lsum = __uint_as_float(__float_as_uint(row_sum(cb)) | ((nan_rows[cb] >> lane) & 1 ? 0x7fc00000u : 0u));
     if (q_row >= n) continue;  // (both lanes of a row leave together, so the lane exchange below stays paired)
     if (whole) {
       const float inv = 1.0f / lsum;

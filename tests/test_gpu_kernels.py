@@ -183,6 +183,40 @@ def test_frame_attention_matches_oracle(H, n, splits):
     ctx.destroy()
 
 
+@pytest.mark.parametrize("variant,splits", [(0, 1), (1, 2), (2, 1), (3, 2)])
+def test_frame_attention_of_nan_and_infinite_inputs(variant, splits):
+    """A NaN key (in a full and in a ragged tile) shows in every row of its head, a query with a NaN or an infinity in its own
+    row alone; a logit of +inf (in the first, a later and the ragged tile) makes its row NaN, one of -inf takes its key out of
+    the row - also where a range begins with such keys only."""
+    n, H = 64 * 4 + 17, 7
+    g = torch.Generator().manual_seed(variant)
+    q, k, v = (torch.randn((H, n, 64), generator=g) for _ in range(3))
+    q[:, :, 0] = 1.0
+    q[3:, 16:32, 0] = q[3:, 48:67, 0] = -1.0
+    q[4, :, 0] = -1.0
+    k[0, 100, 3] = float("nan")
+    k[1, n - 2, 3] = float("nan")
+    q[2, 5, 7] = float("nan")
+    q[2, 200, 60] = float("-inf")
+    k[3, 150, 0] = float("inf")
+    k[5, 3, 0] = float("inf")
+    k[6, n - 5, 0] = float("inf")
+    k[4, :40, 0] = float("inf")
+    q, k, v = (x.to(torch.bfloat16) for x in (q, k, v))
+    ctx = xsv.Context(1, H, 64, n, 5, 4 * n, 4, 64)
+    ctx.set_attend_variant(variant)
+    ctx.set_attend_splits(splits, splits)
+    out = ctx.frame_attend(q.to(DEV), k.to(DEV), v.to(DEV)).cpu().double()
+    ctx.destroy()
+    qd, kd, vd = q.double(), k.double(), v.double()
+    want = torch.matmul(torch.softmax(torch.matmul(qd, kd.transpose(1, 2).contiguous()) / 8.0, -1), vd)
+    assert torch.equal(out.isnan(), want.isnan())
+    assert [int(w.isnan().any(-1).sum()) for w in want] == [n, n, 2, n - 35, 0, n - 35, n - 35]
+    err = (out - want)[~want.isnan()]
+    # bf16 probabilities and outputs: each 2^-9 relative, so a value of magnitude <= 4.5 is off by at most 2 * 2^-9 * 4.5
+    assert err.abs().max() <= 2e-2
+
+
 @pytest.mark.parametrize("variant", [0, 1, 2, 3])
 @pytest.mark.parametrize("jump", [30.0, 59.0, 61.0, 140.0])
 def test_frame_attention_when_the_softmax_reference_has_to_move(variant, jump):
