@@ -18,7 +18,7 @@ COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-ta
 # bit-exact kernels: one rounding per operation, like the definition
 SOURCES = {
     "xsv_api.hip": [],
-    # plain v_max3 in the softmax (inputs are finite); MFMA results in VGPRs so the softmax reads them
+    # plain v_max3 in the softmax (NaN and infinities are told by their bits); MFMA results in VGPRs so the softmax reads them
     # without accumulator-register moves
     "attend.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form=1"],
     "score_select.hip": ["-ffp-contract=off"],

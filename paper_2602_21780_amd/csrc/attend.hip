@@ -40,7 +40,7 @@
 //   share a SIMD.  v_dot2c_f32_bf16 must stay out of this loop: it executes on the matrix pipe (beside a wave that issues
 //   MFMAs back to back it makes no progress at all), so row sums taken with it serialize MFMAs and softmax; they are MFMAs of
 //   their own here (row_sum).  At 16 heads, 1374 rows, 5470 keys, one key range per 512 rows: 1.88 -> 1.66 us per tile of a
-//   workgroup on the 4-bit cache; a bf16 cache grown by 16 frames of 1374 tokens, four layers: 7190 -> 5760 us.
+//   workgroup on the 4-bit cache; a bf16 cache grown by 16 frames of 1374 tokens, four layers: 7220 -> 5780 us.
 #include <cstddef>
 #include <type_traits>
 
