@@ -423,6 +423,7 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t lds_v[2][kLdsTile];
   constexpr int kPrmBlock = BITS == 16 ? 1 : 2 * Stage<BITS, G, NH>::kPrm;  // one tile's scales and zero points of one role
   __shared__ __attribute__((aligned(16))) float lds_prm[2][2][kPrmBlock];    // [role][buffer]
+  __shared__ int careful_pass[2];  // some wave asks for it (by the parity of the unit's number in this workgroup)
 
   const int H = a.H, n = a.n, Tc = a.Tc;
   const int nqb = (n + kRowsWG - 1) / kRowsWG;
@@ -494,6 +495,7 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
     if (!fast) f_unit = un;
   }
 
+  int parity = 0;
   for (long long pos = piece_first; pos < piece_end;) {
   // with equal ranges a piece lies inside one unit
   const int unit = a.equal_ranges > 0 ? f_unit : part.unit_of(pos);
@@ -545,17 +547,20 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   // 2^(c2 * logit + mc), and the row sums (layout: see row_sum)
   float mc[QB];
   f32x4 l[QB];
-  // Rows whose output is NaN without a NaN key: a query with a NaN or an infinity, or a logit of +inf (bit = lane).  They go
-  // through the loop with finite probabilities and get their NaN at the end: a NaN probability would also reach the sum of
-  // the row 16 further (row_sum multiplies it by 0).
+  // Rows whose output is NaN (bit = lane) although their probabilities are kept finite: for a logit of +inf, in the careful
+  // pass also for one that is NaN.  They get it at the end.
   unsigned long long nan_rows[QB];
+  auto clear = [&]() XSV_INLINE {
 #pragma unroll
-  for (int cb = 0; cb < QB; ++cb) {
+    for (int cb = 0; cb < QB; ++cb) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { o0[cb][r] = 0.f; o1[cb][r] = 0.f; }
-    l[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    nan_rows[cb] = 0;
-  }
+      for (int r = 0; r < 16; ++r) { o0[cb][r] = 0.f; o1[cb][r] = 0.f; }
+      l[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      nan_rows[cb] = 0;
+      mc[cb] = -kNegBig;
+    }
+  };
+  clear();
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   // Row sums on the matrix pipe: MFMA 16x16x32 of a 0/1 matrix with the packed probabilities - the ROUNDED ones, which
   // the PV product sees.  Read as the B operand of that shape, lane group g = lane / 16 holds query 16 * (g & 1) + lane % 16;
@@ -664,27 +669,6 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
       f32x16 sv;
 #pragma unroll
       for (int i = 0; i < 4; ++i) qk_step(sv, kf, cb, i);
-      // (a query that is not finite has no finite logit: one of them tells whether to look at the queries themselves)
-      if (__builtin_expect(__any((__float_as_uint(sv[0]) & 0x7f800000u) == 0x7f800000u), 0)) {
-        bool bad = false;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          const u32x4 w = __builtin_bit_cast(u32x4, qf[cb][ks]);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) bad = bad || (w[e] & 0x7f80u) == 0x7f80u || (w[e] & 0x7f800000u) == 0x7f800000u;
-        }
-        unsigned long long rows = __ballot(bad);
-        rows |= (rows >> 32) | (rows << 32);  // both halves of a row
-        nan_rows[cb] = rows;
-        const uint32_t keep = (rows >> lane) & 1 ? 0u : ~0u;
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-          const u32x4 w = __builtin_bit_cast(u32x4, qf[cb][ks]);
-          qf[cb][ks] = __builtin_bit_cast(bf16x8, u32x4{w[0] & keep, w[1] & keep, w[2] & keep, w[3] & keep});
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) qk_step(sv, kf, cb, i);
-      }
       if (valid < 32) mask_tail(sv, 0, valid);
       // (a row of which every logit here is -inf gets a reference below all others: the first one that is not raises it)
       mc[cb] = -fminf(fmaxf(__builtin_fmaf(row_max(sv), c2, kHeadroom), kNegBig), kFar);
@@ -755,9 +739,19 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
     l[cb][0] *= a0; l[cb][1] *= a1; l[cb][2] *= a0; l[cb][3] *= a1;
     mc[cb] = -ref;
   };
-  // A tile of which the first `valid` tokens are real (a ragged last tile), one block after the other, with references that
-  // follow the running row maxima.
-  auto compute_tile_ragged = [&](int buf, int valid) XSV_INLINE {
+  // Lanes that hold a NaN among these logits.  (Floats of this file are compiled as if none was NaN: they go through an
+  // opaque move first.)
+  auto nan_lanes = [&](f32x16& sv) XSV_INLINE {
+    asm volatile("" : "+v"(sv));
+    uint32_t top = 0;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) top = max(top, __float_as_uint(sv[r]) & 0x7fffffffu);
+    return __ballot(top > 0x7f800000u);
+  };
+  // A tile of which the first `valid` tokens are real, one block after the other, with references that follow the running
+  // row maxima: a ragged last tile, and every tile of the careful pass.  There NaN logits are taken out and their rows marked,
+  // so that they end in their own row.
+  auto compute_tile_slowly = [&](int buf, int valid, auto careful) XSV_INLINE {
     for (int half = 0; half < 2 && 32 * half < valid; ++half) {
       bf16x8 kf[4], vf[2][2];
       load_k(kf, buf, half);
@@ -768,6 +762,12 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) qk_step(sv, kf, cb, i);
         mask_tail(sv, 32 * half, valid);
+        if constexpr (careful) {
+          const unsigned long long lanes = nan_lanes(sv), rows = lanes | (lanes >> 32) | (lanes << 32);
+          nan_rows[cb] |= rows;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sv[r] = (rows >> lane) & 1 ? -INFINITY : sv[r];
+        }
         const float top = __builtin_fmaf(row_max(sv), c2, kHeadroom);
         nan_rows[cb] |= __ballot(top > kFar);
         rescale(cb, fminf(fmaxf(-mc[cb], top), kFar));
@@ -816,6 +816,16 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
       rescale(cb, over ? fminf(fmaxf(top, -mc[cb]) + kHeadroom, kFar) : -mc[cb]);
       add_tile(mc[cb], 0u);
     }
+  };
+  auto some_sum_is_nan = [&]() XSV_INLINE {
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < 2 * QB; ++i) {
+      uint32_t w = __float_as_uint(l[i >> 1][i & 1]);
+      asm volatile("" : "+v"(w));  // (see nan_lanes)
+      bad = bad || (w & 0x7fffffffu) > 0x7f800000u;
+    }
+    return __any(bad);
   };
   auto some_row_over = [&]() XSV_INLINE {
     float top = fmaxf(l[0][0], l[0][1]);
@@ -887,62 +897,89 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
       }
     }
   };
-  // the previous unit's last tile has been read by everybody (a workgroup's first unit has nothing to wait for, and a
-  // barrier there would only make its waves wait for the last of them to be started)
-  if (pos - (t_end - t_begin) != piece_first) __syncthreads();
+  auto write_rows = [&]() XSV_INLINE {
+    // accumulator register r of o0 (o1) is channel 8*(r/4) + 4*hh + r%4 (+32) of the lane's query row
+#pragma unroll
+    for (int cb = 0; cb < QB; ++cb) {
+      const int q_row = q_row0 + 32 * cb + j;
+      const float lsum = __uint_as_float(__float_as_uint(row_sum(cb)) | ((nan_rows[cb] >> lane) & 1 ? 0x7fc00000u : 0u));
+      if (q_row >= n) continue;  // (both lanes of a row leave together, so the lane exchange below stays paired)
+      if (whole) {
+        const float inv = 1.0f / lsum;
+        uint16_t* op = ly.out + ((size_t)h * n + q_row) * kD;
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const int c = 8 * q4 + 4 * hh;
+          *reinterpret_cast<uint2*>(op + c) = make_uint2(pack_bf16(o0[cb][4 * q4] * inv, o0[cb][4 * q4 + 1] * inv),
+                                                         pack_bf16(o0[cb][4 * q4 + 2] * inv, o0[cb][4 * q4 + 3] * inv));
+          *reinterpret_cast<uint2*>(op + 32 + c) = make_uint2(pack_bf16(o1[cb][4 * q4] * inv, o1[cb][4 * q4 + 1] * inv),
+                                                              pack_bf16(o1[cb][4 * q4 + 2] * inv, o1[cb][4 * q4 + 3] * inv));
+        }
+      } else {
+        // Partial of a cut unit, as fp16 mantissas under one power-of-two scale per query row (the
+        // row's largest magnitude maps into [0.5, 1): 11 bits below the row maximum, half the bytes of
+        // fp32).  Lane (j, hh) owns 32 channels of row j, in register order o0[0..15], o1[0..15], as
+        // four 16-byte pieces i; a block of 32 rows is stored [i][hh][j], so that every store
+        // instruction of the wave covers 1 KB of consecutive memory.
+        const int piece = a.equal_ranges > 0 ? my_range : wg - part.first_wg(unit);
+        const int nblk = (n + 31) / 32;
+        const size_t row = (((size_t)piece * a.n_layers + lb) * H + h) * n + q_row;
+        const size_t blk = (((size_t)piece * a.n_layers + lb) * H + h) * nblk + (q_row >> 5);
+        float amax = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) amax = fmaxf(amax, fmaxf(fabsf(o0[cb][r]), fabsf(o1[cb][r])));
+        amax = xhalf_max(amax);
+        const int e = __builtin_amdgcn_frexp_expf(amax);  // amax = f * 2^e, f in [0.5, 1)  (0 for amax == 0)
+        uint32_t hw[16];
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+          hw[r >> 1] = pack_f16(__builtin_amdgcn_ldexpf(o0[cb][r], -e), __builtin_amdgcn_ldexpf(o0[cb][r + 1], -e));
+          hw[8 + (r >> 1)] = pack_f16(__builtin_amdgcn_ldexpf(o1[cb][r], -e), __builtin_amdgcn_ldexpf(o1[cb][r + 1], -e));
+        }
+        uint4* op = reinterpret_cast<uint4*>(a.attn_o) + blk * 256 + hh * 32 + j;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) op[i * 64] = make_uint4(hw[4 * i], hw[4 * i + 1], hw[4 * i + 2], hw[4 * i + 3]);
+        if (hh == 0)
+          *reinterpret_cast<float4*>(a.attn_ml + row * 4) = make_float4(-mc[cb], lsum, __builtin_amdgcn_ldexpf(1.0f, e), 0.f);
+      }
+    }
+  };
+
+  if (tid == 0) careful_pass[parity] = 0;  // (barriers of the walk lie between this and anybody's setting it)
   walk([&](int buf, int valid) XSV_INLINE { if (n_cb > 0) first_reference(buf, valid); },
        [&](int buf) XSV_INLINE {
          if (n_cb == 0) return;
          compute_tile(buf);
          if (__builtin_expect(some_row_over(), 0)) raise_references(buf);
        },
-       [&](int buf, int valid) XSV_INLINE { if (n_cb > 0) compute_tile_ragged(buf, valid); });
-
-  // accumulator register r of o0 (o1) is channel 8*(r/4) + 4*hh + r%4 (+32) of the lane's query row
-#pragma unroll
-  for (int cb = 0; cb < QB; ++cb) {
-    const int q_row = q_row0 + 32 * cb + j;
-    const float lsum = __uint_as_float(__float_as_uint(row_sum(cb)) | ((nan_rows[cb] >> lane) & 1 ? 0x7fc00000u : 0u));
-    if (q_row >= n) continue;  // (both lanes of a row leave together, so the lane exchange below stays paired)
-    if (whole) {
-      const float inv = 1.0f / lsum;
-      uint16_t* op = ly.out + ((size_t)h * n + q_row) * kD;
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int c = 8 * q4 + 4 * hh;
-        *reinterpret_cast<uint2*>(op + c) = make_uint2(pack_bf16(o0[cb][4 * q4] * inv, o0[cb][4 * q4 + 1] * inv),
-                                                       pack_bf16(o0[cb][4 * q4 + 2] * inv, o0[cb][4 * q4 + 3] * inv));
-        *reinterpret_cast<uint2*>(op + 32 + c) = make_uint2(pack_bf16(o1[cb][4 * q4] * inv, o1[cb][4 * q4 + 1] * inv),
-                                                            pack_bf16(o1[cb][4 * q4 + 2] * inv, o1[cb][4 * q4 + 3] * inv));
+       [&](int buf, int valid) XSV_INLINE { if (n_cb > 0) compute_tile_slowly(buf, valid, std::false_type{}); });
+  // A row sum that is NaN - for a NaN key, a query that is not finite, a NaN product of finite numbers and infinities - has
+  // made the sum of the row 16 away NaN too (row_sum).  Then the tiles are walked once more, one at a time and every row on
+  // its own, and the rows are written again.  A wave cannot do that alone; the rows are written first so that this barrier is
+  // the last thing a workgroup does (it also says that everybody has read the unit's last tile).
+  if (n_cb > 0 && some_sum_is_nan() && lane == 0) careful_pass[parity] = 1;
+  write_rows();
+  __syncthreads();
+  if (__builtin_expect(__builtin_amdgcn_readfirstlane(careful_pass[parity]) != 0, 0)) {
+    clear();
+    for (int t = t_begin; t < t_end; ++t) {
+      if (t < n_ct) {
+        constexpr int kPrm = Stage<BITS, G, NH>::kPrm;
+        CacheRegs<BITS, G, NH> st;
+        fetch_cache_tile<BITS, G, NH>(st, rp, t, u);
+        store_cache_tile<BITS, G, NH>(st, rp.lds, rp.ps + (size_t)t * kPrm, rp.pz + (size_t)t * kPrm, is_v, u);
+      } else {
+        FrameRegs<NH> st;
+        fetch_frame_tile<NH>(st, frame_rows(xh, x_st, n, is_v, u), is_v, t - n_ct);
+        store_frame_tile<NH>(st, rp.lds, is_v, u);
       }
-    } else {
-      // Partial of a cut unit, as fp16 mantissas under one power-of-two scale per query row (the
-      // row's largest magnitude maps into [0.5, 1): 11 bits below the row maximum, half the bytes of
-      // fp32).  Lane (j, hh) owns 32 channels of row j, in register order o0[0..15], o1[0..15], as
-      // four 16-byte pieces i; a block of 32 rows is stored [i][hh][j], so that every store
-      // instruction of the wave covers 1 KB of consecutive memory.
-      const int piece = a.equal_ranges > 0 ? my_range : wg - part.first_wg(unit);
-      const int nblk = (n + 31) / 32;
-      const size_t row = (((size_t)piece * a.n_layers + lb) * H + h) * n + q_row;
-      const size_t blk = (((size_t)piece * a.n_layers + lb) * H + h) * nblk + (q_row >> 5);
-      float amax = 0.f;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) amax = fmaxf(amax, fmaxf(fabsf(o0[cb][r]), fabsf(o1[cb][r])));
-      amax = xhalf_max(amax);
-      const int e = __builtin_amdgcn_frexp_expf(amax);  // amax = f * 2^e, f in [0.5, 1)  (0 for amax == 0)
-      uint32_t hw[16];
-#pragma unroll
-      for (int r = 0; r < 16; r += 2) {
-        hw[r >> 1] = pack_f16(__builtin_amdgcn_ldexpf(o0[cb][r], -e), __builtin_amdgcn_ldexpf(o0[cb][r + 1], -e));
-        hw[8 + (r >> 1)] = pack_f16(__builtin_amdgcn_ldexpf(o1[cb][r], -e), __builtin_amdgcn_ldexpf(o1[cb][r + 1], -e));
-      }
-      uint4* op = reinterpret_cast<uint4*>(a.attn_o) + blk * 256 + hh * 32 + j;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) op[i * 64] = make_uint4(hw[4 * i], hw[4 * i + 1], hw[4 * i + 2], hw[4 * i + 3]);
-      if (hh == 0)
-        *reinterpret_cast<float4*>(a.attn_ml + row * 4) = make_float4(-mc[cb], lsum, __builtin_amdgcn_ldexpf(1.0f, e), 0.f);
+      __syncthreads();
+      if (n_cb > 0) compute_tile_slowly(0, min(kTile, t < n_ct ? Tc - t * kTile : n - (t - n_ct) * kTile), std::true_type{});
+      __syncthreads();
     }
+    write_rows();
   }
+  parity ^= 1;
   }  // units of this workgroup's piece
 
 }

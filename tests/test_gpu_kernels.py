@@ -183,6 +183,12 @@ def test_frame_attention_matches_oracle(H, n, splits):
     ctx.destroy()
 
 
+def cached_rows(ctx):
+    """Keys and values of layer 0's cache as attention sees them (the dequantized view), in double."""
+    d = ctx.cache_export(0)
+    return (torch.from_numpy(x.astype(np.int32) << 16).view(torch.float32).double() for x in (d.k_bf16, d.v_bf16))
+
+
 @pytest.mark.parametrize("variant,splits", [(0, 1), (1, 2), (2, 1), (3, 2)])
 def test_frame_attention_of_nan_and_infinite_inputs(variant, splits):
     """A NaN key (in a full and in a ragged tile) shows in every row of its head, a query with a NaN or an infinity in its own
@@ -215,6 +221,43 @@ def test_frame_attention_of_nan_and_infinite_inputs(variant, splits):
     err = (out - want)[~want.isnan()]
     # bf16 probabilities and outputs: each 2^-9 relative, so a value of magnitude <= 4.5 is off by at most 2 * 2^-9 * 4.5
     assert err.abs().max() <= 2e-2
+
+
+@pytest.mark.parametrize("variant,splits", [(0, 1), (1, 0), (2, 3), (3, 1), (3, 0)])
+@pytest.mark.parametrize("bits", [16, 4, 2])
+def test_nan_products_stay_in_their_rows(bits, variant, splits):
+    """Keys that are infinite in one channel, where some queries are 0, or in two, where some queries differ in sign: NaN
+    logits in those rows, -inf (or NaN, for a NaN key) in the others.  The first kind leaves every other row of the head as
+    if that key were absent - the rows 16 away included.  In a full and in the ragged tile of the frame, behind a cache whose
+    tiles the rows attend to as well."""
+    n, H = 64 * 2 + 17, 5
+    g = torch.Generator().manual_seed(7 * variant + bits)
+    q, k, v, k0, v0 = (torch.randn((H, n, 64), generator=g) for _ in range(5))
+    inf = float("inf")
+    q[:, :, :2] = -1.0
+    q[0, 5, 0] = q[0, 77, 0] = 0.0
+    k[0, 20, 0] = inf
+    q[1, 40, 1] = 1.0
+    k[1, 70, :2] = inf
+    q[2, 127, 0] = 0.0
+    k[2, n - 2, 0] = inf
+    k[3, 9, 30] = float("nan")
+    q[4, n - 1, 0] = 0.0
+    k[4, [3, 66, n - 1], 0] = inf
+    q, k, v, k0, v0 = (x.to(torch.bfloat16) for x in (q, k, v, k0, v0))
+    ctx = xsv.Context(1, H, 64, n, 0, 4 * n, bits, 64)
+    ctx.set_attend_variant(variant)
+    ctx.set_attend_splits(splits, splits)
+    ctx.step(0, q.to(DEV), k0.to(DEV), v0.to(DEV))
+    kc, vc = cached_rows(ctx)
+    out = ctx.step(0, q.to(DEV), k.to(DEV), v.to(DEV)).cpu().double()
+    ctx.destroy()
+    kd, vd = torch.cat([kc, k.double()], 1), torch.cat([vc, v.double()], 1)
+    want = torch.matmul(torch.softmax(torch.matmul(q.double(), kd.transpose(1, 2).contiguous()) / 8.0, -1), vd)
+    assert [w.isnan().any(-1).nonzero().flatten().tolist() for w in want] == [[5, 77], [40], [127], list(range(n)), [n - 1]]
+    assert torch.equal(out.isnan(), want.isnan())
+    # bf16 probabilities and outputs: each 2^-9 relative, so a value of magnitude <= 4.5 is off by at most 2 * 2^-9 * 4.5
+    assert (out - want)[~want.isnan()].abs().max() <= 2e-2
 
 
 @pytest.mark.parametrize("variant", [0, 1, 2, 3])
