@@ -782,6 +782,9 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   // The tile's contribution is taken out again (the same products with the sign of P turned; not needed where the tile's
   // largest logit makes everything before it vanish below fp32), accumulators and sums are rescaled, and the tile is added
   // with the new reference.  Rare: a logit 60 powers of two above everything before it.
+  // An infinity among the values makes that wrong - infinity minus infinity, and 0 times infinity in the rows that stay - so
+  // accumulators that are not finite ask for the careful pass, which takes nothing out.
+  bool take_out_failed = false;
   auto raise_references = [&](int buf) XSV_INLINE {
 #pragma unroll
     for (int cb = 0; cb < QB; ++cb) {
@@ -797,8 +800,8 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) qk_step(s1, kf, cb, i);
       }
-      const float top = fmaxf(row_max(s0), row_max(s1)) * c2;  // log2 domain
-      nan_rows[cb] |= __ballot(top > kFar);
+      const float most = fmaxf(row_max(s0), row_max(s1)) * c2;  // log2 domain
+      nan_rows[cb] |= __ballot(most > kFar);
       auto add_tile = [&](float mcr, uint32_t sign) XSV_INLINE {
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
@@ -812,9 +815,14 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
           for (int i = 0; i < 4; ++i) pv_step(cb, vf, pw, i);
         }
       };
-      if (__any(over && top + mc[cb] < 40.0f)) add_tile(mc[cb], 0x80008000u);
-      rescale(cb, over ? fminf(fmaxf(top, -mc[cb]) + kHeadroom, kFar) : -mc[cb]);
+      if (__any(over && most + mc[cb] < 40.0f)) add_tile(mc[cb], 0x80008000u);
+      rescale(cb, over ? fminf(fmaxf(most, -mc[cb]) + kHeadroom, kFar) : -mc[cb]);
       add_tile(mc[cb], 0u);
+      asm volatile("" : "+v"(o0[cb]), "+v"(o1[cb]));  // (see nan_lanes)
+      uint32_t top = 0;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) top = max(top, max(__float_as_uint(o0[cb][r]) & 0x7fffffffu, __float_as_uint(o1[cb][r]) & 0x7fffffffu));
+      take_out_failed = take_out_failed || __any(top >= 0x7f800000u);
     }
   };
   auto some_sum_is_nan = [&]() XSV_INLINE {
@@ -954,10 +962,10 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
        },
        [&](int buf, int valid) XSV_INLINE { if (n_cb > 0) compute_tile_slowly(buf, valid, std::false_type{}); });
   // A row sum that is NaN - for a NaN key, a query that is not finite, a NaN product of finite numbers and infinities - has
-  // made the sum of the row 16 away NaN too (row_sum).  Then the tiles are walked once more, one at a time and every row on
+  // made the sum of the row 16 away NaN too (row_sum).  Then, and after a take-out that failed, the tiles are walked once more, one at a time and every row on
   // its own, and the rows are written again.  A wave cannot do that alone; the rows are written first so that this barrier is
   // the last thing a workgroup does (it also says that everybody has read the unit's last tile).
-  if (n_cb > 0 && some_sum_is_nan() && lane == 0) careful_pass[parity] = 1;
+  if (n_cb > 0 && (take_out_failed || some_sum_is_nan()) && lane == 0) careful_pass[parity] = 1;
   write_rows();
   __syncthreads();
   if (__builtin_expect(__builtin_amdgcn_readfirstlane(careful_pass[parity]) != 0, 0)) {

@@ -291,6 +291,41 @@ def test_frame_attention_when_the_softmax_reference_has_to_move(variant, jump):
     assert err.abs().max() <= 2e-2 and err.norm() <= 1e-2 * want.norm()
 
 
+@pytest.mark.parametrize("variant", [0, 1, 2, 3])
+@pytest.mark.parametrize("jump", [40.0, 62.0])
+def test_infinite_values_where_the_softmax_reference_moves(variant, jump):
+    """A key `jump` powers of two above all keys before it, for every other query row, with an infinite value before it, beside
+    it in its tile and behind it: infinite (of that sign) in every row's channel, NaN where a channel has infinities of both
+    signs or a NaN, and the other channels as they are - in the rows whose reference moves and in their neighbours."""
+    n, H = 64 * 3 + 17, 5
+    g = torch.Generator().manual_seed(int(jump))
+    q = torch.zeros((H, n, 64))
+    q[:, ::2, 0] = 8.0
+    q[:, :, 1:] = 0.25 * torch.randn((H, n, 63), generator=g)
+    k = 0.5 * torch.randn((H, n, 64), generator=g)
+    k[:, :, 0] = 0.0
+    k[:, 100, 0] = jump / (8.0 * 0.125 * 1.4426950408889634)   # q.k / 8 * log2(e) of channel 0 = jump
+    v = torch.randn((H, n, 64), generator=g)
+    inf = float("inf")
+    v[0, 90, 7] = inf
+    v[1, 3, 20] = v[1, 110, 20] = -inf
+    v[2, 70, 33], v[2, 120, 33] = inf, -inf
+    v[3, 180, 0] = inf
+    v[4, 100, 63], v[4, 5, 2] = float("nan"), inf
+    q, k, v = (x.to(torch.bfloat16) for x in (q, k, v))
+    ctx = xsv.Context(1, H, 64, n, 5, 4 * n, 4, 64)
+    ctx.set_attend_variant(variant)
+    ctx.set_attend_splits(1, 1)
+    out = ctx.frame_attend(q.to(DEV), k.to(DEV), v.to(DEV)).cpu().double()
+    ctx.destroy()
+    want = torch.matmul(torch.softmax(torch.matmul(q.double(), k.double().transpose(1, 2).contiguous()) / 8.0, -1), v.double())
+    assert int(want.isinf().sum()) == 4 * n and int(want.isnan().sum()) == 2 * n
+    assert torch.equal(out.isnan(), want.isnan()) and torch.equal(out.isinf(), want.isinf())
+    assert torch.equal(out[want.isinf()], want[want.isinf()])
+    # bf16 probabilities and outputs: each 2^-9 relative, so a value of magnitude <= 4.5 is off by at most 2 * 2^-9 * 4.5
+    assert (out - want)[want.isfinite()].abs().max() <= 2e-2
+
+
 def test_measured_peaks_are_plausible():
     """The library's two yardsticks: an MFMA-only loop and a streaming copy, against the published peaks."""
     mfma, copy = xsv.measure_peaks()
