@@ -31,10 +31,13 @@
 //   workgroup is normalized and written directly; otherwise each workgroup writes an unnormalized
 //   partial that combine_kernel merges.
 //   Softmax.  No row maximum and no rescaling on the common path: the reference of the exponent is the row maximum
-//   of a range's first 32 tokens plus a headroom of 60 powers of two, probabilities are clamped to 1 (a modifier of the
-//   exponential, so nothing can overflow), and only when a row sum reaches 1 - looked at once per tile - the tile is taken
-//   out again, the reference raised and the tile added anew (raise_references).  The loop over full tiles is straight-line
-//   code: a ragged last tile (cache or frame) has its own, simpler, code behind it.
+//   of a range's first 32 tokens plus 8 powers of two, and probabilities may grow above 1 - they are as exact there, in bf16 as
+//   in fp32.  Only when a tile's row sum passes 2^24 - looked at once per tile - are the references moved, which rescales sums and
+//   accumulators (recenter).  The loop over full tiles is straight-line code: a ragged last tile (cache or frame) has its own,
+//   simpler, code behind it.  NaN, infinite logits and overflowing accumulators send the workgroup through its tiles once more,
+//   each row on its own (the careful pass).
+//   The headroom is small on purpose.  Products of probability and value are accumulated at the probabilities' scale: at 2^-60
+//   values below 2^-66 lose bits and below 2^-89 vanish.  At 2^-8 they keep what bf16 holds down to its smallest numbers.
 //   What bounds the loop: vector issue.  Per wave and tile 64 fma + 64 exp + 32 conversions, 56 instructions of dequantizing,
 //   and about 8 cycles of issue for each of 40 MFMAs come to some 1350 cycles, against 1170 of the matrix pipe; two waves
 //   share a SIMD.  v_dot2c_f32_bf16 must stay out of this loop: it executes on the matrix pipe (beside a wave that issues
@@ -59,11 +62,15 @@ constexpr int kLdsTile = 64 * kLdsStride;  // elements of one K (or V) tile in L
 // captured registers go through memory
 #define XSV_INLINE __attribute__((always_inline))
 constexpr float kNegBig = -1.0e30f;
-constexpr float kFar = 3.0e38f;  // above every finite logit in the log2 domain (their scale is below 0.2): references end here
-// A row's reference is put this many powers of two above its largest logit so far: probabilities start at 2^-60 and are
-// clamped to 1 by the exponential's own output modifier, so nothing overflows while the reference stands; it has to move only
-// when a row's sum reaches 1.  Probabilities down to 2^-66 of the row's largest stay normal numbers.
-constexpr float kHeadroom = 60.0f;
+// References end here.  Logits (times the softmax scale, log2 domain) above this count as +infinity: fp32 does not resolve the
+// difference of two such numbers anywhere near 1.
+constexpr float kFar = 3.0e38f;
+// A row's reference is put this many powers of two above its largest logit so far, so that sums over a whole range of like
+// logits stay of the order of 1 (values up to the largest bf16 numbers do not overflow) ...
+constexpr float kHeadroom = 8.0f;
+// ... and moves when a row's sum passes this: 96 powers of two are left for what a single tile can add.  On a 2-bit cache of 24
+// frames' selection the first tokens of a range lie 36 powers of two below the largest (89 at most).
+constexpr float kSumLimit = 0x1p24f;
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
@@ -401,10 +408,6 @@ template <int BITS, int G, int NW, int QB, bool ONE_LAYER>
 __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   constexpr int NT = NW * 64, NH = NT / 2;
   constexpr int kRowsWG = 32 * QB * NW;  // query rows per workgroup
-  // The probabilities' clamp passes a NaN through (MODE.DX10_CLAMP, on by default, makes it 0: a NaN key would drop out of
-  // the softmax instead of showing in every row that attends to it).
-  constexpr int kModeReg = 1, kDx10ClampBit = 8;
-  __builtin_amdgcn_s_setreg(kModeReg | (kDx10ClampBit << 6), 0);
   {
     // The argument block is read field by field further down, each read a scalar load the next instructions wait
     // for, and at the start of a launch every one of them misses the scalar cache: several memory round trips in a
@@ -544,18 +547,18 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
 
   f32x16 o0[QB], o1[QB];
   // softmax state per query block: mc = -(reference of the exponent, log2 domain) so that a probability is
-  // 2^(c2 * logit + mc), and the row sums (layout: see row_sum)
-  float mc[QB];
-  f32x4 l[QB];
-  // Rows whose output is NaN (bit = lane) although their probabilities are kept finite: for a logit of +inf, in the careful
-  // pass also for one that is NaN.  They get it at the end.
+  // 2^(c2 * logit + mc), the sum of this lane's row up to the tile at hand, and the sums of that tile (layout: see tile_sum)
+  float mc[QB], l[QB];
+  f32x4 lt[QB];
+  // Rows with a logit that is NaN or +infinity (bit = lane; the careful pass finds them): their probabilities are kept finite
+  // and their output becomes NaN at the end.
   unsigned long long nan_rows[QB];
   auto clear = [&]() XSV_INLINE {
 #pragma unroll
     for (int cb = 0; cb < QB; ++cb) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) { o0[cb][r] = 0.f; o1[cb][r] = 0.f; }
-      l[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      l[cb] = 0.f;
       nan_rows[cb] = 0;
       mc[cb] = -kNegBig;
     }
@@ -568,12 +571,21 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   // every lane - are the sums of query lane % 16 (16 + lane % 16) over both halves' tokens.
   const uint32_t ones = (((lane & 15) ^ (lane >> 4)) & 1) ? 0u : 0x3f803f80u;
   const u32x4 sum_rows = {ones, ones, ones, ones};
-  auto row_sum = [&](int cb) XSV_INLINE { return (lane & 16) ? l[cb][1] : l[cb][0]; };
-  // step i (0..3) of O^T += V^T P^T for one query block: token step i/2, channel half i%2
-  auto pv_step = [&](int cb, const bf16x8 (&vf)[2][2], const u32x4 (&pb)[2], int i) XSV_INLINE {
+  // (A probability that is not finite makes the sum of the row 16 away NaN.  That is one reason to take a tile's sums by
+  // themselves and to look at them before they are added to the rows': what was summed up before is not lost.)
+  const uint32_t odd_rows = (lane & 16) ? ~0u : 0u;  // (a mask: chosen by a condition, the register would be indexed dynamically)
+  auto tile_sum = [&](int cb) XSV_INLINE {
+    return __uint_as_float((__float_as_uint(lt[cb][1]) & odd_rows) | (__float_as_uint(lt[cb][0]) & ~odd_rows));
+  };
+  auto sum_step = [&](int cb, const u32x4& p, bool fresh) XSV_INLINE {
+    lt[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, sum_rows), __builtin_bit_cast(bf16x8, p),
+                                                     fresh ? f32x4{0.f, 0.f, 0.f, 0.f} : lt[cb], 0, 0, 0);
+  };
+  // step i (0..3) of O^T += V^T P^T for one query block: token step i/2, channel half i%2; `fresh`: the tile's sums begin here
+  auto pv_step = [&](int cb, const bf16x8 (&vf)[2][2], const u32x4 (&pb)[2], int i, bool fresh) XSV_INLINE {
     const int k2 = i >> 1;
     const bf16x8 p = __builtin_bit_cast(bf16x8, pb[k2]);
-    if (!(i & 1)) l[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, sum_rows), p, l[cb], 0, 0, 0);
+    if (!(i & 1)) sum_step(cb, pb[k2], fresh && i == 0);
     if (i & 1) o1[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[k2][1], p, o1[cb], 0, 0, 0);
     else o0[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[k2][0], p, o0[cb], 0, 0, 0);
   };
@@ -612,16 +624,19 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   };
   // Probabilities of one query block over the 32 tokens of a half-step: registers r = 8*k2 .. 8*k2+7 of the logits become
   // the packed B operand of token step k2.  `hook(i)`, i = 0..3, is called before each quarter: the caller issues MFMAs
-  // there, so that the matrix pipe works underneath this arithmetic.
-  auto softmax_half = [&](f32x16& sv, u32x4 (&pb)[2], float mcr, auto&& hook) XSV_INLINE {
+  // there, so that the matrix pipe works underneath this arithmetic.  `clamp`: to 1 (an output modifier of the exponential).
+  auto softmax_half = [&](f32x16& sv, u32x4 (&pb)[2], float mcr, auto clamp, auto&& hook) XSV_INLINE {
+    auto prob = [&](float x) XSV_INLINE {
+      const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(x, c2, mcr));
+      if constexpr (clamp) return __builtin_amdgcn_fmed3f(p, 0.f, 1.f);
+      else return p;
+    };
 #pragma unroll
     for (int q4 = 0; q4 < 4; ++q4) {
       hook(q4);
 #pragma unroll
       for (int r = 4 * q4; r < 4 * q4 + 4; r += 2) {
-        const float p0 = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(__builtin_fmaf(sv[r], c2, mcr)), 0.f, 1.f);
-        const float p1 = __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(__builtin_fmaf(sv[r + 1], c2, mcr)), 0.f, 1.f);
-        pb[r >> 3][(r >> 1) & 3] = pack_bf16(p0, p1);
+        pb[r >> 3][(r >> 1) & 3] = pack_bf16(prob(sv[r]), prob(sv[r + 1]));
       }
     }
     // prescribed issue order of this block, per quarter: its MFMAs spread between its 10 vector instructions (4 fma,
@@ -695,24 +710,24 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
       // other's softmax arithmetic, instead of the older wave finishing its tile first and the younger one
       // then working through its own alone; measured 2.7 % on the kernel)
       __builtin_amdgcn_s_setprio(3);
-      softmax_half(sA, pA, mc[0], with_mfma<1, false>([&](int i) XSV_INLINE { qk_step(sB, kf, 1, i); }));
+      softmax_half(sA, pA, mc[0], std::false_type{}, with_mfma<1, false>([&](int i) XSV_INLINE { qk_step(sB, kf, 1, i); }));
       load_k(kf, buf, 1);
       __builtin_amdgcn_s_setprio(2);
-      softmax_half(sB, pB, mc[1], with_mfma<2, true>([&](int i) XSV_INLINE {
-        pv_step(0, vf, pA, i);
+      softmax_half(sB, pB, mc[1], std::false_type{}, with_mfma<2, true>([&](int i) XSV_INLINE {
+        pv_step(0, vf, pA, i, true);
         qk_step(sA, kf, 0, i);
       }));
       // ---- half 1 ----
       __builtin_amdgcn_s_setprio(1);
-      softmax_half(sA, pA, mc[0], with_mfma<2, true>([&](int i) XSV_INLINE {
-        pv_step(1, vf, pB, i);
+      softmax_half(sA, pA, mc[0], std::false_type{}, with_mfma<2, true>([&](int i) XSV_INLINE {
+        pv_step(1, vf, pB, i, true);
         qk_step(sB, kf, 1, i);
       }));
       load_v(vf, buf, 1);
       __builtin_amdgcn_s_setprio(0);
-      softmax_half(sB, pB, mc[1], with_mfma<1, true>([&](int i) XSV_INLINE { pv_step(0, vf, pA, i); }));
+      softmax_half(sB, pB, mc[1], std::false_type{}, with_mfma<1, true>([&](int i) XSV_INLINE { pv_step(0, vf, pA, i, false); }));
 #pragma unroll
-      for (int i = 0; i < 4; ++i) pv_step(1, vf, pB, i);
+      for (int i = 0; i < 4; ++i) pv_step(1, vf, pB, i, false);
     } else {
       load_k(kf, buf, 0);
 #pragma unroll
@@ -723,9 +738,9 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
         load_v(vf, buf, half);
         if (half == 0) load_k(kf, buf, 1);
         u32x4 pw[2];
-          softmax_half(sv, pw, mc[0], with_mfma<0, false>([](int) XSV_INLINE {}));
+        softmax_half(sv, pw, mc[0], std::false_type{}, with_mfma<0, false>([](int) XSV_INLINE {}));
 #pragma unroll
-        for (int i = 0; i < 4; ++i) pv_step(0, vf, pw, i);
+        for (int i = 0; i < 4; ++i) pv_step(0, vf, pw, i, half == 0);
       }
     }
   };
@@ -735,22 +750,22 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
     const float alpha = __builtin_amdgcn_exp2f(-mc[cb] - ref);
 #pragma unroll
     for (int r = 0; r < 16; ++r) { o0[cb][r] *= alpha; o1[cb][r] *= alpha; }
-    const float a0 = __shfl(alpha, lane & 15), a1 = __shfl(alpha, (lane & 15) + 16);  // (layout of the row sums)
-    l[cb][0] *= a0; l[cb][1] *= a1; l[cb][2] *= a0; l[cb][3] *= a1;
+    l[cb] *= alpha;
     mc[cb] = -ref;
   };
-  // Lanes that hold a NaN among these logits.  (Floats of this file are compiled as if none was NaN: they go through an
-  // opaque move first.)
+  // Lanes that hold a NaN among these logits.  (Floats of this file are compiled as if none was NaN, so they go through an
+  // opaque step first.  Its wait covers the time an MFMA's results take: the compiler does not see a reader of theirs here.)
   auto nan_lanes = [&](f32x16& sv) XSV_INLINE {
-    asm volatile("" : "+v"(sv));
+    asm volatile("s_nop 15" : "+v"(sv));
     uint32_t top = 0;
 #pragma unroll
     for (int r = 0; r < 16; ++r) top = max(top, __float_as_uint(sv[r]) & 0x7fffffffu);
     return __ballot(top > 0x7f800000u);
   };
   // A tile of which the first `valid` tokens are real, one block after the other, with references that follow the running
-  // row maxima: a ragged last tile, and every tile of the careful pass.  There NaN logits are taken out and their rows marked,
-  // so that they end in their own row.
+  // row maxima: a ragged last tile, and every tile of the careful pass.  There the rows of NaN logits are marked, the logits
+  // taken out and probabilities clamped (to 1, for logits so large that the headroom is lost to rounding), so that whatever is
+  // not finite ends in its own row.
   auto compute_tile_slowly = [&](int buf, int valid, auto careful) XSV_INLINE {
     for (int half = 0; half < 2 && 32 * half < valid; ++half) {
       bf16x8 kf[4], vf[2][2];
@@ -769,83 +784,101 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
           for (int r = 0; r < 16; ++r) sv[r] = (rows >> lane) & 1 ? -INFINITY : sv[r];
         }
         const float top = __builtin_fmaf(row_max(sv), c2, kHeadroom);
-        nan_rows[cb] |= __ballot(top > kFar);
+        if constexpr (careful) nan_rows[cb] |= __ballot(top > kFar);
         rescale(cb, fminf(fmaxf(-mc[cb], top), kFar));
         u32x4 pw[2];
-        softmax_half(sv, pw, mc[cb], with_mfma<0, false>([](int) XSV_INLINE {}));
+        softmax_half(sv, pw, mc[cb], careful, with_mfma<0, false>([](int) XSV_INLINE {}));
 #pragma unroll
-        for (int i = 0; i < 4; ++i) pv_step(cb, vf, pw, i);
+        for (int i = 0; i < 4; ++i) pv_step(cb, vf, pw, i, true);
+        l[cb] += tile_sum(cb);
       }
     }
   };
-  // After a full tile: rows whose sum has reached 1 - probabilities of this tile may have been clamped - get a new reference.
-  // The tile's contribution is taken out again (the same products with the sign of P turned; not needed where the tile's
-  // largest logit makes everything before it vanish below fp32), accumulators and sums are rescaled, and the tile is added
-  // with the new reference.  Rare: a logit 60 powers of two above everything before it.
-  // An infinity among the values makes that wrong - infinity minus infinity, and 0 times infinity in the rows that stay - so
-  // accumulators that are not finite ask for the careful pass, which takes nothing out.
-  bool take_out_failed = false;
-  auto raise_references = [&](int buf) XSV_INLINE {
+  // Largest of the tile's row sums that this lane holds (numbers that are not negative, and NaN: by their bits, NaN is largest).
+  auto largest_sum = [&]() XSV_INLINE {
+    uint32_t top = 0;
+#pragma unroll
+    for (int cb = 0; cb < QB; ++cb) top = max(top, max(__float_as_uint(lt[cb][0]), __float_as_uint(lt[cb][1])));
+    return top;
+  };
+  constexpr uint32_t kInfBits = 0x7f800000u;
+  // After a full tile with a row sum above kSumLimit: every row whose sum has grown above 1 gets a reference that puts it below
+  // 2^-8 again (all of them, so that rows which grow alike are not moved one tile after the other); that is a factor for its
+  // sum and accumulators.  Where probabilities come near an overflow, the row's accumulators may be lost, and so is the tile's
+  // sum of the row 16 away.  What such a row had before weighs less than 2^-58 beside this tile (its sum was below 2^24 a
+  // tile): it begins anew with it.  NaN, infinite logits and accumulators that are not finite even so - infinite values, or
+  // products of values beyond 2^27 - ask for the careful pass.
+  bool ask = false;
+  auto recenter = [&](int buf) XSV_INLINE {
 #pragma unroll
     for (int cb = 0; cb < QB; ++cb) {
-      const bool over = row_sum(cb) >= 1.0f;
-      if (!__any(over)) continue;
-      f32x16 s0, s1;
-      {
-        bf16x8 kf[4];
-        load_k(kf, buf, 0);
+      if (__any(__float_as_uint(tile_sum(cb)) >= __float_as_uint(0x1p100f))) {
+        f32x16 s0, s1;
+        {
+          bf16x8 kf[4];
+          load_k(kf, buf, 0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) qk_step(s0, kf, cb, i);
-        load_k(kf, buf, 1);
+          for (int i = 0; i < 4; ++i) qk_step(s0, kf, cb, i);
+          load_k(kf, buf, 1);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) qk_step(s1, kf, cb, i);
-      }
-      const float most = fmaxf(row_max(s0), row_max(s1)) * c2;  // log2 domain
-      nan_rows[cb] |= __ballot(most > kFar);
-      auto add_tile = [&](float mcr, uint32_t sign) XSV_INLINE {
+          for (int i = 0; i < 4; ++i) qk_step(s1, kf, cb, i);
+        }
+        const float top = fmaxf(row_max(s0), row_max(s1)) * c2;  // log2 domain
+        if ((nan_lanes(s0) | nan_lanes(s1) | __ballot(top > kFar)) != 0) {
+          ask = true;
+          return;
+        }
+        const bool far = top + mc[cb] > 90.0f;  // (64 probabilities below that stay below the test above)
+        mc[cb] = far ? -fminf(top + kHeadroom, kFar) : mc[cb];
+        l[cb] = far ? 0.f : l[cb];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { o0[cb][r] = far ? 0.f : o0[cb][r]; o1[cb][r] = far ? 0.f : o1[cb][r]; }
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
           bf16x8 vf[2][2];
           load_v(vf, buf, half);
           u32x4 pw[2];
-          softmax_half(half == 0 ? s0 : s1, pw, over ? mcr : -INFINITY, with_mfma<0, false>([](int) XSV_INLINE {}));
+          softmax_half(half == 0 ? s0 : s1, pw, mc[cb], std::false_type{}, with_mfma<0, false>([](int) XSV_INLINE {}));
 #pragma unroll
-          for (int i = 0; i < 8; ++i) pw[i >> 2][i & 3] ^= sign;
+          for (int k2 = 0; k2 < 2; ++k2) {
+            sum_step(cb, pw[k2], half == 0 && k2 == 0);  // every row's (of rows that stay, as before)
+            u32x4 w = pw[k2];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) pv_step(cb, vf, pw, i);
+            for (int i = 0; i < 4; ++i) w[i] = far ? w[i] : 0u;
+            o0[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[k2][0], __builtin_bit_cast(bf16x8, w), o0[cb], 0, 0, 0);
+            o1[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[k2][1], __builtin_bit_cast(bf16x8, w), o1[cb], 0, 0, 0);
+          }
         }
-      };
-      if (__any(over && most + mc[cb] < 40.0f)) add_tile(mc[cb], 0x80008000u);
-      rescale(cb, over ? fminf(fmaxf(most, -mc[cb]) + kHeadroom, kFar) : -mc[cb]);
-      add_tile(mc[cb], 0u);
-      asm volatile("" : "+v"(o0[cb]), "+v"(o1[cb]));  // (see nan_lanes)
+      }
+      asm volatile("s_nop 15" : "+v"(o0[cb]), "+v"(o1[cb]), "+v"(lt[cb]));  // (see nan_lanes)
       uint32_t top = 0;
 #pragma unroll
       for (int r = 0; r < 16; ++r) top = max(top, max(__float_as_uint(o0[cb][r]) & 0x7fffffffu, __float_as_uint(o1[cb][r]) & 0x7fffffffu));
-      take_out_failed = take_out_failed || __any(top >= 0x7f800000u);
+      ask = ask || __any(top >= kInfBits);
+      // (a factor of 2^-96 at most, so that it is a normal number; the next tile's end takes the rest)
+      l[cb] += tile_sum(cb);
+      lt[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const int up = l[cb] > 1.0f ? min(__builtin_amdgcn_frexp_expf(l[cb]) + (int)kHeadroom, 96) : 0;
+      rescale(cb, (float)up - mc[cb]);
     }
   };
-  auto some_sum_is_nan = [&]() XSV_INLINE {
-    bool bad = false;
+
+  // A full tile's sums looked at and added to the rows'.  A wave of one query block does that behind the conversion of the next
+  // tile, so that it need not wait for them (2-bit stack of 24 layers 2479 -> 2445 us); with two blocks that costs registers
+  // and gains nothing (one 4-bit layer alone 39.6 -> 40.7 us).
+  constexpr bool kSettleLate = QB == 1;
+  auto settle = [&](int buf) XSV_INLINE {
+    if (__builtin_expect(__any(largest_sum() > __float_as_uint(kSumLimit)) && !ask, 0)) recenter(buf);
 #pragma unroll
-    for (int i = 0; i < 2 * QB; ++i) {
-      uint32_t w = __float_as_uint(l[i >> 1][i & 1]);
-      asm volatile("" : "+v"(w));  // (see nan_lanes)
-      bad = bad || (w & 0x7fffffffu) > 0x7f800000u;
-    }
-    return __any(bad);
-  };
-  auto some_row_over = [&]() XSV_INLINE {
-    float top = fmaxf(l[0][0], l[0][1]);
-    if constexpr (QB == 2) top = fmaxf(top, fmaxf(l[1][0], l[1][1]));
-    return __any(top >= 1.0f);
+    for (int cb = 0; cb < QB; ++cb) l[cb] += tile_sum(cb);
   };
 
   // This range's tiles: first its tiles of the packed cache, then its tiles of the frame.  In either phase a tile is
   // fetched into registers while the one before it is computed, then converted into the free one of the two LDS buffers:
   // one barrier per tile.  A ragged last tile (cache or frame) is computed outside of the loop over the full ones, which
-  // is straight-line code.  `first(buf, valid)`: before the first tile; `full(buf)`, `ragged(buf, valid)`: the tiles.
-  auto walk = [&](auto&& first, auto&& full, auto&& ragged) XSV_INLINE {
+  // is straight-line code.  `first(buf, valid)`: before the first tile; `full(buf)`, `ragged(buf, valid)`: the tiles;
+  // `late(buf)`: after a full tile, behind the conversion of the next one.
+  auto walk = [&](auto&& first, auto&& full, auto&& late, auto&& ragged) XSV_INLINE {
     int cur = 0;
     if (c_begin < c_end) {
       constexpr bool kQuant = BITS != 16;
@@ -870,6 +903,7 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
           const float* prm = rp.prm + (cur ^ 1) * kPrmBlock;
           store_cache_tile<BITS, G, NH>(st, rp.lds + (cur ^ 1) * kLdsTile, prm, prm + kPrm, is_v, u);
         }
+        late(cur);
         if (kQuant && t + 2 < c_end) store_params<BITS, G, NH>(pst, rp.prm + cur * kPrmBlock, u);
         no_loads_in_flight();
         cur ^= 1;
@@ -896,6 +930,7 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
         if (t + 1 < f_end) fetch_frame_tile<NH>(st, fr, is_v, t + 1);
         full(cur);
         if (t + 1 < f_end) store_frame_tile<NH>(st, rp.lds + (cur ^ 1) * kLdsTile, is_v, u);
+        late(cur);
         no_loads_in_flight();
         cur ^= 1;
       }
@@ -910,7 +945,7 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
 #pragma unroll
     for (int cb = 0; cb < QB; ++cb) {
       const int q_row = q_row0 + 32 * cb + j;
-      const float lsum = __uint_as_float(__float_as_uint(row_sum(cb)) | ((nan_rows[cb] >> lane) & 1 ? 0x7fc00000u : 0u));
+      const float lsum = __uint_as_float(__float_as_uint(l[cb]) | ((nan_rows[cb] >> lane) & 1 ? 0x7fc00000u : 0u));
       if (q_row >= n) continue;  // (both lanes of a row leave together, so the lane exchange below stays paired)
       if (whole) {
         const float inv = 1.0f / lsum;
@@ -958,14 +993,20 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
        [&](int buf) XSV_INLINE {
          if (n_cb == 0) return;
          compute_tile(buf);
-         if (__builtin_expect(some_row_over(), 0)) raise_references(buf);
+         if constexpr (!kSettleLate) settle(buf);
+       },
+       [&](int buf) XSV_INLINE {
+         if constexpr (kSettleLate) { if (n_cb > 0) settle(buf); }
        },
        [&](int buf, int valid) XSV_INLINE { if (n_cb > 0) compute_tile_slowly(buf, valid, std::false_type{}); });
-  // A row sum that is NaN - for a NaN key, a query that is not finite, a NaN product of finite numbers and infinities - has
-  // made the sum of the row 16 away NaN too (row_sum).  Then, and after a take-out that failed, the tiles are walked once more, one at a time and every row on
-  // its own, and the rows are written again.  A wave cannot do that alone; the rows are written first so that this barrier is
-  // the last thing a workgroup does (it also says that everybody has read the unit's last tile).
-  if (n_cb > 0 && (take_out_failed || some_sum_is_nan()) && lane == 0) careful_pass[parity] = 1;
+  // A row sum that is not finite (row_max and the clamp of the ragged tile pass over a NaN, its sum shows it), and what recenter
+  // could not settle: the tiles are walked once more, one at a time and every row on its own, and the rows are written again.
+  // A wave cannot do that alone; the rows are written first so that this barrier is the last thing a workgroup does (it also
+  // says that everybody has read the unit's last tile).
+  bool lost = ask;
+#pragma unroll
+  for (int cb = 0; cb < QB; ++cb) lost = lost || __any(__float_as_uint(l[cb]) >= kInfBits);
+  if (n_cb > 0 && lost && lane == 0) careful_pass[parity] = 1;
   write_rows();
   __syncthreads();
   if (__builtin_expect(__builtin_amdgcn_readfirstlane(careful_pass[parity]) != 0, 0)) {

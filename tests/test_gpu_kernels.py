@@ -292,7 +292,7 @@ def test_frame_attention_when_the_softmax_reference_has_to_move(variant, jump):
 
 
 @pytest.mark.parametrize("variant", [0, 1, 2, 3])
-@pytest.mark.parametrize("jump", [40.0, 62.0])
+@pytest.mark.parametrize("jump", [40.0, 62.0, 100.0])
 def test_infinite_values_where_the_softmax_reference_moves(variant, jump):
     """A key `jump` powers of two above all keys before it, for every other query row, with an infinite value before it, beside
     it in its tile and behind it: infinite (of that sign) in every row's channel, NaN where a channel has infinities of both
@@ -324,6 +324,79 @@ def test_infinite_values_where_the_softmax_reference_moves(variant, jump):
     assert torch.equal(out[want.isinf()], want[want.isinf()])
     # bf16 probabilities and outputs: each 2^-9 relative, so a value of magnitude <= 4.5 is off by at most 2 * 2^-9 * 4.5
     assert (out - want)[want.isfinite()].abs().max() <= 2e-2
+
+
+def frame_attention(q, k, v, variant, splits):
+    H, n, _ = q.shape
+    ctx = xsv.Context(1, H, 64, n, 0, 4 * n, 4, 64)
+    ctx.set_attend_variant(variant)
+    ctx.set_attend_splits(splits, splits)
+    out = ctx.frame_attend(q.to(DEV), k.to(DEV), v.to(DEV)).cpu().double()
+    ctx.destroy()
+    want = torch.matmul(torch.softmax(torch.matmul(q.double(), k.double().transpose(1, 2).contiguous()) / 8.0, -1), v.double())
+    return out, want
+
+
+@pytest.mark.parametrize("variant,splits", [(0, 1), (1, 2), (2, 1), (3, 2)])
+@pytest.mark.parametrize("power", [-120, -110, -95, -70, 60, 100])
+def test_values_of_every_magnitude(variant, splits, power):
+    """Values of one head, or of one channel, times 2^power: the same result times 2^power."""
+    n, H = 64 * 8 + 17, 2
+    g = torch.Generator().manual_seed(variant)
+    q, k, v = (torch.randn((H, n, 64), generator=g) for _ in range(3))
+    v[0] *= 2.0 ** power
+    # one channel: only where every element is normalized by itself - a row of a cut unit's partial has a common exponent
+    if splits == 1:
+        v[1, :, 5] *= 2.0 ** power
+    q, k, v = (x.to(torch.bfloat16) for x in (q, k, v))
+    out, want = frame_attention(q, k, v, variant, splits)
+    out[0] *= 2.0 ** -power
+    want[0] *= 2.0 ** -power
+    if splits == 1:
+        out[1, :, 5] *= 2.0 ** -power
+        want[1, :, 5] *= 2.0 ** -power
+    # bf16 probabilities and outputs: each 2^-9 relative, so a value of magnitude <= 4.5 is off by at most 2 * 2^-9 * 4.5
+    assert (out - want).abs().max() <= 2e-2
+
+
+@pytest.mark.parametrize("variant", [0, 3])
+def test_one_infinite_value_leaves_the_other_channels_of_a_cut_row(variant):
+    n, H = 64 * 8 + 17, 2
+    g = torch.Generator().manual_seed(11)
+    q, k, v = (torch.randn((H, n, 64), generator=g).to(torch.bfloat16) for _ in range(3))
+    v[0, 30, 7] = float("inf")
+    out, want = frame_attention(q, k, v, variant, 2)
+    assert torch.equal(out.isinf(), want.isinf()) and int(want.isinf().sum()) == n
+    # bf16 probabilities and outputs: each 2^-9 relative, so a value of magnitude <= 4.5 is off by at most 2 * 2^-9 * 4.5
+    assert (out - want)[want.isfinite()].abs().max() <= 2e-2
+
+
+@pytest.mark.parametrize("variant", [0, 1, 2, 3])
+@pytest.mark.parametrize("jump", [31.0, 33.0, 127.0, 134.0, 137.0, 300.0])
+def test_frame_attention_at_the_limits_of_the_softmax_reference(variant, jump):
+    """Around what a reference stands (32 powers of two above the first keys), what one tile may add before it moves (135) and
+    beyond."""
+    test_frame_attention_when_the_softmax_reference_has_to_move(variant, jump)
+
+
+@pytest.mark.parametrize("variant", [0, 3])
+@pytest.mark.parametrize("rise", [26.0, 28.0, 31.0])
+def test_sums_that_move_the_softmax_reference_without_a_large_logit(variant, rise):
+    """All keys behind the first tile `rise` powers of two above those of the first: no single probability passes the limit, the
+    sum of a few tiles does - for every other query row."""
+    n, H = 64 * 8 + 17, 2
+    g = torch.Generator().manual_seed(int(rise))
+    q = torch.zeros((H, n, 64))
+    q[:, ::2, 0] = 8.0
+    q[:, :, 1:] = 0.25 * torch.randn((H, n, 63), generator=g)
+    k = 0.5 * torch.randn((H, n, 64), generator=g)
+    k[:, :, 0] = 0.0
+    k[:, 64:, 0] = rise / (8.0 * 0.125 * 1.4426950408889634)
+    v = torch.randn((H, n, 64), generator=g)
+    q, k, v = (x.to(torch.bfloat16) for x in (q, k, v))
+    out, want = frame_attention(q, k, v, variant, 1)
+    # bf16 probabilities and outputs: each 2^-9 relative, so a value of magnitude <= 4.5 is off by at most 2 * 2^-9 * 4.5
+    assert (out - want).abs().max() <= 2e-2
 
 
 def test_measured_peaks_are_plausible():
