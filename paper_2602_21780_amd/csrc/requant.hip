@@ -31,7 +31,9 @@
 
 #include "xsv_internal.h"
 
+#define XSV_QUOTIENT __device__ __forceinline__
 namespace xsv {
+#include "quotient.h"
 
 __device__ __forceinline__ float round_bf16(float x) { return (float)(__bf16)x; }
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -42,16 +44,6 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   const f32x2 v = {a, b};  // one v_cvt_pk_bf16_f32
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-
-// x / s rounded to nearest, bit for bit the IEEE quotient, for x a bf16 number, from y = RN(1 / s): a product and one
-// correction with its remainder.  That one correction is enough has been checked for every pair of an 8-bit significand x
-// and a 24-bit significand s (2^30 quotients; the exponents do not matter while nothing over- or underflows); a second
-// one would be needed only for x of full precision.  For |x / s| < 1/2 the intermediates may lose bits to underflow, which
-// cannot move rint() of the result off zero.
-__device__ __forceinline__ float exact_quotient(float x, float s, float y) {
-  const float q = x * y;
-  return __builtin_fmaf(__builtin_fmaf(-q, s, x), y, q);
 }
 
 struct QParam {
@@ -72,9 +64,7 @@ __device__ __forceinline__ QParam group_param(float lo, float hi) {
   constexpr float kBig = 0x1p60f, kSmall = 0x1p-60f, kFar = 0x1p21f;
   const float d = hi - lo;
   QParam p;
-  // RN(d / levels) by the same one correction (checked for every significand of d)
-  p.s = d * inv;
-  p.s = __builtin_fmaf(__builtin_fmaf(-p.s, levels, d), inv, p.s);
+  p.s = exact_scale(d, levels, inv);
   if (d == 0.0f) p.s = 1.0f;
   const float mag = fmaxf(fabsf(lo), fabsf(hi));
   const bool safe = p.s >= kSmall && p.s <= kBig && mag <= kBig && mag <= kFar * p.s;

@@ -95,6 +95,22 @@ def test_header_compiles_as_c_and_every_entry_point_links(tmp_path):
     assert r.returncode == 0 and "abi ok" in r.stdout, (r.returncode, r.stdout, r.stderr)
 
 
+def test_quotients_without_division_are_exact_for_every_significand(tmp_path):
+    """The quantizers' quotient and scale (csrc/quotient.h, the code that the kernels inline) against the division: all 2^30
+    pairs of a bf16 and an fp32 significand, and every significand of a range."""
+    import shutil
+    import subprocess
+    cc = shutil.which("gcc") or shutil.which("cc")
+    if cc is None:
+        pytest.skip("no C compiler")
+    exe = str(tmp_path / "quotient_check")
+    r = subprocess.run([cc, "-std=c99", "-O3", "-march=native", "-ffp-contract=off", "-Wall", "-Wextra", "-Werror",
+                        os.path.join(ROOT, "tests", "c", "quotient_check.c"), "-o", exe, "-lm"], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and r.stdout.split() == ["0", "0"], r.stdout
+
+
 def test_key_ranges_cover_the_tiles_with_equal_cost(lib):
     """The host routine that places the key ranges of an attention launch: the ranges tile [0, tiles) without gaps,
     none is empty, the full ranges cost the same to within one tile, and a short last range costs about its share."""
