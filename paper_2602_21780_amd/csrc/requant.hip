@@ -598,10 +598,11 @@ hipError_t launch_requant(const RequantArgs& a, hipStream_t stream) {
 // ---- the stateless quantizers ------------------------------------------------------------------------
 // A plain bf16 tensor [H][T][64] straight to canonical codes (a byte each), scales and zero points: one workgroup per
 // (block of 64 tokens, head), thread = (token tid/4, 16 channels), one read of the tensor and one write of the result.
-// The arithmetic, the order of every min / max included (a group of zeros of both signs keeps the sign that the
-// re-quantization gives it), is requant_kernel's.  Bound: memory, in principle - at 16 heads x 4096 tokens a launch moves
-// 13 MB and takes less time than launching it and waiting for it (the calls are synchronous).  Keys and values of that
-// size took 5.2 ms as a throw-away context that was filled, re-quantized and unpacked (its allocations and its first fill).
+// The arithmetic is requant_kernel's.  The order of the elements in a min / max is not, and need not be: the hardware takes -0
+// for smaller than +0, so a group of zeros of both signs has the same extremes, and zero point, in any order.  Bound: memory, in
+// principle - at 16 heads x 4096 tokens a launch moves 13 MB and takes less time than launching it and waiting for it (the calls
+// are synchronous).  Keys and values of that size take 51 us, and took 1.2 to 5.7 ms as a throw-away context that was filled,
+// re-quantized and unpacked (its allocations vary by that much).
 // `wide`: the codes' address allows 16-byte stores (any address is accepted).
 __device__ __forceinline__ void load_row16(const uint16_t* p, float* x) {
   const uint4* p4 = reinterpret_cast<const uint4*>(p);

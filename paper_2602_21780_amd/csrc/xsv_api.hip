@@ -283,7 +283,7 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
       ly.vc = reinterpret_cast<const uint32_t*>(lc.vc); ly.vs = lc.vs; ly.vz = lc.vz;
       ly.q = b.q[i]; ly.k = b.k[i]; ly.v = b.v[i]; ly.out = b.out[i];
     }
-    a.n_layers = n_layers; a.H = p.H; a.bits = p.bits; a.G = p.G; a.Tcap = p.Tcap;
+    a.n_layers = n_layers; a.H = p.H; a.bits = p.bits; a.G = p.G;
     a.code_head = (uint32_t)((size_t)p.Tcap * (kD * p.bits / 32));
     a.kparam_head = (uint32_t)((size_t)(p.Tcap / p.G) * kD);
     a.vparam_head = (uint32_t)((size_t)p.Tcap * (kD / p.G));

@@ -130,7 +130,6 @@ struct AttendLayer {
 struct AttendArgs {
   AttendLayer layer[kMaxBatch];
   int n_layers, H, bits, G;
-  int Tcap;
   uint32_t code_head, kparam_head, vparam_head;  // elements (dwords / floats) between two heads of kc|vc, ks|kz, vs|vz
   int64_t q_sh, q_st, k_sh, k_st, v_sh, v_st;    // strides of the frame tensors in elements
   uint16_t* attn_o;  // partial outputs of cut units, see Workspace

@@ -125,6 +125,34 @@ def test_cache_of_one_frame_equals_the_stateless_quantizers(bits, G, T):
         assert torch.equal(odd[1:1 + codes.numel()], codes.reshape(-1)) and odd[0] == 0 and not odd[1 + codes.numel():].any()
 
 
+@pytest.mark.parametrize("bits,G", [(4, 64), (4, 32), (2, 64), (2, 32)])
+def test_zeros_of_both_signs_give_the_same_zero_point_everywhere(bits, G):
+    """A group whose smallest element is a zero: its zero point is +0 if a -0 is among the elements and -0 otherwise, wherever
+    in the group that is - the minimum of zeros of both signs is -0 in whatever order a kernel takes it - in the cache and
+    from the stateless quantizers, bit for bit."""
+    H, T = 2, 256
+    g = torch.Generator().manual_seed(bits + G)
+    x = torch.zeros((H, T, 64))
+    x[torch.rand((H, T, 64), generator=g) < 0.02] = -0.0
+    x[1] = x[1] + torch.rand((T, 64), generator=g) * (torch.rand((T, 64), generator=g) < 0.5)
+    x = x.to(torch.bfloat16)
+    neg = torch.signbit(x.float())
+    assert float(x.float().min()) == 0.0 and bool(neg.any())
+    ctx = xsv.Context(1, H, 64, T, 0, 4 * T, bits, G)
+    xd = x.to(DEV)
+    ctx.step(0, xd, xd, xd)
+    d = ctx.cache_export(0)
+    ctx.destroy()
+    zero = x.float() == 0
+    for fn, cached, groups in ((xsv.quantize_k, d.k_zero, lambda t: t.reshape(H, T // G, G, 64).any(2)),
+                               (xsv.quantize_v, d.v_zero, lambda t: t.reshape(H, T, 64 // G, G).any(3))):
+        holds_zero, holds_neg = groups(zero), groups(neg)
+        assert bool((holds_zero & holds_neg).any()) and bool((holds_zero & ~holds_neg).any())
+        want = torch.where(holds_neg, 0.0, -0.0).view(torch.int32)
+        for got in (torch.from_numpy(cached).reshape(holds_zero.shape), fn(xd, bits, G)[2].cpu()):
+            assert torch.equal(got.view(torch.int32)[holds_zero], want[holds_zero])
+
+
 @pytest.mark.parametrize("H,n,n_s,P,g", [(2, 64, 5, 192, 16), (16, 1374, 5, 2722, 16), (3, 37, 5, 70, 4), (1, 21, 0, 1, 1),
                                          (20, 150, 5, 333, 16), (37, 90, 3, 100, 7)])
 def test_score_matches_oracle(H, n, n_s, P, g):
