@@ -26,8 +26,8 @@ PEAK_HBM_GBS = 8000.0
 # Not measurable from inside this process: HBM bytes per attend_kernel launch of this workload from the two
 # rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE) summarized in profiles/attend_cfg2_hbm_traffic.md.  Reported under
 # "traffic_from_profile" with the profile's date and only for the grid it was measured on; "traffic" itself stays null.
-TRAFFIC_PROFILE = {"file": "profiles/attend_cfg2_hbm_traffic.md", "date": "2026-11-28", "workgroups": 240,
-                   "fetch_bytes": 24.7e6, "write_bytes": 15.8e6}
+TRAFFIC_PROFILE = {"file": "profiles/attend_cfg2_hbm_traffic.md", "date": "2026-12-03", "workgroups": 240,
+                   "fetch_bytes": 13.4e6, "write_bytes": 15.8e6}
 
 
 def algorithmic_work(spec, Tc, Tn, P):

@@ -22,9 +22,9 @@
 // Bound: vector arithmetic (every retained element is read once and written once, packed, but dequantized, compared,
 // divided, rounded and packed in between); hence the forms of the quotient and of the rounding below, which are exact.
 // One thread per (token, 16 channels) of both tensors, with the keys' extremes through a tile in LDS, two more fused
-// multiply-adds per quotient and a conversion per code, took 14 us for a layer alone (16 heads, 4096 tokens, 4 bits; 30 us
-// beside the attention kernel) where this takes 11 (25), and the frame of a 24-layer stack with all layers per launch, the
-// attention kernel running at the same time, 941 us where this has it at 907.
+// multiply-adds per quotient and a conversion per code, took 174 us for the 24 layers of a frame in one launch (16 heads, 4096
+// tokens, 4 bits) where this takes 150; with the attention kernel running beside it such a frame went from 941 to 907 us.  One
+// layer alone is bound by its dependency chain and gained nothing: 12.5 us before, 13.1 now.
 // move_kernel: the same gather for a 16-bit cache, rows copied as they are.
 // Compiled with -ffp-contract=off; division is IEEE, rounding is nearest-even.
 #include <cstddef>
