@@ -1007,7 +1007,19 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   // says that everybody has read the unit's last tile).
   bool lost = ask;
 #pragma unroll
-  for (int cb = 0; cb < QB; ++cb) lost = lost || __any(__float_as_uint(l[cb]) >= kInfBits);
+  for (int cb = 0; cb < QB; ++cb) {
+    lost = lost || __any(__float_as_uint(l[cb]) >= kInfBits);
+    // An accumulator can overflow without any sum being large: values near 2^128, probabilities that add up to 1/2 or more.
+    // (One sum over all of them is not finite if one of them is not; a false alarm costs time only.)
+    if (__any(l[cb] >= 0.5f)) {
+      f32x4 all = {0.f, 0.f, 0.f, 0.f};  // (four chains: this stands at the end of every launch)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) all[r & 3] += o0[cb][r] + o1[cb][r];
+      uint32_t bits = __float_as_uint((all[0] + all[1]) + (all[2] + all[3]));
+      asm volatile("" : "+v"(bits));  // (see nan_lanes; an integer here, or the test becomes one for infinity alone)
+      lost = lost || __any((bits & kInfBits) == kInfBits);
+    }
+  }
   if (n_cb > 0 && lost && lane == 0) careful_pass[parity] = 1;
   write_rows();
   __syncthreads();

@@ -387,6 +387,25 @@ def test_values_of_every_magnitude(variant, splits, power):
     assert (out - want).abs().max() <= 2e-2
 
 
+@pytest.mark.parametrize("variant,splits", [(0, 1), (1, 2), (2, 1), (3, 2)])
+@pytest.mark.parametrize("rise", [12.0, 20.0, 30.0])
+def test_huge_values_whose_weights_rise_along_the_keys(variant, splits, rise):
+    """Values of 2^120 and keys `rise` powers of two above those of the first tile: weights times values, at the scale of the first
+    tile's weights, are beyond fp32, the output is not."""
+    n, H = 64 * 8 + 17, 2
+    g = torch.Generator().manual_seed(int(rise) + variant)
+    q = 0.25 * torch.randn((H, n, 64), generator=g)
+    q[:, :, 0] = 8.0
+    k = 0.5 * torch.randn((H, n, 64), generator=g)
+    k[:, :, 0] = 0.0
+    k[:, 64:, 0] = rise / (8.0 * 0.125 * 1.4426950408889634)
+    v = torch.randn((H, n, 64), generator=g) * 2.0 ** 120
+    q, k, v = (x.to(torch.bfloat16) for x in (q, k, v))
+    out, want = frame_attention(q, k, v, variant, splits)
+    # bf16 probabilities and outputs: each 2^-9 relative, so a value of magnitude <= 4.5 is off by at most 2 * 2^-9 * 4.5
+    assert ((out - want) * 2.0 ** -120).abs().max() <= 2e-2
+
+
 @pytest.mark.parametrize("variant", [0, 3])
 def test_one_infinite_value_leaves_the_other_channels_of_a_cut_row(variant):
     n, H = 64 * 8 + 17, 2
