@@ -1,56 +1,78 @@
 // Token importance and keep-list selection (paper Sec. 3.2) for gfx950.
 //
 // The importance  S_j = (1/N_pooled) sum_i (Qbar Kbar^T)[i][j]  is linear in the pooled queries, so
-// it is evaluated as  S_j = qtilde . Kbar_j  with  qtilde = (1/N_pooled) sum_i Qbar_i :
-//   pool_query_kernel   one pass over Q: weighted row sums (weight 1/(H N_pooled) for a special
-//                       row, 1/(H N_pooled |group|) for a patch row), kPoolSeg workgroups (row segments)
-//                       and partials per head; every score workgroup adds the partials in a fixed
-//                       order, so the result is reproducible bit for bit and needs no atomics.
-//   score_kernel        one pass over the packed keys of the prunable middle: dequantized view,
-//                       head mean, dot product with qtilde.  64 tokens x all heads per workgroup,
-//                       16 channels per thread, all loads of a workgroup issued before any use.
-//   Per-head variant (ScoreArgs::per_head, not the paper's): the averages over heads are left out,
-//   qtilde_h comes from head h's partial alone and head h's keys give head h's own score vector.
-//   select_kernel       exact top-k by radix select on order-preserving integer keys held in
-//                       registers (4 passes of 8 bits, histograms in LDS, bin search by a shuffle
-//                       scan), ties at the threshold resolved toward smaller positions, then an
-//                       ordered compaction that emits the keep list ascending.
+// it is evaluated as  S_j = qtilde . Kbar_j  with  qtilde = (1/N_pooled) sum_i Qbar_i.  Three parts:
+//   pool    one pass over Q: weighted row sums (weight 1/(H N_pooled) for a special
+//           row, 1/(H N_pooled |group|) for a patch row), two workgroups and kPoolParts partials per head, added up
+//           by everybody who needs qtilde in one fixed order: reproducible bit for bit, no atomics on floats.
+//   score   one pass over the packed keys of the prunable middle: dequantized view,
+//           head mean, dot product with qtilde.  64 tokens x all heads per workgroup, 8 channels per thread, all loads of a
+//           workgroup issued before any use.
+//   select  exact top-k by radix select on order-preserving integer keys held in
+//           registers (digits of 11, 11 and 10 bits, histograms in LDS), ties at the threshold resolved toward smaller
+//           positions, then an ordered compaction that emits the keep list ascending.
+// front_kernel is all three in one launch for one layer, a role per workgroup.  Each part takes a few microseconds, most of it the latency of
+// a kernel's start, of its arguments and of one or two trips to memory: one layer of 16 heads x 1374 tokens with 2722 middle
+// positions took 21.2 us as three kernels with nothing beside them, and takes 13.8 as one.
+// A workgroup waits only for workgroups of a smaller index, which the hardware has started before it: score for its layer's pool
+// (only at the end, with the key means in registers), select for its layer's score.  What they hand over goes through
+// agent-scope stores and loads (past the caches that the dies of the chip do not share) and a counter per part; the last select
+// of a layer puts the counters back to zero.
+//   Per-head variant (FrontCommon::per_head, not the paper's): the averages over heads are left out,
+//   qtilde_h comes from head h's partials alone and head h's keys give head h's own score vector and list.
 // Compiled with -ffp-contract=off: the dequantized view must be (code - zero) * scale with one
 // rounding per operation.
+#include <type_traits>
+
 #include "xsv_internal.h"
 
 namespace xsv {
 
-__device__ __forceinline__ float round_bf16(float x) { return (float)(__bf16)x; }
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-constexpr int kPoolThreads = 1024;
+constexpr int kThreads = 512;    // of pool, select and (but for plain keys) score
+constexpr int kHeadChunk = 16;   // heads whose keys a score workgroup holds in registers at a time
 
-// grid (H * kPoolSeg, layers), 1024 threads: thread = (row lane tid/8 of 128, channel run tid%8); a workgroup
-// takes one of kPoolSeg row segments of one head.  One partial weighted row sum [64] per (head, segment);
-// the score kernel adds the partials in (head, segment) order.
-__global__ __launch_bounds__(kPoolThreads) void pool_query_kernel(const ScoreArgs a) {
-  __shared__ float red[kPoolThreads / 8][kD + 1];
-  const int lb = blockIdx.y, h = blockIdx.x / kPoolSeg, seg = blockIdx.x % kPoolSeg;
-  const int H = a.pool.H, n = a.n, n_s = a.n_special, g = a.pool_size;
-  const int seg_rows = (n + kPoolSeg - 1) / kPoolSeg, r_end = min(n, (seg + 1) * seg_rows);
-  const int n_pooled = n_s + (n - n_s + g - 1) / g;
+// ---- handing over between workgroups ------------------------------------------------------------------
+template <typename T>
+__device__ __forceinline__ T load_agent(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename T>
+__device__ __forceinline__ void store_agent(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// This workgroup's part is done.  (Its agent-scope stores have reached memory when a wave's count of outstanding ones is zero.)
+__device__ __forceinline__ void arrive(uint32_t* counter) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// All `n` workgroups of the part in front are done.
+__device__ __forceinline__ void wait_for(const uint32_t* counter, uint32_t n) {
+  while (load_agent(counter) != n) __builtin_amdgcn_s_sleep(1);
+  asm volatile("" ::: "memory");
+}
+enum { kPoolDone = 0, kScoreDone = 1, kSelectSeen = 2 };  // FrontLayer::sync
+
+// ---- pool ----------------------------------------------------------------------------------------------
+constexpr int kPoolLds = (kThreads / 8) * (kD + 1);
+// Thread = (row lane, channel run).  A head has 128 row lanes (lane i: rows i, i + 128, ..), 64 to each of its two workgroups,
+// and each 32 lanes' sum is a partial.
+template <bool SYNC>
+__device__ __forceinline__ void pool_part(const FrontLayer& ly, const FrontCommon& a, int h, int half, float* lds) {
+  float(*red)[kD + 1] = reinterpret_cast<float(*)[kD + 1]>(lds);
+  const int H = a.H, n = a.n, n_s = a.n_special, g = a.pool_size;
+  const int n_groups = (n - n_s + g - 1) / g, n_pooled = n_s + n_groups;
   const int tid = threadIdx.x, rl = tid >> 3, o = tid & 7;
-  const uint16_t* qh = a.b.q[lb] + (size_t)h * a.b.q_sh;
-  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  const uint16_t* qh = ly.q + (size_t)h * a.q_sh + o * 8;
   const float base = a.per_head ? (float)n_pooled : (float)(H * n_pooled);
-#pragma unroll 4
-  for (int r = seg * seg_rows + rl; r < r_end; r += kPoolThreads / 8) {
-    float w;
-    if (r < n_s) {
-      w = 1.0f / base;
-    } else {
-      const int u = (r - n_s) / g;
-      const int size = min(g, n - n_s - u * g);
-      w = 1.0f / (base * (float)size);
-    }
-    const uint4 v = *reinterpret_cast<const uint4*>(qh + (size_t)r * a.b.q_st + o * 8);
+  // a special row, a row of a whole group, a row of the last group
+  const int last = n_s + (n_groups - 1) * g;  // its first row
+  const float w_special = 1.0f / base, w_whole = 1.0f / (base * (float)min(g, n - n_s)), w_last = 1.0f / (base * (float)(n - last));
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 6
+  for (int r = half * 64 + rl; r < n; r += 128) {
+    const float w = r < n_s ? w_special : (r < last ? w_whole : w_last);
+    const uint4 v = *reinterpret_cast<const uint4*>(qh + (size_t)r * a.q_st);
     const uint32_t ww[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -61,133 +83,132 @@ __global__ __launch_bounds__(kPoolThreads) void pool_query_kernel(const ScoreArg
 #pragma unroll
   for (int e = 0; e < 8; ++e) red[rl][o * 8 + e] = acc[e];
   __syncthreads();
-  // fold the 128 row lanes in a fixed order: 4 segments of 32, then a chain
-  __shared__ float seg4[4][kD];
-  if (tid < 4 * kD) {
+  if (tid < 2 * kD) {
     const int sg = tid >> 6, c = tid & 63;
     float s = 0.f;
-    for (int i = sg * 32; i < sg * 32 + 32; ++i) s += red[i][c];
-    seg4[sg][c] = s;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) s += red[sg * 32 + i][c];
+    float* out = ly.qpart + ((size_t)h * kPoolParts + half * 2 + sg) * kD + c;
+    if (SYNC) store_agent(out, s);
+    else *out = s;
   }
-  __syncthreads();
-  if (tid < kD) {
-    float* part = a.ws.qpart + (size_t)(a.b.layer0 + lb) * a.ws.qpart_rows * kD;
-    part[(size_t)blockIdx.x * kD + tid] = ((seg4[0][tid] + seg4[1][tid]) + seg4[2][tid]) + seg4[3][tid];
-  }
+  if (SYNC) arrive(ly.sync + kPoolDone);
 }
 
-hipError_t launch_pool_query(const ScoreArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL(pool_query_kernel, dim3(a.pool.H * kPoolSeg, a.b.n_layers), dim3(kPoolThreads), 0, stream, a);
-  return hipGetLastError();
+// Channel c of head h's pooled query: its partials in order.
+template <bool SYNC>
+__device__ __forceinline__ float head_query(const FrontLayer& ly, int h, int c) {
+  static_assert(kPoolParts == 4, "the order of the sum");
+  const float* p = ly.qpart + (size_t)h * kPoolParts * kD + c;
+  float x[kPoolParts];
+#pragma unroll
+  for (int i = 0; i < kPoolParts; ++i) x[i] = SYNC ? load_agent(p + i * kD) : p[i * kD];
+  return ((x[0] + x[1]) + x[2]) + x[3];
 }
 
-// grid (blocks of 64 cache positions covering the middle, layers), 256 threads:
-// thread = (token tid/4 of the block, channel quarter tid%4 = 16 channels).
-// Everything a workgroup needs is requested up front (one memory round trip): the H partial query
-// sums, the group parameters of all heads (staged in LDS, they are shared by the block's tokens)
-// and the thread's packed codes of all heads.
-template <int BITS, int G, int HMAX, bool PER_HEAD>
-__global__ __launch_bounds__(256) void score_kernel(const ScoreArgs a) {
+// ---- score ---------------------------------------------------------------------------------------------
+template <int BITS, int G, bool PER_HEAD>
+constexpr int score_lds() {
+  return (PER_HEAD ? kHeadChunk * kD : kD) + (BITS == 16 ? 0 : kHeadChunk * (kTile / G) * 2 * kD);
+}
+// Thread = (token tid/8 of the workgroup's THREADS/8, channels 8 * (tid%8) ..).  Everything a workgroup needs is requested up
+// front (one memory round trip): the group parameters of all heads (staged in LDS, they are shared by the block's tokens) and the
+// thread's codes of all heads.
+template <int BITS, int G, bool PER_HEAD, int THREADS, bool SYNC>
+__device__ __forceinline__ void score_part(const FrontLayer& ly, const FrontCommon& a, int block, float* lds) {
   constexpr bool kQuant = BITS != 16;
-  constexpr int kGroups = kQuant ? kTile / G : 1;  // key groups inside a block of 64 positions
-  constexpr int kRowDw = kD * BITS / 32;           // dwords per key row
-  constexpr int kDwT = kRowDw / 4;                 // dwords per thread (16 channels)
-  __shared__ float qtilde[PER_HEAD ? HMAX * kD : kD];  // per head: one row per head of the chunk
-  __shared__ float prm[kQuant ? HMAX * kGroups * 2 * kD : 1];  // [head][group][scale|zero][channel]
+  constexpr int kRows = THREADS / 8;
+  static_assert(!kQuant || kRows == kTile, "the block's parameters are those of one tile");
+  constexpr int kGroups = kQuant ? kTile / G : 1;      // key groups inside a block of 64 positions
+  constexpr int kRowDw = kD * BITS / 32;               // dwords per key row
+  constexpr int kDwT = kQuant ? 1 : 4;                 // dwords per thread (2 bits: shared by two threads)
+  float* qtilde = lds;                                 // per head: one row per head of the chunk
+  float* prm = lds + (PER_HEAD ? kHeadChunk * kD : kD);  // [head][group][scale|zero][channel]
 
-  const int lb = blockIdx.y;
-  const int H = a.pool.H;
-  const int tid = threadIdx.x, r = tid >> 2, cq = tid & 3;
-  const int block = a.T_first / kTile + blockIdx.x;
-  const int pos = block * kTile + r;  // cache position
+  const int H = a.H, tid = threadIdx.x, r = tid >> 3, c8 = tid & 7;
+  const int first = (a.T_first / kRows + block) * kRows, pos = first + r;  // cache position
   const bool valid = pos >= a.T_first && pos < a.T_first + a.P;
-  const bool plain = a.k_plain != nullptr;
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(ly.kc) + (size_t)pos * kRowDw + (kQuant ? c8 * kRowDw / 8 : 4 * c8);
+  const size_t head_stride = (size_t)a.head_rows * kRowDw;
 
-  const uint32_t* src;
-  size_t head_stride;  // dwords
-  if (plain) {
-    src = reinterpret_cast<const uint32_t*>(a.k_plain) + (size_t)(pos - a.T_first) * kRowDw + cq * kDwT;
-    head_stride = (size_t)a.P * kRowDw;
-  } else {
-    const LayerCache lc = layer_cache(a.pool, a.b.src_buf(lb), a.b.layer0 + lb);
-    src = reinterpret_cast<const uint32_t*>(lc.kc) + (size_t)pos * kRowDw + cq * kDwT;
-    head_stride = (size_t)a.pool.Tcap * kRowDw;
-  }
-  const float* part = a.ws.qpart + (size_t)(a.b.layer0 + lb) * a.ws.qpart_rows * kD;
-
-  auto fold_partials = [&]() {  // the H partial query sums, in head order (called once, behind the chunk's loads)
-    if (!PER_HEAD && tid < kD) {
-      float s = 0.f;
-#pragma unroll 16
-      for (int h = 0; h < H * kPoolSeg; ++h) s += part[(size_t)h * kD + tid];
-      qtilde[tid] = s;
+  float acc[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+  // sum over the thread's 16 channels' worth of products in channel order: the odd lanes go on from their neighbours
+  auto dot16 = [&](const float* qt, const float* x) {
+    float d = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) d += qt[e] * x[e];
+    const float even = __shfl_xor(d, 1);
+    d = even;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) d += qt[e] * x[e];
+    d += __shfl_xor(d, 2);
+    d += __shfl_xor(d, 4);
+    return d;  // (in odd lanes)
+  };
+  auto store_score = [&](int list, float s) {
+    float* out = ly.scores + (size_t)list * a.stride + (pos - a.T_first);
+    if (valid && c8 == 1) {
+      if (SYNC) store_agent(out, s);
+      else *out = s;
     }
   };
-  float acc[16];
+  for (int h0 = 0; h0 < H; h0 += kHeadChunk) {  // (one chunk for H <= kHeadChunk)
+    const int hn = min(kHeadChunk, H - h0);
+    uint32_t w[kHeadChunk][kDwT];
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-  for (int h0 = 0; h0 < H; h0 += HMAX) {  // heads in chunks of HMAX (one chunk for H <= HMAX)
-    const int hn = min(HMAX, H - h0);
-    // codes (or bf16 rows) of this thread's 16 channels, all heads of the chunk
-    uint32_t w[HMAX][kDwT];
-#pragma unroll
-    for (int h = 0; h < HMAX; ++h)
-#pragma unroll
-      for (int i = 0; i < kDwT; ++i) w[h][i] = (valid && h < hn) ? src[(h0 + h) * head_stride + i] : 0u;
-    if constexpr (PER_HEAD) {
-      if (h0 > 0) __syncthreads();  // the previous chunk's rows are no longer read
-      for (int i = tid; i < hn * kD; i += 256) {  // head h0 + i / 64: its segments in order
-        const float* ph = part + ((size_t)(h0 + i / kD) * kPoolSeg) * kD + i % kD;
-        float s = ph[0];
-#pragma unroll
-        for (int sg = 1; sg < kPoolSeg; ++sg) s += ph[sg * kD];
-        qtilde[i] = s;
+    for (int h = 0; h < kHeadChunk; ++h) {
+      const uint32_t* p = src + (h0 + h) * head_stride;
+      if constexpr (kQuant) {
+        w[h][0] = (valid && h < hn) ? *p : 0u;
+      } else {
+        const uint4 v = (valid && h < hn) ? *reinterpret_cast<const uint4*>(p) : make_uint4(0, 0, 0, 0);
+        w[h][0] = v.x; w[h][1] = v.y; w[h][2] = v.z; w[h][3] = v.w;
       }
     }
+    constexpr int kPrmIter = kQuant ? kHeadChunk * kGroups * 2 * kD / THREADS : 1;
+    float pr[kPrmIter];
     if constexpr (kQuant) {
-      const LayerCache lc = layer_cache(a.pool, a.b.src_buf(lb), a.b.layer0 + lb);
-      const int gcap = a.pool.Tcap / G;
-      constexpr int kPrmIter = HMAX * kGroups * 2 * kD / 256;
-      float pr[kPrmIter];  // loaded first, stored to LDS below: every load is in flight before the first wait
 #pragma unroll
       for (int it = 0; it < kPrmIter; ++it) {
-        const int i = tid + it * 256;
+        const int i = tid + it * THREADS;
         const int c = i % kD, sz = (i / kD) & 1, gi = (i / (2 * kD)) % kGroups, h = i / (2 * kD * kGroups);
-        const float* p = sz ? lc.kz : lc.ks;
-        pr[it] = h < hn ? p[((size_t)(h0 + h) * gcap + block * kGroups + gi) * kD + c] : 0.f;
+        pr[it] = h < hn ? (sz ? ly.kz : ly.ks)[((size_t)(h0 + h) * (a.head_rows / G) + first / G + gi) * kD + c] : 0.f;
       }
-      if (h0 == 0) fold_partials();
-      if (h0 > 0 && !PER_HEAD) __syncthreads();  // the previous chunk's parameters are no longer read
-#pragma unroll
-      for (int it = 0; it < kPrmIter; ++it) prm[tid + it * 256] = pr[it];
-    } else {
-      if (h0 == 0) fold_partials();
     }
-    __syncthreads();
+    if (h0 > 0) __syncthreads();  // the previous chunk's rows and parameters are no longer read
+    if constexpr (PER_HEAD) {
+      if (SYNC && h0 == 0) wait_for(ly.sync + kPoolDone, 2 * H);
+      for (int i = tid; i < hn * kD; i += THREADS) qtilde[i] = head_query<SYNC>(ly, h0 + i / kD, i % kD);
+    }
+    if constexpr (kQuant) {
 #pragma unroll
-    for (int h = 0; h < HMAX; ++h) {
+      for (int it = 0; it < kPrmIter; ++it) prm[tid + it * THREADS] = pr[it];
+    }
+    if (kQuant || PER_HEAD) __syncthreads();
+#pragma unroll
+    for (int h = 0; h < kHeadChunk; ++h) {
       if (h < hn) {
-        float x[16];  // head h's key row (this thread's 16 channels), dequantized view
+        float x[8];  // head h's key row (this thread's 8 channels), dequantized view
         if constexpr (kQuant) {
-          const float* ks = prm + ((h * kGroups + (r / G) % kGroups) * 2) * kD + cq * 16;
+          const float* ks = prm + ((h * kGroups + (r / G) % kGroups) * 2) * kD + c8 * 8;
           const float* kz = ks + kD;
-          // codes to floats by bytes: one mask per 4 (4-bit: per 8) codes, then one byte-to-float conversion each,
+          // codes to floats by bytes: one mask per 4 (2-bit: 2) codes, then one byte-to-float conversion each,
           // instead of a bit-field extract and a conversion per code
-          float code[16];
+          constexpr int kPerByte = 8 / BITS;
+          const uint32_t codes = BITS == 4 ? w[h][0] : w[h][0] >> (16 * (c8 & 1));
+          float code[8];
 #pragma unroll
-          for (int d = 0; d < kDwT; ++d) {
-            constexpr int kPerDw = 32 / BITS;  // 8 or 16 codes per dword
+          for (int sft = 0; sft < kPerByte; ++sft) {  // code e sits in byte e / kPerByte of (codes >> BITS * (e % kPerByte)) & mask
+            uint32_t t = (codes >> (BITS * sft)) & (BITS == 4 ? 0x0f0f0f0fu : 0x03030303u);
+            asm volatile("" : "+v"(t));  // (keeps the mask shared by the conversions below)
 #pragma unroll
-            for (int sft = 0; sft < 8 / BITS; ++sft) {  // code e of the dword sits in byte e / (8 / BITS) of (w >> BITS * (e % (8 / BITS))) & mask
-              uint32_t t = (w[h][d] >> (BITS * sft)) & (BITS == 4 ? 0x0f0f0f0fu : 0x03030303u);
-              asm volatile("" : "+v"(t));  // (keeps the mask shared by the four conversions below)
-#pragma unroll
-              for (int b = 0; b < 4; ++b) code[d * kPerDw + b * (8 / BITS) + sft] = (float)((t >> (8 * b)) & 0xffu);
-            }
+            for (int b = 0; b < 8 / kPerByte; ++b) code[b * kPerByte + sft] = (float)((t >> (8 * b)) & 0xffu);
           }
           // canonical view, rounded to bf16 in pairs (one packed conversion per two values)
 #pragma unroll
-          for (int e = 0; e < 16; e += 2) {
+          for (int e = 0; e < 8; e += 2) {
             typedef __attribute__((ext_vector_type(2))) float f2;
             typedef __attribute__((ext_vector_type(2))) __bf16 b2;
             const f2 v = {(code[e] - kz[e]) * ks[e], (code[e + 1] - kz[e + 1]) * ks[e + 1]};
@@ -197,58 +218,38 @@ __global__ __launch_bounds__(256) void score_kernel(const ScoreArgs a) {
           }
         } else {
 #pragma unroll
-          for (int e = 0; e < 8; ++e) {
+          for (int e = 0; e < 4; ++e) {
             x[2 * e] = bf16_lo(w[h][e]);
             x[2 * e + 1] = bf16_hi(w[h][e]);
           }
         }
         if constexpr (PER_HEAD) {
-          const float* qt = qtilde + h * kD + cq * 16;
-          float dot = 0.f;
-#pragma unroll
-          for (int e = 0; e < 16; ++e) dot += qt[e] * x[e];
-          dot += __shfl_xor(dot, 1);
-          dot += __shfl_xor(dot, 2);
-          if (valid && cq == 0)
-            a.ws.scores[list_index(a.ws.sets, a.b.layer0 + lb, h0 + h) * a.ws.scores_stride + (pos - a.T_first)] = dot;
+          store_score(h0 + h, dot16(qtilde + h * kD + c8 * 8, x));
         } else {
 #pragma unroll
-          for (int e = 0; e < 16; ++e) acc[e] += x[e];
+          for (int e = 0; e < 8; ++e) acc[e] += x[e];
         }
       }
     }
   }
-  if constexpr (PER_HEAD) return;
-  const float* qt = qtilde + cq * 16;
-  float dot = 0.f;
-  const float fH = (float)H;
+  if constexpr (!PER_HEAD) {
+    const float fH = (float)H;
 #pragma unroll
-  for (int e = 0; e < 16; ++e) dot += qt[e] * (acc[e] / fH);
-  dot += __shfl_xor(dot, 1);
-  dot += __shfl_xor(dot, 2);
-  if (valid && cq == 0) a.ws.scores[list_index(a.ws.sets, a.b.layer0 + lb, 0) * a.ws.scores_stride + (pos - a.T_first)] = dot;
+    for (int e = 0; e < 8; ++e) acc[e] /= fH;
+    if (tid < kD) {
+      if (SYNC) wait_for(ly.sync + kPoolDone, 2 * H);
+      float s = 0.f;
+#pragma unroll 8
+      for (int h = 0; h < H; ++h) s += head_query<SYNC>(ly, h, tid);
+      qtilde[tid] = s;
+    }
+    __syncthreads();
+    store_score(0, dot16(qtilde + c8 * 8, acc));
+  }
+  if (SYNC) arrive(ly.sync + kScoreDone);
 }
 
-template <bool PER_HEAD>
-static hipError_t launch_score_t(const ScoreArgs& a, hipStream_t stream) {
-  const int first_block = a.T_first / kTile;
-  const int last_block = (a.T_first + a.P - 1) / kTile;
-  const dim3 grid(last_block - first_block + 1, a.b.n_layers);
-  const int bits = a.k_plain ? 16 : a.pool.bits, G = a.pool.G;
-  if (bits == 16) hipLaunchKernelGGL((score_kernel<16, 64, 16, PER_HEAD>), grid, dim3(256), 0, stream, a);
-  else if (bits == 4 && G == 64) hipLaunchKernelGGL((score_kernel<4, 64, 16, PER_HEAD>), grid, dim3(256), 0, stream, a);
-  else if (bits == 4 && G == 32) hipLaunchKernelGGL((score_kernel<4, 32, 16, PER_HEAD>), grid, dim3(256), 0, stream, a);
-  else if (bits == 2 && G == 64) hipLaunchKernelGGL((score_kernel<2, 64, 16, PER_HEAD>), grid, dim3(256), 0, stream, a);
-  else if (bits == 2 && G == 32) hipLaunchKernelGGL((score_kernel<2, 32, 16, PER_HEAD>), grid, dim3(256), 0, stream, a);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
-}
-
-hipError_t launch_score(const ScoreArgs& a, hipStream_t stream) {
-  return a.per_head ? launch_score_t<true>(a, stream) : launch_score_t<false>(a, stream);
-}
-
-// ---- selection --------------------------------------------------------------------------------------
+// ---- select --------------------------------------------------------------------------------------------
 
 // float → unsigned key with the same order (larger score ↔ larger key); -0 and +0 stay distinct
 // neighbours, which only matters for exact-zero scores.
@@ -257,149 +258,253 @@ __device__ __forceinline__ uint32_t order_key(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-constexpr int kSelThreads = 256;  // 4 waves: cheap barriers; one histogram bin per thread
-
-// exclusive prefix sums of two counters over the workgroup's threads, in thread order
-__device__ __forceinline__ void block_exclusive_scan2(int& a, int& b, int* sh /* 2*16 */, int& total_a, int& total_b) {
-  static_assert(kSelThreads / 64 <= 16, "wave totals live in 16 slots");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int ia = a, ib = b;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int ta = __shfl_up(ia, d), tb = __shfl_up(ib, d);
-    if (lane >= d) { ia += ta; ib += tb; }
-  }
-  if (lane == 63) { sh[wave] = ia; sh[16 + wave] = ib; }
-  __syncthreads();
-  int oa = 0, ob = 0;
-  total_a = 0; total_b = 0;
-  for (int w = 0; w < kSelThreads / 64; ++w) {
-    if (w < wave) { oa += sh[w]; ob += sh[16 + w]; }
-    total_a += sh[w]; total_b += sh[16 + w];
-  }
-  a = oa + ia - a;
-  b = ob + ib - b;
-  __syncthreads();
+// inclusive sum over the lanes up to this one, by lane shifts of the ALU
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);   // row_shr:1
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true);   // row_shr:2
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);   // row_shr:4
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);   // row_shr:8
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return x;
 }
 
-// one workgroup per list (layer, or layer and head); KPT > 0: each thread keeps its (at most KPT) keys in registers
-template <int KPT>
-__global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectArgs a) {
-  __shared__ int hist[256];
-  __shared__ int wave_tot[4];
-  __shared__ int sh_scan[32];
-  __shared__ uint32_t sh_prefix;
-  __shared__ int sh_need;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const float* scores = a.scores + (size_t)blockIdx.x * a.scores_stride;
-  int32_t* keep = a.keep + (size_t)blockIdx.x * a.keep_stride;
+constexpr int kBins = 2048, kBinsT = kBins / kThreads;  // bins, and bins per thread
+constexpr int kSelWaves = kThreads / 64;
+constexpr int kSelLds = kBins + 2 * kSelWaves + 2 + 2 * 64;
+
+// One list.  A wave holds chunks of 64 consecutive scores, one per lane: chunk c belongs to wave c % kSelWaves.  KPT: scores per
+// thread; lists longer than KPT * kThreads are read again in every pass, a segment of so many at a time.
+template <int KPT, bool SYNC>
+__device__ __forceinline__ void select_part(const SelectArgs& a, int list, uint32_t* lds) {
+  static_assert(KPT * kSelWaves <= 128, "two chunks per lane in the prefix sums of the compaction");
+  uint32_t* hist = lds;
+  uint32_t* wave_tot = hist + kBins;           // [2][kSelWaves]: by the parity of the pass
+  uint32_t* found = wave_tot + 2 * kSelWaves;  // digit, rank inside it
+  uint32_t* counts = found + 2;                // per chunk of a segment: kept | equal << 16
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float* scores = a.scores + (size_t)list * a.scores_stride;
+  int32_t* keep = a.keep + (size_t)list * a.keep_stride;
   const int P = a.P, k = a.k;
+  constexpr int kSegment = KPT * kThreads;
+  const int segments = (P + kSegment - 1) / kSegment;
 
-  // thread t owns the contiguous positions [t*per, (t+1)*per)
-  const int per = (P + kSelThreads - 1) / kSelThreads;
-  const int j0 = min(P, tid * per), j1 = min(P, j0 + per);
-  uint32_t keys[KPT > 0 ? KPT : 1];
-  if constexpr (KPT > 0) {
+  uint32_t keys[KPT];
+  auto at = [&](int segment, int i) { return segment * kSegment + 64 * (i * kSelWaves + wave) + lane; };
+  auto load = [&](int segment) {
 #pragma unroll
-    for (int i = 0; i < KPT; ++i) keys[i] = (j0 + i < j1) ? order_key(scores[j0 + i]) : 0u;
-  }
-  auto key_at = [&](int i) -> uint32_t {  // i-th key of this thread
-    if constexpr (KPT > 0) return keys[i];
-    else return order_key(scores[j0 + i]);
+    for (int i = 0; i < KPT; ++i) {
+      const int j = at(segment, i);
+      keys[i] = j < P ? order_key(SYNC ? load_agent(scores + j) : scores[j]) : 0u;
+    }
   };
+  load(0);
+  for (int i = tid; i < a.T_first; i += kThreads) keep[i] = i;
+  for (int i = tid; i < a.T_cur; i += kThreads) keep[a.T_first + k + i] = a.T_first + P + i;
 
-  // k-th largest key by radix select, most significant byte first
+  // k-th largest key by radix select, most significant digit first
   uint32_t prefix = 0;
-  int need = k;  // rank still to find inside the current prefix class (1-based from the top)
+  uint32_t need = k;  // rank still to find inside the current prefix class (1-based from the top)
 #pragma unroll
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    hist[tid] = 0;
+  for (int pass = 0; pass < 3; ++pass) {
+    const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
+    const uint32_t digits = pass == 2 ? 1023u : 2047u, hi_mask = pass == 0 ? 0u : ~((digits << shift) | ((1u << shift) - 1u));
+#pragma unroll
+    for (int b = 0; b < kBinsT; ++b) hist[b * kThreads + tid] = 0;
     __syncthreads();
-    const uint32_t hi_mask = pass == 0 ? 0u : (0xffffffffu << (shift + 8));
-    if constexpr (KPT > 0) {
+    for (int s = 0; s < segments; ++s) {
+      if (segments > 1) load(s);
 #pragma unroll
       for (int i = 0; i < KPT; ++i)
-        if (j0 + i < j1 && (keys[i] & hi_mask) == prefix) atomicAdd(&hist[(keys[i] >> shift) & 255u], 1);
-    } else {
-      for (int i = 0; i < j1 - j0; ++i) {
-        const uint32_t key = key_at(i);
-        if ((key & hi_mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1);
-      }
+        if (at(s, i) < P && (keys[i] & hi_mask) == prefix) atomicAdd(&hist[(keys[i] >> shift) & digits], 1u);
     }
     __syncthreads();
-    // bin b holds the wanted rank iff  (#keys in bins above b) < need <= (that + hist[b]);
-    // suffix sums over the 256 bins: per-wave shuffle scan + 4 wave totals
-    const int h = hist[tid];
-    int incl = h;
+    // thread t looks at the t-th kBinsT bins from the top; the wanted rank lies in bin b iff
+    // (#keys in bins above b) < need <= (that + hist[b])
+    uint32_t h[kBinsT], mine = 0;
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int v = __shfl_down(incl, d);
-      if (lane + d < 64) incl += v;
+    for (int b = 0; b < kBinsT; ++b) {
+      h[b] = hist[kBins - 1 - (tid * kBinsT + b)];
+      mine += h[b];
     }
-    if (lane == 0) wave_tot[wave] = incl;
+    const uint32_t incl = wave_prefix(mine);
+    uint32_t* tot = wave_tot + (pass & 1) * kSelWaves;
+    if (lane == 63) tot[wave] = incl;
     __syncthreads();
-    int above = incl - h;
-    for (int w = wave + 1; w < 4; ++w) above += wave_tot[w];
-    if (above < need && need <= above + h) {
-      sh_prefix = prefix | ((uint32_t)tid << shift);
-      sh_need = need - above;
+    uint32_t above = incl - mine;
+    for (int w = 0; w < wave; ++w) above += tot[w];
+#pragma unroll
+    for (int b = 0; b < kBinsT; ++b) {
+      if (above < need && need <= above + h[b]) {
+        found[0] = kBins - 1 - (tid * kBinsT + b);
+        found[1] = need - above;
+      }
+      above += h[b];
     }
     __syncthreads();
-    prefix = sh_prefix;
-    need = sh_need;
+    prefix |= found[0] << shift;
+    need = found[1];
   }
-  const uint32_t thr = prefix;  // key of the k-th largest score
-  const int need_eq = need;     // how many of the scores equal to it are kept (smallest positions)
+  const uint32_t thr = prefix;  // key of the k-th largest score; `need` of the scores equal to it are kept (smallest positions)
 
   // ordered compaction
-  int n_gt = 0, n_eq = 0;
-  for (int i = 0; i < j1 - j0; ++i) {
-    const uint32_t key = key_at(i);
-    n_gt += key > thr;
-    n_eq += key == thr;
-  }
-  int gt_before = n_gt, eq_before = n_eq, tot_gt, tot_eq;
-  block_exclusive_scan2(gt_before, eq_before, sh_scan, tot_gt, tot_eq);
-  int out = a.T_first + gt_before + min(eq_before, need_eq);
-  int eq_rank = eq_before;
-  for (int i = 0; i < j1 - j0; ++i) {
-    const uint32_t key = key_at(i);
-    bool take = key > thr;
-    if (key == thr) {
-      take = eq_rank < need_eq;
-      ++eq_rank;
+  uint32_t gt_before = 0, eq_before = 0;  // in the segments before
+  for (int s = 0; s < segments; ++s) {
+    if (segments > 1) {
+      __syncthreads();  // (the counts of the segment before have been read)
+      load(s);
     }
-    if (take) keep[out++] = a.T_first + j0 + i;
+    unsigned long long gt[KPT], eq[KPT];
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) {
+      const bool in = at(s, i) < P;
+      gt[i] = __ballot(in && keys[i] > thr);
+      eq[i] = __ballot(in && keys[i] == thr);
+      if (lane == 0) counts[i * kSelWaves + wave] = (uint32_t)__popcll(gt[i]) | (uint32_t)__popcll(eq[i]) << 16;
+    }
+    __syncthreads();
+    // (a segment holds at most 8192 scores, so that neither half overflows)
+    const uint32_t c0 = 2 * lane < KPT * kSelWaves ? counts[2 * lane] : 0u, c1 = 2 * lane < KPT * kSelWaves ? counts[2 * lane + 1] : 0u;
+    const uint32_t incl = wave_prefix(c0 + c1);
+    const unsigned long long below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) {
+      const int chunk = i * kSelWaves + wave;
+      uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)(incl - c0 - c1), chunk >> 1);
+      if (chunk & 1) before += (uint32_t)__builtin_amdgcn_readlane((int)c0, chunk >> 1);
+      const uint32_t g = gt_before + (before & 0xffffu) + (uint32_t)__popcll(gt[i] & below);
+      const uint32_t e = eq_before + (before >> 16) + (uint32_t)__popcll(eq[i] & below);
+      const bool take = ((gt[i] >> lane) & 1) || (((eq[i] >> lane) & 1) && e < need);
+      if (take) keep[a.T_first + g + min(e, need)] = a.T_first + at(s, i);
+    }
+    const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    gt_before += all & 0xffffu;
+    eq_before += all >> 16;
   }
-  for (int i = tid; i < a.T_first; i += kSelThreads) keep[i] = i;
-  for (int i = tid; i < a.T_cur; i += kSelThreads) keep[a.T_first + k + i] = a.T_first + P + i;
 }
 
-hipError_t launch_select(const SelectArgs& a, hipStream_t stream) {
-  static_assert(kSelThreads == 256, "one histogram bin per thread");
-  if (a.P <= 16 * kSelThreads) hipLaunchKernelGGL(select_kernel<16>, dim3(a.n_lists), dim3(kSelThreads), 0, stream, a);
-  else if (a.P <= 32 * kSelThreads) hipLaunchKernelGGL(select_kernel<32>, dim3(a.n_lists), dim3(kSelThreads), 0, stream, a);
-  else hipLaunchKernelGGL(select_kernel<0>, dim3(a.n_lists), dim3(kSelThreads), 0, stream, a);
+// ---- kernels -------------------------------------------------------------------------------------------
+constexpr int max_of(int a, int b) { return a > b ? a : b; }
+
+// One layer: 2 H pool, then score, then select workgroups.
+template <int BITS, int G, bool PER_HEAD, int KPT>
+__global__ __launch_bounds__(kThreads) void front_kernel(const FrontArgsT<1> args) {
+  constexpr int kLds = max_of(max_of(kPoolLds, score_lds<BITS, G, PER_HEAD>()), kSelLds);
+  __shared__ __attribute__((aligned(16))) float lds[kLds];
+#if defined(__HIP_DEVICE_COMPILE__)
+  {
+    // every field of the arguments that is read further down would wait for its own line of them: all lines at once
+    const uint32_t* w = static_cast<const uint32_t*>(__builtin_amdgcn_kernarg_segment_ptr());
+    static_assert(sizeof(args) > 128 && sizeof(args) <= 4 * 64, "four loads reach every line");
+    const uint32_t w0 = w[0], w1 = w[16], w2 = w[32], w3 = w[sizeof(args) / 4 - 1];
+    asm volatile("" ::"s"(w0), "s"(w1), "s"(w2), "s"(w3));
+  }
+#endif
+  const FrontCommon& a = args.c;
+  const FrontLayer& ly = args.layer[0];
+  const int b = blockIdx.x;
+  if (b < 2 * a.H) {
+    pool_part<true>(ly, a, b >> 1, b & 1, lds);
+  } else if (b < 2 * a.H + a.score_wgs) {
+    score_part<BITS, G, PER_HEAD, kThreads, true>(ly, a, b - 2 * a.H, lds);
+  } else {
+    wait_for(ly.sync + kScoreDone, a.score_wgs);
+    __syncthreads();
+    const uint32_t lists = PER_HEAD ? a.H : 1;
+    // the last one of a layer to have seen that leaves the counters as it found them
+    if (threadIdx.x == 0 && __hip_atomic_fetch_add(ly.sync + kSelectSeen, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == lists - 1) {
+      for (int i = 0; i < 3; ++i) store_agent(ly.sync + i, 0u);
+    }
+    const SelectArgs s{ly.scores, ly.keep, a.stride, a.stride, a.P, a.k, a.T_first, a.T_cur};
+    select_part<KPT, true>(s, b - 2 * a.H - a.score_wgs, reinterpret_cast<uint32_t*>(lds));
+  }
+}
+
+// The parts by themselves, for many layers at a time and for plain bf16 keys.
+template <int LAYERS>
+__global__ __launch_bounds__(kThreads) void pool_kernel(const FrontArgsT<LAYERS> args) {
+  __shared__ float lds[kPoolLds];
+  pool_part<false>(args.layer[blockIdx.y], args.c, blockIdx.x >> 1, blockIdx.x & 1, lds);
+}
+template <int BITS, int G, bool PER_HEAD, int THREADS, int LAYERS>
+__global__ __launch_bounds__(THREADS) void score_kernel(const FrontArgsT<LAYERS> args) {
+  __shared__ __attribute__((aligned(16))) float lds[score_lds<BITS, G, PER_HEAD>()];
+  score_part<BITS, G, PER_HEAD, THREADS, false>(args.layer[blockIdx.y], args.c, blockIdx.x, lds);
+}
+template <int KPT>
+__global__ __launch_bounds__(kThreads) void select_kernel(const SelectArgs a) {
+  __shared__ uint32_t lds[kSelLds];
+  select_part<KPT, false>(a, blockIdx.x, lds);
+}
+
+static int score_blocks(const FrontCommon& c, int rows) { return (c.T_first + c.P - 1) / rows - c.T_first / rows + 1; }
+
+constexpr int kPlainThreads = 128;  // 16 positions: a list of 2722 is then spread over 170 workgroups (pool and score of
+// 16 heads: 28.6 us with 43, 10.0 with 170)
+hipError_t launch_score(const FrontArgs& a, hipStream_t stream) {
+  const FrontArgsT<1> one{a.c, {a.layer[0]}};
+  hipLaunchKernelGGL(pool_kernel<1>, dim3(2 * a.c.H), dim3(kThreads), 0, stream, one);
+  hipLaunchKernelGGL((score_kernel<16, 64, false, kPlainThreads, 1>), dim3(score_blocks(a.c, kPlainThreads / 8)), dim3(kPlainThreads), 0,
+                     stream, one);
   return hipGetLastError();
 }
 
-// keep = [0, T_first) ∪ (middle, if kept) ∪ current
-__global__ __launch_bounds__(256) void fill_keep_kernel(int32_t* keep, int keep_stride, int T_first, int P, int T_cur,
-                                                        int keep_middle) {
-  int32_t* out = keep + (size_t)blockIdx.y * keep_stride;
-  const int total = T_first + (keep_middle ? P : 0) + T_cur;
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= total) return;
-  out[i] = (keep_middle || i < T_first) ? i : i + P;
+// Scores per thread of a select workgroup: 8 while they do (4096 scores), since all of them are looked at in every pass.
+static bool few_scores(int P) { return P <= 8 * kThreads; }
+
+hipError_t launch_select(const SelectArgs& a, int n_lists, hipStream_t stream) {
+  if (few_scores(a.P)) hipLaunchKernelGGL(select_kernel<8>, dim3(n_lists), dim3(kThreads), 0, stream, a);
+  else hipLaunchKernelGGL(select_kernel<16>, dim3(n_lists), dim3(kThreads), 0, stream, a);
+  return hipGetLastError();
 }
 
-hipError_t launch_fill_keep(int32_t* keep, int keep_stride, int n_lists, int T_first, int P, int T_cur, bool keep_middle,
-                            hipStream_t stream) {
+template <int BITS, int G, bool PER_HEAD>
+static hipError_t launch_front_t(FrontArgs& a, hipStream_t stream) {
+  FrontCommon& c = a.c;
+  c.score_wgs = score_blocks(c, kTile);
+  const int lists = PER_HEAD ? c.H : 1;
+  if (c.n_layers == 1) {
+    const dim3 grid(2 * c.H + c.score_wgs + lists);
+    const FrontArgsT<1> one{c, {a.layer[0]}};
+    if (few_scores(c.P)) hipLaunchKernelGGL((front_kernel<BITS, G, PER_HEAD, 8>), grid, dim3(kThreads), 0, stream, one);
+    else hipLaunchKernelGGL((front_kernel<BITS, G, PER_HEAD, 16>), grid, dim3(kThreads), 0, stream, one);
+    return hipGetLastError();
+  }
+  // Many layers: their parts fill the chip by themselves, and workgroups that wait only hold places that others could use
+  // (24 layers of the sizes above: 104 us as one launch, 46 as three).
+  hipLaunchKernelGGL(pool_kernel<kMaxBatch>, dim3(2 * c.H, c.n_layers), dim3(kThreads), 0, stream, a);
+  hipLaunchKernelGGL((score_kernel<BITS, G, PER_HEAD, kThreads, kMaxBatch>), dim3(c.score_wgs, c.n_layers), dim3(kThreads), 0, stream, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  // (the lists of consecutive layers follow each other)
+  return launch_select(SelectArgs{a.layer[0].scores, a.layer[0].keep, c.stride, c.stride, c.P, c.k, c.T_first, c.T_cur}, c.n_layers * lists, stream);
+}
+
+hipError_t launch_front(FrontArgs& a, int bits, int G, hipStream_t stream) {
+  auto launch = [&](auto b, auto g) {
+    constexpr int BITS = decltype(b)::value, GROUP = decltype(g)::value;
+    return a.c.per_head ? launch_front_t<BITS, GROUP, true>(a, stream) : launch_front_t<BITS, GROUP, false>(a, stream);
+  };
+  using std::integral_constant;
+  if (bits == 16) return launch(integral_constant<int, 16>{}, integral_constant<int, 64>{});
+  if (bits == 4 && G == 64) return launch(integral_constant<int, 4>{}, integral_constant<int, 64>{});
+  if (bits == 4 && G == 32) return launch(integral_constant<int, 4>{}, integral_constant<int, 32>{});
+  if (bits == 2 && G == 64) return launch(integral_constant<int, 2>{}, integral_constant<int, 64>{});
+  if (bits == 2 && G == 32) return launch(integral_constant<int, 2>{}, integral_constant<int, 32>{});
+  return hipErrorInvalidValue;
+}
+
+// keep = [0, T_first) ∪ (middle, if kept) ∪ current
+__global__ __launch_bounds__(256) void fill_keep_kernel(int32_t* keep, int T_first, int P, int T_cur, int keep_middle) {
+  const int total = T_first + (keep_middle ? P : 0) + T_cur;
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < total) keep[i] = (keep_middle || i < T_first) ? i : i + P;
+}
+
+hipError_t launch_fill_keep(int32_t* keep, int T_first, int P, int T_cur, bool keep_middle, hipStream_t stream) {
   const int total = T_first + (keep_middle ? P : 0) + T_cur;
   if (total <= 0) return hipSuccess;
-  hipLaunchKernelGGL(fill_keep_kernel, dim3((total + 255) / 256, n_lists), dim3(256), 0, stream, keep, keep_stride,
-                     T_first, P, T_cur, keep_middle ? 1 : 0);
+  hipLaunchKernelGGL(fill_keep_kernel, dim3((total + 255) / 256), dim3(256), 0, stream, keep, T_first, P, T_cur, keep_middle ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -33,6 +33,7 @@ struct LayerState {
   int pending_Tn = 0;   // keep length decided by score_prune
   int last_P = 0;       // scores computed by the last score_prune (0 if none)
   int last_keep = 0;
+  int last_cut = 0;     // tokens it left out
 };
 
 }  // namespace
@@ -348,38 +349,30 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
 
 int do_score_prune(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q) {
   const PrunePlan p = plan_for(ctx->cfg, ctx->layers[layer0]);
-  // the lists of layers [layer0, layer0 + n_layers) are contiguous: sets per layer
-  const int sets = ctx->ws.sets, n_lists = n_layers * sets;
-  int32_t* keep = ctx->ws.keep + list_index(sets, layer0, 0) * ctx->ws.scores_stride;
-  if (!p.prune) {
-    if (launch_fill_keep(keep, ctx->ws.scores_stride, n_lists, p.T, 0, 0, true, ctx->work) != hipSuccess) return hip_fail(ctx);
-  } else if (!p.score) {
-    // k == 0: first ∪ current;  k == P: everything (cannot happen once T > budget, kept for completeness)
-    if (launch_fill_keep(keep, ctx->ws.scores_stride, n_lists, p.T_first, p.P, p.T_cur, p.k == p.P, ctx->work) != hipSuccess)
-      return hip_fail(ctx);
-  } else {
-    ScoreArgs s{};
-    int rc = fill_batch(ctx, s.b, layer0, n_layers, q, nullptr, nullptr, nullptr);
+  // Without scores (nothing is pruned, or nothing of the middle kept) there is nothing to launch: the re-quantization knows
+  // where its rows come from (RequantArgs::identity_end) and xsv_last_selection what the list would be.
+  if (p.score) {
+    Batch b;
+    int rc = fill_batch(ctx, b, layer0, n_layers, q, nullptr, nullptr, nullptr);
     if (rc != XSV_OK) return rc;
-    s.pool = ctx->pool;
-    s.ws = ctx->ws;
-    s.Tc = ctx->layers[layer0].T;
-    s.n = ctx->cfg.tokens_per_frame;
-    s.n_special = ctx->cfg.n_special;
-    s.pool_size = ctx->cfg.pool_size;
-    s.T_first = p.T_first;
-    s.P = p.P;
-    s.k_plain = nullptr;
-    s.per_head = ctx->cfg.score_mode == 1;
-    if (launch_pool_query(s, ctx->work) != hipSuccess) return hip_fail(ctx);
-    if (launch_score(s, ctx->work) != hipSuccess) return hip_fail(ctx);
-    SelectArgs sel{};
-    sel.scores = ctx->ws.scores + list_index(sets, layer0, 0) * ctx->ws.scores_stride;
-    sel.keep = keep;
-    sel.scores_stride = sel.keep_stride = ctx->ws.scores_stride;
-    sel.n_lists = n_lists;
-    sel.P = p.P; sel.k = p.k; sel.T_first = p.T_first; sel.T_cur = p.T_cur;
-    if (launch_select(sel, ctx->work) != hipSuccess) return hip_fail(ctx);
+    FrontArgs f;
+    const Workspace& ws = ctx->ws;
+    const int sets = ws.sets;
+    for (int i = 0; i < n_layers; ++i) {
+      const int l = layer0 + i;
+      const LayerCache lc = layer_cache(ctx->pool, b.src_buf(i), l);
+      const size_t list = list_index(sets, l, 0) * ws.scores_stride;
+      f.layer[i] = FrontLayer{b.q[i], lc.kc, lc.ks, lc.kz, ws.qpart + (size_t)l * ctx->pool.H * kPoolParts * kD, ws.scores + list, ws.keep + list, ws.sync + 4 * l};
+    }
+    f.c = FrontCommon{};
+    f.c.q_sh = b.q_sh; f.c.q_st = b.q_st;
+    f.c.n_layers = n_layers; f.c.H = ctx->pool.H; f.c.n = ctx->cfg.tokens_per_frame;
+    f.c.n_special = ctx->cfg.n_special; f.c.pool_size = ctx->cfg.pool_size;
+    f.c.T_first = p.T_first; f.c.P = p.P; f.c.k = p.k; f.c.T_cur = p.T_cur;
+    f.c.head_rows = ctx->pool.Tcap;
+    f.c.stride = ws.scores_stride;
+    f.c.per_head = ctx->cfg.score_mode == 1;
+    if (launch_front(f, ctx->pool.bits, ctx->pool.G, ctx->work) != hipSuccess) return hip_fail(ctx);
   }
   for (int i = 0; i < n_layers; ++i) {
     LayerState& L = ctx->layers[layer0 + i];
@@ -387,6 +380,7 @@ int do_score_prune(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q) 
     L.pending_Tn = p.Tn;
     L.last_P = p.score ? p.P : 0;
     L.last_keep = p.Tn;
+    L.last_cut = p.T - p.Tn;
   }
   return XSV_OK;
 }
@@ -543,12 +537,12 @@ int xsv_create(const xsv_config* cfg, void* hip_stream, xsv_ctx** out) {
   Workspace& w = ctx->ws;
   std::memset(&w, 0, sizeof(w));
   w.scores_stride = p.Tcap + (int)n;
-  w.qpart_rows = c.n_heads * kPoolSeg;
   w.sets = p.sets;
   A(&ctx->stable_flag, (size_t)c.n_layers * c.n_heads * (p.Tcap / kTile), true);
   A(&w.scores, (size_t)c.n_layers * w.sets * w.scores_stride, true);
   A(&w.keep, (size_t)c.n_layers * w.sets * w.scores_stride, true);
-  A(&w.qpart, (size_t)c.n_layers * w.qpart_rows * kD, true);
+  A(&w.qpart, (size_t)c.n_layers * c.n_heads * kPoolParts * kD, true);
+  A(&w.sync, (size_t)c.n_layers * 4, true);
   // partial attention outputs: up to 16 key ranges for one layer, or 2 per layer when batched
   // (partials are stored in blocks of 32 query rows per head)
   const size_t part_rows = (size_t)std::max(16, 2 * std::min(c.n_layers, kMaxBatch)) * c.n_heads * round_up((int)n, 32);
@@ -1022,7 +1016,9 @@ int xsv_last_selection(xsv_ctx* ctx, int layer, int32_t* n_scores, float* scores
     if (scores && L.last_P > 0)
       good = hipMemcpyAsync(scores + (size_t)st * L.last_P, ctx->ws.scores + row, (size_t)L.last_P * 4, hipMemcpyDeviceToHost,
                             ctx->stream) == hipSuccess;
-    if (keep && L.last_keep > 0 && good)
+    if (keep && L.last_P == 0)  // no list was needed: everything, or the first and the current frame
+      for (int i = 0; i < L.last_keep; ++i) keep[(size_t)st * L.last_keep + i] = i < L.last_keep - ctx->cfg.tokens_per_frame ? i : i + L.last_cut;
+    else if (keep && L.last_keep > 0 && good)
       good = hipMemcpyAsync(keep + (size_t)st * L.last_keep, ctx->ws.keep + row, (size_t)L.last_keep * 4, hipMemcpyDeviceToHost,
                             ctx->stream) == hipSuccess;
   }
@@ -1063,26 +1059,27 @@ int xsv_quantize_v(void* hip_stream, const void* v_bf16, int H, int T, int d, in
   return quantize_plain(hip_stream, v_bf16, H, T, d, bits, G, codes_u8, scale, zero, false);
 }
 
+static FrontArgs plain_score(const xsv_tensor& q, const void* k_mid_bf16, int H, int n, int n_s, int P, int g, float* qpart, float* scores) {
+  FrontArgs f;
+  f.c = FrontCommon{};
+  f.c.q_sh = q.stride_head; f.c.q_st = q.stride_token;
+  f.c.n_layers = 1; f.c.H = H; f.c.n = n; f.c.n_special = n_s; f.c.pool_size = g;
+  f.c.P = P;
+  f.c.head_rows = P;
+  f.c.stride = P;
+  f.layer[0] = FrontLayer{static_cast<const uint16_t*>(q.ptr), static_cast<const uint8_t*>(k_mid_bf16), nullptr, nullptr, qpart, scores, nullptr, nullptr};
+  return f;
+}
+
 int xsv_score(void* hip_stream, xsv_tensor q, const void* k_mid_bf16, int H, int n, int n_s, int P, int d, int g,
               float* scores) {
   if (!tensor_ok(q) || !k_mid_bf16 || !scores || H < 1 || n < 1 || n_s < 0 || n_s > n || P < 1 || g < 1) return XSV_ERR_ARG;
   if (d != kD) return XSV_ERR_UNSUPPORTED;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   Temp tmp;
-  ScoreArgs s{};
-  s.pool.H = H; s.pool.L = 1; s.pool.bits = 16; s.pool.G = 64; s.pool.Tcap = round_up(P, kTile);
-  s.b.n_layers = 1; s.b.layer0 = 0;
-  s.b.q[0] = static_cast<const uint16_t*>(q.ptr);
-  s.b.q_sh = q.stride_head; s.b.q_st = q.stride_token;
-  s.ws.qpart_rows = H * kPoolSeg;
-  s.ws.sets = 1;
-  s.ws.qpart = tmp.get<float>((size_t)s.ws.qpart_rows * kD);
-  if (!s.ws.qpart) return XSV_ERR_OOM;
-  s.ws.scores = scores;
-  s.ws.scores_stride = P;
-  s.Tc = P; s.n = n; s.n_special = n_s; s.pool_size = g; s.T_first = 0; s.P = P;
-  s.k_plain = static_cast<const uint16_t*>(k_mid_bf16);
-  if (launch_pool_query(s, stream) != hipSuccess || launch_score(s, stream) != hipSuccess) return XSV_ERR_HIP;
+  float* qpart = tmp.get<float>((size_t)H * kPoolParts * kD);
+  if (!qpart) return XSV_ERR_OOM;
+  if (launch_score(plain_score(q, k_mid_bf16, H, n, n_s, P, g, qpart, scores), stream) != hipSuccess) return XSV_ERR_HIP;
   return hipStreamSynchronize(stream) == hipSuccess ? XSV_OK : XSV_ERR_HIP;
 }
 
@@ -1093,7 +1090,7 @@ int xsv_score(void* hip_stream, xsv_tensor q, const void* k_mid_bf16, int H, int
 // (each device holds its own copy) and that pointer is what the kernels get.
 constexpr int kNoAllocMaxHeads = XSV_NOALLOC_MAX_HEADS;
 constexpr int kNoAllocMaxDevices = 64;
-static __device__ __align__(256) float scratch[kNoAllocMaxHeads * kPoolSeg * kD];
+static __device__ __align__(256) float scratch[kNoAllocMaxHeads * kPoolParts * kD];
 
 static std::mutex g_scratch_mutex;
 static float* g_scratch_ptr[kNoAllocMaxDevices];  // device address of `scratch` on device i, once resolved
@@ -1124,20 +1121,9 @@ int xsv_score_noalloc(void* hip_stream, xsv_tensor q, const void* k_mid_bf16, in
   int rc = XSV_OK;
   float* qpart = scratch_of_current_device(&rc);
   if (!qpart) return rc;
-  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  ScoreArgs s{};
-  s.pool.H = H; s.pool.L = 1; s.pool.bits = 16; s.pool.G = 64; s.pool.Tcap = round_up(P, kTile);
-  s.b.n_layers = 1; s.b.layer0 = 0;
-  s.b.q[0] = static_cast<const uint16_t*>(q.ptr);
-  s.b.q_sh = q.stride_head; s.b.q_st = q.stride_token;
-  s.ws.qpart_rows = H * kPoolSeg;
-  s.ws.sets = 1;
-  s.ws.qpart = qpart;  // every entry a call reads is written by that call's pooling kernel first: nothing to clear
-  s.ws.scores = scores;
-  s.ws.scores_stride = P;
-  s.Tc = P; s.n = n; s.n_special = n_s; s.pool_size = g; s.T_first = 0; s.P = P;
-  s.k_plain = static_cast<const uint16_t*>(k_mid_bf16);
-  if (launch_pool_query(s, stream) != hipSuccess || launch_score(s, stream) != hipSuccess) return XSV_ERR_HIP;
+  // (every entry of the array a call reads is written by that call's pooling kernel first: nothing to clear)
+  const FrontArgs f = plain_score(q, k_mid_bf16, H, n, n_s, P, g, qpart, scores);
+  if (launch_score(f, static_cast<hipStream_t>(hip_stream)) != hipSuccess) return XSV_ERR_HIP;
   return XSV_OK;
 }
 
@@ -1146,11 +1132,11 @@ int xsv_topk_keep(void* hip_stream, const float* scores, int P, int k, int T_fir
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   hipError_t e;
   if (k == 0 || k == P) {
-    e = launch_fill_keep(keep, 0, 1, T_first, P, T_cur, k == P, stream);
+    e = launch_fill_keep(keep, T_first, P, T_cur, k == P, stream);
   } else {
     SelectArgs s{};
-    s.scores = scores; s.keep = keep; s.n_lists = 1; s.P = P; s.k = k; s.T_first = T_first; s.T_cur = T_cur;
-    e = launch_select(s, stream);
+    s.scores = scores; s.keep = keep; s.P = P; s.k = k; s.T_first = T_first; s.T_cur = T_cur;
+    e = launch_select(s, 1, stream);
   }
   if (e != hipSuccess) return XSV_ERR_HIP;
   return hipStreamSynchronize(stream) == hipSuccess ? XSV_OK : XSV_ERR_HIP;

@@ -21,10 +21,7 @@ namespace xsv {
 constexpr int kD = 64;         // head_dim
 constexpr int kTile = 64;      // tokens per value block and per attention key tile
 constexpr int kMaxBatch = 32;  // layers per batched launch
-// Row segments (workgroups) per head of the pooled-query pass.  One: beside the attention launch of a step
-// only a few compute units are idle when the chain starts, and with four segments (3 us faster alone) the
-// extra workgroups wait for units and the step as a whole gets 1.6 % slower.
-constexpr int kPoolSeg = 1;
+constexpr int kPoolParts = 4;    // partial sums per head of the pooled-query pass
 
 struct CachePool {
   uint8_t* kc;
@@ -100,12 +97,12 @@ struct Batch {
 struct Workspace {
   float* scores;      // [L][sets][Tcap + n]  importance of the middle tokens
   int32_t* keep;      // [L][sets][Tcap + n]  keep list
-  float* qpart;       // [L][qpart_rows = H * kPoolSeg][64] partial weighted query sums
+  float* qpart;       // [L][H][kPoolParts][64] partial weighted query sums
+  uint32_t* sync;     // [L][4] counters of front_kernel, zero between launches
   uint16_t* attn_o;   // [pieces][batch layers][H][ceil(n/32)] blocks of 32 rows x 64 fp16 mantissas of the unnormalized
                       // partial outputs, each block stored [16-byte piece 0..3][lane half][row] (4 KB)
   float* attn_ml;     // [pieces][batch layers][H][n][4]  softmax reference (log2 domain), row sum, row scale, -
   int scores_stride;  // Tcap + n
-  int qpart_rows;
   int sets;           // lists per layer (CachePool::sets)
 };
 
@@ -160,30 +157,46 @@ void partition_unit_query(long long n_units, int n_tiles, int n_wgs, int unit, i
 hipError_t launch_attend(const AttendArgs& a, hipStream_t stream, hipEvent_t between = nullptr);
 int attend_rows_per_workgroup(int variant);
 
-struct ScoreArgs {
-  CachePool pool;
-  Batch b;
-  Workspace ws;
-  int Tc, n, n_special, pool_size;
-  int T_first, P;  // middle = cache positions [T_first, T_first + P)
-  // stateless form: keys come from a plain bf16 tensor [H][P][64] instead of the pool
-  const uint16_t* k_plain;
-  int per_head;  // 1: no averages over heads, head h's scores go to list (layer, h)
+// Pool, score and select (score_select.hip).  One layer: device pointers, resolved on the host.
+struct FrontLayer {
+  const uint16_t* q;   // head 0
+  const uint8_t* kc;   // packed keys, scales and zero points of head 0 (plain keys: a bf16 tensor [H][P][64], T_first = 0)
+  const float* ks;
+  const float* kz;
+  float* qpart;        // [H][kPoolParts][64]
+  float* scores;       // first list of the layer
+  int32_t* keep;
+  uint32_t* sync;      // see Workspace
 };
-hipError_t launch_pool_query(const ScoreArgs& a, hipStream_t stream);
-hipError_t launch_score(const ScoreArgs& a, hipStream_t stream);
+struct FrontCommon {
+  int64_t q_sh, q_st;  // strides in elements
+  int n_layers, H, n, n_special, pool_size;
+  int T_first, P, k, T_cur;  // middle = cache positions [T_first, T_first + P), k of them are kept
+  int head_rows;       // key rows between two heads
+  int stride;          // between two lists
+  int per_head;        // 1: no averages over heads, head h has list h of the layer
+  int score_wgs;       // (filled by launch_front)
+};
+template <int LAYERS>
+struct FrontArgsT {
+  FrontCommon c;
+  FrontLayer layer[LAYERS];
+};
+using FrontArgs = FrontArgsT<kMaxBatch>;
+// Scores and keep lists of the layers' middle tokens, 0 < k < P.
+hipError_t launch_front(FrontArgs& a, int bits, int G, hipStream_t stream);
+// Scores of plain bf16 keys: two launches, no counters.
+hipError_t launch_score(const FrontArgs& a, hipStream_t stream);
 
 struct SelectArgs {
-  const float* scores;  // [n_lists][scores_stride]
-  int32_t* keep;        // [n_lists][keep_stride]
+  const float* scores;  // [lists][scores_stride]
+  int32_t* keep;        // [lists][keep_stride]
   int scores_stride, keep_stride;
-  int n_lists;          // layers x index sets per layer
   int P, k, T_first, T_cur;
 };
-hipError_t launch_select(const SelectArgs& a, hipStream_t stream);
-// keep = 0..T-1 (nothing pruned) or first ∪ current (k == 0)
-hipError_t launch_fill_keep(int32_t* keep, int keep_stride, int n_lists, int T_first, int P, int T_cur,
-                            bool keep_middle, hipStream_t stream);
+hipError_t launch_select(const SelectArgs& a, int n_lists, hipStream_t stream);
+// keep = 0..T-1 (keep_middle) or first ∪ current
+hipError_t launch_fill_keep(int32_t* keep, int T_first, int P, int T_cur, bool keep_middle, hipStream_t stream);
 
 struct RequantArgs {
   CachePool pool;

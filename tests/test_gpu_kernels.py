@@ -182,6 +182,25 @@ def test_topk_keep_bit_exact_with_ties(P, k):
         assert np.array_equal(keep, ref.select(scores.cpu().numpy(), k, 7, 5))
 
 
+@pytest.mark.parametrize("P", [2, 63, 64, 65, 511, 513, 4095, 4096, 4097, 8191, 8192, 8193, 16385])
+def test_topk_keep_at_the_edges_of_chunks_and_segments(P):
+    """Lists around a wave's chunk of 64 scores and the 4096 / 8192 scores a workgroup holds in registers; scores that differ
+    only in one of the three digits of their order keys, ties of both zeros, infinities."""
+    g = torch.Generator().manual_seed(P)
+    bits = torch.randint(0, 1 << 10, (P,), generator=g, dtype=torch.int32)
+    low = (0x3F800000 + bits).view(torch.float32)                                   # last digit only
+    middle = (0x3F800000 + (bits << 10)).view(torch.float32)                        # middle digit only
+    wild = torch.randn(P, generator=g) * torch.exp2(torch.randint(-100, 100, (P,), generator=g).float())
+    few = torch.tensor([0.0, -0.0, 1.0, -1.0, float("inf"), float("-inf")])[torch.randint(0, 6, (P,), generator=g)]
+    for scores in (low, -middle, wild, few):
+        for k in sorted({1, P // 2, P - 1}):
+            keep = xsv.topk_keep(scores.to(DEV), k, 3, 2).cpu().numpy()
+            key = scores.view(torch.int32).numpy().astype(np.int64)
+            key = np.where(key < 0, -(key & 0x7FFFFFFF) - 1, key)                   # the order of the scores, -0 below +0
+            order = np.sort(np.lexsort((np.arange(P), -key))[:k])
+            assert keep.tolist() == [0, 1, 2] + (order + 3).tolist() + [P + 3, P + 4], (P, k)
+
+
 def test_topk_keep_all_equal_scores_take_smallest_positions():
     scores = torch.zeros(1000, device=DEV)
     keep = xsv.topk_keep(scores, 10, 0, 0).cpu().numpy()

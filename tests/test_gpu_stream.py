@@ -175,6 +175,33 @@ def test_every_workgroup_shape_of_the_attention_kernel(variant, splits):
     ctx.destroy()
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+def test_long_lists_are_selected_exactly_and_unneeded_ones_are_reported(mode):
+    """Middles of more than the 8192 scores a select workgroup holds at a time, several layers and (mode 1) a list per head: the
+    keep list is the exact top-k of the reported scores.  Steps that need no scores report the list they stand for."""
+    H, n, budget, L = 2, 600, 9900, 2
+    ctx = xsv.Context(L, H, 64, n, 5, budget, 2, 64, score_mode=mode)
+    g = torch.Generator().manual_seed(mode)
+    T = 0
+    for f in range(19):
+        q, k, v = (torch.randn((H, n, 64), generator=g).to(torch.bfloat16).to(DEV) for _ in range(3))
+        for l in range(L):
+            ctx.step(l, q, k, v)
+        T += n
+        for l in range(L):
+            scores, keep = ctx.last_selection(l)
+            scores, keep = np.atleast_2d(scores), np.atleast_2d(keep)
+            if T <= budget:
+                assert scores.shape[-1] == 0 and all(row.tolist() == list(range(T)) for row in keep)
+            else:
+                P = T - 2 * n
+                assert scores.shape[-1] == P > 8192
+                for s, row in zip(scores, keep):
+                    assert np.array_equal(row, ref.select(s, budget - 2 * n, n, n))
+        T = min(T, budget)
+    ctx.destroy()
+
+
 def test_budget_below_two_frames_keeps_first_and_current():
     spec = CONFIGS[0].with_(name="k0", budget=100)
     run_stream(spec, 4)
