@@ -31,6 +31,9 @@ int xsv_set_short_range(xsv_ctx* ctx, int percent);
  * cache, in percent (25..400, default 95: bf16 rows need no dequantization).  When every (head, query block) is cut into the same key ranges, the
  * ranges are chosen to cost the same by this measure, so that all workgroups of a launch end together. */
 int xsv_set_frame_tile_cost(xsv_ctx* ctx, int percent);
+/* Tuning: how often a workgroup of the score launch of a layer looks for the pooled query, which others of the launch are working
+ * out, before it pools the queries by itself (0 .. 2^20, default 8192: some milliseconds).  Results are the same bit for bit. */
+int xsv_set_pool_polls(xsv_ctx* ctx, int polls);
 /* Measurement aid.  While enabled, every attention launch of this context (xsv_dequant_attend, xsv_step,
  * xsv_step_all_layers) is bracketed by events on the context's stream: before the attention kernel,
  * between it and the kernel that merges key-range partials, after, and once more right behind.

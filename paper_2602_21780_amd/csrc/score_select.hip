@@ -7,17 +7,19 @@
 //           by everybody who needs qtilde in one fixed order: reproducible bit for bit, no atomics on floats.
 //   score   one pass over the packed keys of the prunable middle: dequantized view,
 //           head mean, dot product with qtilde.  64 tokens x all heads per workgroup, 8 channels per thread, all loads of a
-//           workgroup issued before any use.
+//           workgroup issued before any use.  (Per-head lists: 256 tokens x one head.)
 //   select  exact top-k by radix select on order-preserving integer keys held in
 //           registers (digits of 11, 11 and 10 bits, histograms in LDS), ties at the threshold resolved toward smaller
 //           positions, then an ordered compaction that emits the keep list ascending.
 // front_kernel is all three in one launch for one layer, a role per workgroup.  Each part takes a few microseconds, most of it the latency of
 // a kernel's start, of its arguments and of one or two trips to memory: one layer of 16 heads x 1374 tokens with 2722 middle
 // positions took 21.2 us as three kernels with nothing beside them, and takes 13.8 as one.
-// A workgroup waits only for workgroups of a smaller index, which the hardware has started before it: score for its layer's pool
-// (only at the end, with the key means in registers), select for its layer's score.  What they hand over goes through
-// agent-scope stores and loads (past the caches that the dies of the chip do not share) and a counter per part; the last select
-// of a layer puts the counters back to zero.
+// Nothing in it waits without end, whatever else is on the chip.  The workgroup that completes a list's scores goes on to select
+// it.  A score workgroup does wait for the pool (only at the end, with the key means in registers), which has smaller indices and
+// as a rule has been started before it; but launches of several streams may hold the places each other's pools need, so the wait
+// is bounded (FrontCommon::polls) and a workgroup that runs out of patience pools the queries itself, in the same order.  What is
+// handed over goes through agent-scope stores and loads (past the caches that the dies of the chip do not share) and one counter
+// per list, which the last workgroup to arrive puts back to zero.
 //   Per-head variant (FrontCommon::per_head, not the paper's): the averages over heads are left out,
 //   qtilde_h comes from head h's partials alone and head h's keys give head h's own score vector and list.
 // Compiled with -ffp-contract=off: the dequantized view must be (code - zero) * scale with one
@@ -40,25 +42,41 @@ __device__ __forceinline__ T load_agent(const T* p) { return __hip_atomic_load(p
 template <typename T>
 __device__ __forceinline__ void store_agent(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// This workgroup's part is done.  (Its agent-scope stores have reached memory when a wave's count of outstanding ones is zero.)
-__device__ __forceinline__ void arrive(uint32_t* counter) {
+// FrontLayer::sync, one per list: pool workgroups that are done in the low half, score workgroups in the high half.
+constexpr uint64_t kPoolArrived = 1, kScoreArrived = 1ull << 32;
+// This workgroup's part is done; to thread 0 (only): the counter before that.  The last to arrive leaves zero.
+// (A wave's agent-scope stores have reached memory when its count of outstanding ones is zero.)
+__device__ __forceinline__ uint64_t arrive(uint64_t* counter, uint64_t mine, uint64_t all) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (threadIdx.x == 0) __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  uint64_t before = 0;
+  if (threadIdx.x == 0) {
+    before = __hip_atomic_fetch_add(counter, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (before + mine == all) store_agent(counter, (uint64_t)0);
+  }
+  return before;
 }
-// All `n` workgroups of the part in front are done.
-__device__ __forceinline__ void wait_for(const uint32_t* counter, uint32_t n) {
-  while (load_agent(counter) != n) __builtin_amdgcn_s_sleep(1);
+// `n` pool workgroups are done; false if they were not in the time that `polls` looks take.
+__device__ __forceinline__ bool wait_for_pool(const uint64_t* counter, uint32_t n, int polls) {
+  bool done = false;
+  for (int i = 0; i < polls && !done; ++i) {
+    done = (uint32_t)load_agent(counter) == n;
+    if (!done) __builtin_amdgcn_s_sleep(1);
+  }
   asm volatile("" ::: "memory");
+  return done;
 }
-enum { kPoolDone = 0, kScoreDone = 1, kSelectSeen = 2 };  // FrontLayer::sync
+// A list's arrivals.
+__device__ __forceinline__ uint32_t pools_of(const FrontCommon& a, bool per_head) { return per_head ? 2u : 2u * a.H; }
+__device__ __forceinline__ uint64_t all_of(const FrontCommon& a, bool per_head) {
+  return pools_of(a, per_head) * kPoolArrived + (uint64_t)a.blocks * kScoreArrived;
+}
 
 // ---- pool ----------------------------------------------------------------------------------------------
 constexpr int kPoolLds = (kThreads / 8) * (kD + 1);
 // Thread = (row lane, channel run).  A head has 128 row lanes (lane i: rows i, i + 128, ..), 64 to each of its two workgroups,
-// and each 32 lanes' sum is a partial.
-template <bool SYNC>
-__device__ __forceinline__ void pool_part(const FrontLayer& ly, const FrontCommon& a, int h, int half, float* lds) {
+// and each 32 lanes' sum is a partial: returned by threads tid < 128 for partial 2 * half + tid / 64, channel tid % 64.
+__device__ __forceinline__ float pool_partial(const FrontLayer& ly, const FrontCommon& a, int h, int half, float* lds) {
   float(*red)[kD + 1] = reinterpret_cast<float(*)[kD + 1]>(lds);
   const int H = a.H, n = a.n, n_s = a.n_special, g = a.pool_size;
   const int n_groups = (n - n_s + g - 1) / g, n_pooled = n_s + n_groups;
@@ -83,52 +101,88 @@ __device__ __forceinline__ void pool_part(const FrontLayer& ly, const FrontCommo
 #pragma unroll
   for (int e = 0; e < 8; ++e) red[rl][o * 8 + e] = acc[e];
   __syncthreads();
+  float s = 0.f;
   if (tid < 2 * kD) {
     const int sg = tid >> 6, c = tid & 63;
-    float s = 0.f;
 #pragma unroll
     for (int i = 0; i < 32; ++i) s += red[sg * 32 + i][c];
-    float* out = ly.qpart + ((size_t)h * kPoolParts + half * 2 + sg) * kD + c;
+  }
+  return s;
+}
+template <bool SYNC>
+__device__ __forceinline__ void pool_part(const FrontLayer& ly, const FrontCommon& a, int h, int half, float* lds) {
+  const float s = pool_partial(ly, a, h, half, lds);
+  const int tid = threadIdx.x;
+  if (tid < 2 * kD) {
+    float* out = ly.qpart + ((size_t)h * kPoolParts + half * 2) * kD + tid;
     if (SYNC) store_agent(out, s);
     else *out = s;
   }
-  if (SYNC) arrive(ly.sync + kPoolDone);
+  if (SYNC) arrive(ly.sync + (a.per_head ? h : 0), kPoolArrived, all_of(a, a.per_head));
 }
 
+static_assert(kPoolParts == 4, "the order of the sums");
+__device__ __forceinline__ float add_partials(const float* x) { return ((x[0] + x[1]) + x[2]) + x[3]; }
 // Channel c of head h's pooled query: its partials in order.
 template <bool SYNC>
 __device__ __forceinline__ float head_query(const FrontLayer& ly, int h, int c) {
-  static_assert(kPoolParts == 4, "the order of the sum");
   const float* p = ly.qpart + (size_t)h * kPoolParts * kD + c;
   float x[kPoolParts];
 #pragma unroll
   for (int i = 0; i < kPoolParts; ++i) x[i] = SYNC ? load_agent(p + i * kD) : p[i * kD];
-  return ((x[0] + x[1]) + x[2]) + x[3];
+  return add_partials(x);
+}
+
+// The sum of the pooled queries of heads [h0, h1) without the pool workgroups' help, to qtilde; `lds`: kPoolLds + kPoolParts * kD.
+__device__ __forceinline__ void pool_alone(const FrontLayer& ly, const FrontCommon& a, int h0, int h1, float* qtilde, float* lds) {
+  const int tid = threadIdx.x;
+  float* parts = lds + kPoolLds;
+  float sum = 0.f;
+  for (int h = h0; h < h1; ++h) {
+    for (int half = 0; half < 2; ++half) {
+      const float s = pool_partial(ly, a, h, half, lds);
+      if (tid < 2 * kD) parts[half * 2 * kD + tid] = s;
+      __syncthreads();
+    }
+    if (tid < kD) {
+      const float x[kPoolParts] = {parts[tid], parts[kD + tid], parts[2 * kD + tid], parts[3 * kD + tid]};
+      sum += add_partials(x);
+    }
+  }
+  if (tid < kD) qtilde[tid] = sum;
+  __syncthreads();
 }
 
 // ---- score ---------------------------------------------------------------------------------------------
+constexpr int kHeadTiles = 4;  // tiles of a score workgroup that works on one head
+template <bool PER_HEAD>
+constexpr int kScoreItems = PER_HEAD ? kHeadTiles : kHeadChunk;  // (head, tile) pairs whose keys a workgroup holds in registers
 template <int BITS, int G, bool PER_HEAD>
 constexpr int score_lds() {
-  return (PER_HEAD ? kHeadChunk * kD : kD) + (BITS == 16 ? 0 : kHeadChunk * (kTile / G) * 2 * kD);
+  return kD + (BITS == 16 ? 0 : kScoreItems<PER_HEAD> * (kTile / G) * 2 * kD);
 }
 // Thread = (token tid/8 of the workgroup's THREADS/8, channels 8 * (tid%8) ..).  Everything a workgroup needs is requested up
-// front (one memory round trip): the group parameters of all heads (staged in LDS, they are shared by the block's tokens) and the
-// thread's codes of all heads.
+// front (one memory round trip): the group parameters of all its items (staged in LDS, they are shared by a tile's tokens) and the
+// thread's codes of all items.  An item is a head's keys of the workgroup's tile, or a tile of the workgroup's head.
+// `lds`: score_lds(), and what pool_alone takes behind the first kD floats.
 template <int BITS, int G, bool PER_HEAD, int THREADS, bool SYNC>
-__device__ __forceinline__ void score_part(const FrontLayer& ly, const FrontCommon& a, int block, float* lds) {
+__device__ __forceinline__ void score_part(const FrontLayer& ly, const FrontCommon& a, int list, int block, float* lds) {
   constexpr bool kQuant = BITS != 16;
   constexpr int kRows = THREADS / 8;
   static_assert(!kQuant || kRows == kTile, "the block's parameters are those of one tile");
+  constexpr int kItems = kScoreItems<PER_HEAD>;
   constexpr int kGroups = kQuant ? kTile / G : 1;      // key groups inside a block of 64 positions
   constexpr int kRowDw = kD * BITS / 32;               // dwords per key row
   constexpr int kDwT = kQuant ? 1 : 4;                 // dwords per thread (2 bits: shared by two threads)
-  float* qtilde = lds;                                 // per head: one row per head of the chunk
-  float* prm = lds + (PER_HEAD ? kHeadChunk * kD : kD);  // [head][group][scale|zero][channel]
+  float* qtilde = lds;
+  float* prm = lds + kD;                               // [item][group][scale|zero][channel]
+  __shared__ int pooled;
 
   const int H = a.H, tid = threadIdx.x, r = tid >> 3, c8 = tid & 7;
-  const int first = (a.T_first / kRows + block) * kRows, pos = first + r;  // cache position
-  const bool valid = pos >= a.T_first && pos < a.T_first + a.P;
-  const uint32_t* src = reinterpret_cast<const uint32_t*>(ly.kc) + (size_t)pos * kRowDw + (kQuant ? c8 * kRowDw / 8 : 4 * c8);
+  const int first = (a.T_first / kRows + block * (PER_HEAD ? kItems : 1)) * kRows;  // cache position of the first row
+  auto position = [&](int item) { return first + r + (PER_HEAD ? item * kRows : 0); };
+  auto in_middle = [&](int pos) { return pos >= a.T_first && pos < a.T_first + a.P; };
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(ly.kc) + (size_t)(first + r) * kRowDw + (kQuant ? c8 * kRowDw / 8 : 4 * c8);
   const size_t head_stride = (size_t)a.head_rows * kRowDw;
 
   float acc[8];
@@ -147,50 +201,68 @@ __device__ __forceinline__ void score_part(const FrontLayer& ly, const FrontComm
     d += __shfl_xor(d, 4);
     return d;  // (in odd lanes)
   };
-  auto store_score = [&](int list, float s) {
+  auto store_score = [&](int pos, float s) {
     float* out = ly.scores + (size_t)list * a.stride + (pos - a.T_first);
-    if (valid && c8 == 1) {
+    if (in_middle(pos) && c8 == 1) {
       if (SYNC) store_agent(out, s);
       else *out = s;
     }
   };
-  for (int h0 = 0; h0 < H; h0 += kHeadChunk) {  // (one chunk for H <= kHeadChunk)
-    const int hn = min(kHeadChunk, H - h0);
-    uint32_t w[kHeadChunk][kDwT];
+  // qtilde of heads [h0, h1), at a point where nobody needs the parameters behind it any more (or yet)
+  auto pooled_query = [&](int h0, int h1) {
+    if (tid < kD) {
+      const bool done = !SYNC || __all(wait_for_pool(ly.sync + list, pools_of(a, PER_HEAD), a.polls));
+      float s = 0.f;
+      if (done) {
+#pragma unroll 8
+        for (int h = h0; h < h1; ++h) s += head_query<SYNC>(ly, h, tid);
+      }
+      qtilde[tid] = s;
+      if (SYNC && tid == 0) pooled = done;
+    }
+    __syncthreads();
+    if constexpr (SYNC) {
+      if (!pooled) pool_alone(ly, a, h0, h1, qtilde, lds + kD);
+    }
+  };
+  const int head_begin = PER_HEAD ? list : 0, head_end = PER_HEAD ? list + 1 : H;
+  for (int h0 = head_begin; h0 < head_end; h0 += kHeadChunk) {  // (one chunk for H <= kHeadChunk)
+    const int hn = PER_HEAD ? kItems : min(kHeadChunk, H - h0);  // items of this chunk
+    uint32_t w[kItems][kDwT];
 #pragma unroll
-    for (int h = 0; h < kHeadChunk; ++h) {
-      const uint32_t* p = src + (h0 + h) * head_stride;
+    for (int i = 0; i < kItems; ++i) {
+      const uint32_t* p = src + (PER_HEAD ? h0 * head_stride + (size_t)(i * kRows * kRowDw) : (h0 + i) * head_stride);
+      const bool valid = in_middle(position(i)) && i < hn;
       if constexpr (kQuant) {
-        w[h][0] = (valid && h < hn) ? *p : 0u;
+        w[i][0] = valid ? *p : 0u;
       } else {
-        const uint4 v = (valid && h < hn) ? *reinterpret_cast<const uint4*>(p) : make_uint4(0, 0, 0, 0);
-        w[h][0] = v.x; w[h][1] = v.y; w[h][2] = v.z; w[h][3] = v.w;
+        const uint4 v = valid ? *reinterpret_cast<const uint4*>(p) : make_uint4(0, 0, 0, 0);
+        w[i][0] = v.x; w[i][1] = v.y; w[i][2] = v.z; w[i][3] = v.w;
       }
     }
-    constexpr int kPrmIter = kQuant ? kHeadChunk * kGroups * 2 * kD / THREADS : 1;
+    constexpr int kPrmIter = kQuant ? kItems * kGroups * 2 * kD / THREADS : 1;
     float pr[kPrmIter];
     if constexpr (kQuant) {
 #pragma unroll
       for (int it = 0; it < kPrmIter; ++it) {
         const int i = tid + it * THREADS;
-        const int c = i % kD, sz = (i / kD) & 1, gi = (i / (2 * kD)) % kGroups, h = i / (2 * kD * kGroups);
-        pr[it] = h < hn ? (sz ? ly.kz : ly.ks)[((size_t)(h0 + h) * (a.head_rows / G) + first / G + gi) * kD + c] : 0.f;
+        const int c = i % kD, sz = (i / kD) & 1, gi = (i / (2 * kD)) % kGroups, item = i / (2 * kD * kGroups);
+        const int h = PER_HEAD ? h0 : h0 + item, row = first + (PER_HEAD ? item * kRows : 0);
+        const bool valid = item < hn && row < a.T_first + a.P;
+        pr[it] = valid ? (sz ? ly.kz : ly.ks)[((size_t)h * (a.head_rows / G) + row / G + gi) * kD + c] : 0.f;
       }
     }
-    if (h0 > 0) __syncthreads();  // the previous chunk's rows and parameters are no longer read
-    if constexpr (PER_HEAD) {
-      if (SYNC && h0 == 0) wait_for(ly.sync + kPoolDone, 2 * H);
-      for (int i = tid; i < hn * kD; i += THREADS) qtilde[i] = head_query<SYNC>(ly, h0 + i / kD, i % kD);
-    }
+    if (h0 > head_begin) __syncthreads();  // the previous chunk's parameters are no longer read
+    if constexpr (PER_HEAD) pooled_query(h0, h0 + 1);
     if constexpr (kQuant) {
 #pragma unroll
       for (int it = 0; it < kPrmIter; ++it) prm[tid + it * THREADS] = pr[it];
+      __syncthreads();
     }
-    if (kQuant || PER_HEAD) __syncthreads();
 #pragma unroll
-    for (int h = 0; h < kHeadChunk; ++h) {
+    for (int h = 0; h < kItems; ++h) {
       if (h < hn) {
-        float x[8];  // head h's key row (this thread's 8 channels), dequantized view
+        float x[8];  // the item's key row (this thread's 8 channels), dequantized view
         if constexpr (kQuant) {
           const float* ks = prm + ((h * kGroups + (r / G) % kGroups) * 2) * kD + c8 * 8;
           const float* kz = ks + kD;
@@ -224,7 +296,7 @@ __device__ __forceinline__ void score_part(const FrontLayer& ly, const FrontComm
           }
         }
         if constexpr (PER_HEAD) {
-          store_score(h0 + h, dot16(qtilde + h * kD + c8 * 8, x));
+          store_score(position(h), dot16(qtilde + c8 * 8, x));
         } else {
 #pragma unroll
           for (int e = 0; e < 8; ++e) acc[e] += x[e];
@@ -236,17 +308,9 @@ __device__ __forceinline__ void score_part(const FrontLayer& ly, const FrontComm
     const float fH = (float)H;
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] /= fH;
-    if (tid < kD) {
-      if (SYNC) wait_for(ly.sync + kPoolDone, 2 * H);
-      float s = 0.f;
-#pragma unroll 8
-      for (int h = 0; h < H; ++h) s += head_query<SYNC>(ly, h, tid);
-      qtilde[tid] = s;
-    }
-    __syncthreads();
-    store_score(0, dot16(qtilde + c8 * 8, acc));
+    pooled_query(0, H);
+    store_score(first + r, dot16(qtilde + c8 * 8, acc));
   }
-  if (SYNC) arrive(ly.sync + kScoreDone);
 }
 
 // ---- select --------------------------------------------------------------------------------------------
@@ -386,11 +450,12 @@ __device__ __forceinline__ void select_part(const SelectArgs& a, int list, uint3
 // ---- kernels -------------------------------------------------------------------------------------------
 constexpr int max_of(int a, int b) { return a > b ? a : b; }
 
-// One layer: 2 H pool, then score, then select workgroups.
+// One layer: 2 H pool workgroups, then a.blocks score workgroups per list.
 template <int BITS, int G, bool PER_HEAD, int KPT>
 __global__ __launch_bounds__(kThreads) void front_kernel(const FrontArgsT<1> args) {
-  constexpr int kLds = max_of(max_of(kPoolLds, score_lds<BITS, G, PER_HEAD>()), kSelLds);
+  constexpr int kLds = max_of(max_of(kD + kPoolLds + kPoolParts * kD, score_lds<BITS, G, PER_HEAD>()), kSelLds);
   __shared__ __attribute__((aligned(16))) float lds[kLds];
+  __shared__ int last;
 #if defined(__HIP_DEVICE_COMPILE__)
   {
     // every field of the arguments that is read further down would wait for its own line of them: all lines at once
@@ -405,18 +470,16 @@ __global__ __launch_bounds__(kThreads) void front_kernel(const FrontArgsT<1> arg
   const int b = blockIdx.x;
   if (b < 2 * a.H) {
     pool_part<true>(ly, a, b >> 1, b & 1, lds);
-  } else if (b < 2 * a.H + a.score_wgs) {
-    score_part<BITS, G, PER_HEAD, kThreads, true>(ly, a, b - 2 * a.H, lds);
-  } else {
-    wait_for(ly.sync + kScoreDone, a.score_wgs);
-    __syncthreads();
-    const uint32_t lists = PER_HEAD ? a.H : 1;
-    // the last one of a layer to have seen that leaves the counters as it found them
-    if (threadIdx.x == 0 && __hip_atomic_fetch_add(ly.sync + kSelectSeen, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == lists - 1) {
-      for (int i = 0; i < 3; ++i) store_agent(ly.sync + i, 0u);
-    }
+    return;
+  }
+  const int list = PER_HEAD ? (b - 2 * a.H) / a.blocks : 0;
+  score_part<BITS, G, PER_HEAD, kThreads, true>(ly, a, list, b - 2 * a.H - list * a.blocks, lds);
+  const uint64_t before = arrive(ly.sync + list, kScoreArrived, all_of(a, PER_HEAD));
+  if (threadIdx.x == 0) last = (int)(before >> 32) == a.blocks - 1;
+  __syncthreads();
+  if (last) {
     const SelectArgs s{ly.scores, ly.keep, a.stride, a.stride, a.P, a.k, a.T_first, a.T_cur};
-    select_part<KPT, true>(s, b - 2 * a.H - a.score_wgs, reinterpret_cast<uint32_t*>(lds));
+    select_part<KPT, true>(s, list, reinterpret_cast<uint32_t*>(lds));
   }
 }
 
@@ -429,7 +492,8 @@ __global__ __launch_bounds__(kThreads) void pool_kernel(const FrontArgsT<LAYERS>
 template <int BITS, int G, bool PER_HEAD, int THREADS, int LAYERS>
 __global__ __launch_bounds__(THREADS) void score_kernel(const FrontArgsT<LAYERS> args) {
   __shared__ __attribute__((aligned(16))) float lds[score_lds<BITS, G, PER_HEAD>()];
-  score_part<BITS, G, PER_HEAD, THREADS, false>(args.layer[blockIdx.y], args.c, blockIdx.x, lds);
+  const int list = PER_HEAD ? blockIdx.x / args.c.blocks : 0;
+  score_part<BITS, G, PER_HEAD, THREADS, false>(args.layer[blockIdx.y], args.c, list, blockIdx.x - list * args.c.blocks, lds);
 }
 template <int KPT>
 __global__ __launch_bounds__(kThreads) void select_kernel(const SelectArgs a) {
@@ -437,15 +501,16 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const SelectArgs a) {
   select_part<KPT, false>(a, blockIdx.x, lds);
 }
 
+// blocks of `rows` positions that the middle touches
 static int score_blocks(const FrontCommon& c, int rows) { return (c.T_first + c.P - 1) / rows - c.T_first / rows + 1; }
 
 constexpr int kPlainThreads = 128;  // 16 positions: a list of 2722 is then spread over 170 workgroups (pool and score of
 // 16 heads: 28.6 us with 43, 10.0 with 170)
 hipError_t launch_score(const FrontArgs& a, hipStream_t stream) {
-  const FrontArgsT<1> one{a.c, {a.layer[0]}};
+  FrontArgsT<1> one{a.c, {a.layer[0]}};
+  one.c.blocks = score_blocks(a.c, kPlainThreads / 8);
   hipLaunchKernelGGL(pool_kernel<1>, dim3(2 * a.c.H), dim3(kThreads), 0, stream, one);
-  hipLaunchKernelGGL((score_kernel<16, 64, false, kPlainThreads, 1>), dim3(score_blocks(a.c, kPlainThreads / 8)), dim3(kPlainThreads), 0,
-                     stream, one);
+  hipLaunchKernelGGL((score_kernel<16, 64, false, kPlainThreads, 1>), dim3(one.c.blocks), dim3(kPlainThreads), 0, stream, one);
   return hipGetLastError();
 }
 
@@ -461,10 +526,10 @@ hipError_t launch_select(const SelectArgs& a, int n_lists, hipStream_t stream) {
 template <int BITS, int G, bool PER_HEAD>
 static hipError_t launch_front_t(FrontArgs& a, hipStream_t stream) {
   FrontCommon& c = a.c;
-  c.score_wgs = score_blocks(c, kTile);
-  const int lists = PER_HEAD ? c.H : 1;
+  const int tiles = score_blocks(c, kTile), lists = PER_HEAD ? c.H : 1;
+  c.blocks = PER_HEAD ? (tiles + kHeadTiles - 1) / kHeadTiles : tiles;
   if (c.n_layers == 1) {
-    const dim3 grid(2 * c.H + c.score_wgs + lists);
+    const dim3 grid(2 * c.H + c.blocks * lists);
     const FrontArgsT<1> one{c, {a.layer[0]}};
     if (few_scores(c.P)) hipLaunchKernelGGL((front_kernel<BITS, G, PER_HEAD, 8>), grid, dim3(kThreads), 0, stream, one);
     else hipLaunchKernelGGL((front_kernel<BITS, G, PER_HEAD, 16>), grid, dim3(kThreads), 0, stream, one);
@@ -473,7 +538,7 @@ static hipError_t launch_front_t(FrontArgs& a, hipStream_t stream) {
   // Many layers: their parts fill the chip by themselves, and workgroups that wait only hold places that others could use
   // (24 layers of the sizes above: 104 us as one launch, 46 as three).
   hipLaunchKernelGGL(pool_kernel<kMaxBatch>, dim3(2 * c.H, c.n_layers), dim3(kThreads), 0, stream, a);
-  hipLaunchKernelGGL((score_kernel<BITS, G, PER_HEAD, kThreads, kMaxBatch>), dim3(c.score_wgs, c.n_layers), dim3(kThreads), 0, stream, a);
+  hipLaunchKernelGGL((score_kernel<BITS, G, PER_HEAD, kThreads, kMaxBatch>), dim3(c.blocks * lists, c.n_layers), dim3(kThreads), 0, stream, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // (the lists of consecutive layers follow each other)

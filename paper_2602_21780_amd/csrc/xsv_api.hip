@@ -72,6 +72,7 @@ struct xsv_ctx {
   int frame_tile_cost = 95;  // cost of a key tile of the frame's own rows in percent of a cache tile's (attention range cut)
   int short_pct = -1; // xsv_step: length of one extra, short key range per unit, in percent of a long one (0 = none, -1 = default)
   int side_cus = -1;  // compute units xsv_step leaves to the prune chain while attention runs (-1: by launch size)
+  int pool_polls = 1 << 13;  // a look takes half a microsecond or more: several times the longest launch it could wait behind
   size_t part_rows = 0;  // rows the partial-output workspace holds
   int n_cu = 256;
   bool broken = false;
@@ -362,7 +363,7 @@ int do_score_prune(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q) 
       const int l = layer0 + i;
       const LayerCache lc = layer_cache(ctx->pool, b.src_buf(i), l);
       const size_t list = list_index(sets, l, 0) * ws.scores_stride;
-      f.layer[i] = FrontLayer{b.q[i], lc.kc, lc.ks, lc.kz, ws.qpart + (size_t)l * ctx->pool.H * kPoolParts * kD, ws.scores + list, ws.keep + list, ws.sync + 4 * l};
+      f.layer[i] = FrontLayer{b.q[i], lc.kc, lc.ks, lc.kz, ws.qpart + (size_t)l * ctx->pool.H * kPoolParts * kD, ws.scores + list, ws.keep + list, ws.sync + (size_t)l * sets};
     }
     f.c = FrontCommon{};
     f.c.q_sh = b.q_sh; f.c.q_st = b.q_st;
@@ -372,6 +373,7 @@ int do_score_prune(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q) 
     f.c.head_rows = ctx->pool.Tcap;
     f.c.stride = ws.scores_stride;
     f.c.per_head = ctx->cfg.score_mode == 1;
+    f.c.polls = ctx->pool_polls;
     if (launch_front(f, ctx->pool.bits, ctx->pool.G, ctx->work) != hipSuccess) return hip_fail(ctx);
   }
   for (int i = 0; i < n_layers; ++i) {
@@ -542,7 +544,7 @@ int xsv_create(const xsv_config* cfg, void* hip_stream, xsv_ctx** out) {
   A(&w.scores, (size_t)c.n_layers * w.sets * w.scores_stride, true);
   A(&w.keep, (size_t)c.n_layers * w.sets * w.scores_stride, true);
   A(&w.qpart, (size_t)c.n_layers * c.n_heads * kPoolParts * kD, true);
-  A(&w.sync, (size_t)c.n_layers * 4, true);
+  A(&w.sync, (size_t)c.n_layers * w.sets, true);
   // partial attention outputs: up to 16 key ranges for one layer, or 2 per layer when batched
   // (partials are stored in blocks of 32 query rows per head)
   const size_t part_rows = (size_t)std::max(16, 2 * std::min(c.n_layers, kMaxBatch)) * c.n_heads * round_up((int)n, 32);
@@ -683,6 +685,12 @@ int xsv_set_frame_tile_cost(xsv_ctx* ctx, int percent) {
 int xsv_set_side_cus(xsv_ctx* ctx, int compute_units) {
   if (!ctx || compute_units < -1 || compute_units > ctx->n_cu / 2) return XSV_ERR_ARG;
   ctx->side_cus = compute_units;
+  return XSV_OK;
+}
+
+int xsv_set_pool_polls(xsv_ctx* ctx, int polls) {
+  if (!ctx || polls < 0 || polls > (1 << 20)) return XSV_ERR_ARG;
+  ctx->pool_polls = polls;
   return XSV_OK;
 }
 

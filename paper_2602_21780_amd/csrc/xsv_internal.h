@@ -98,7 +98,7 @@ struct Workspace {
   float* scores;      // [L][sets][Tcap + n]  importance of the middle tokens
   int32_t* keep;      // [L][sets][Tcap + n]  keep list
   float* qpart;       // [L][H][kPoolParts][64] partial weighted query sums
-  uint32_t* sync;     // [L][4] counters of front_kernel, zero between launches
+  uint64_t* sync;     // [L][sets] counters of front_kernel, zero between launches
   uint16_t* attn_o;   // [pieces][batch layers][H][ceil(n/32)] blocks of 32 rows x 64 fp16 mantissas of the unnormalized
                       // partial outputs, each block stored [16-byte piece 0..3][lane half][row] (4 KB)
   float* attn_ml;     // [pieces][batch layers][H][n][4]  softmax reference (log2 domain), row sum, row scale, -
@@ -166,7 +166,7 @@ struct FrontLayer {
   float* qpart;        // [H][kPoolParts][64]
   float* scores;       // first list of the layer
   int32_t* keep;
-  uint32_t* sync;      // see Workspace
+  uint64_t* sync;      // see Workspace
 };
 struct FrontCommon {
   int64_t q_sh, q_st;  // strides in elements
@@ -175,7 +175,8 @@ struct FrontCommon {
   int head_rows;       // key rows between two heads
   int stride;          // between two lists
   int per_head;        // 1: no averages over heads, head h has list h of the layer
-  int score_wgs;       // (filled by launch_front)
+  int polls;           // how often front_kernel looks for the pool before it pools by itself (a matter of time only)
+  int blocks;          // score workgroups per list (filled by the launchers)
 };
 template <int LAYERS>
 struct FrontArgsT {

@@ -202,6 +202,25 @@ def test_long_lists_are_selected_exactly_and_unneeded_ones_are_reported(mode):
     ctx.destroy()
 
 
+@pytest.mark.parametrize("mode,H,n,budget,bits,G", [(0, 17, 70, 1100, 4, 32), (0, 3, 200, 900, 2, 64), (1, 17, 70, 1100, 4, 64),
+                                                    (1, 2, 257, 1600, 2, 32), (0, 2, 100, 420, 16, 64), (1, 2, 100, 420, 16, 64)])
+def test_score_workgroups_that_pool_by_themselves(mode, H, n, budget, bits, G):
+    """Without a look at the pooled query (the bounded wait set to nothing) every score workgroup works it out: scores, lists and
+    outputs bit for bit those of a stream that waits, over steps that reuse the layer's counters.  More heads than a workgroup
+    holds at a time, middles around its tiles."""
+    waits, alone = (xsv.Context(1, H, 64, n, 5, budget, bits, G, score_mode=mode) for _ in range(2))
+    alone.set_pool_polls(0)
+    g = torch.Generator().manual_seed(n)
+    for f in range(budget // n + 4):
+        q, k, v = (torch.randn((H, n, 64), generator=g).to(torch.bfloat16).to(DEV) for _ in range(3))
+        assert torch.equal(waits.step(0, q, k, v), alone.step(0, q, k, v))
+        for x, y in zip(waits.last_selection(0), alone.last_selection(0)):
+            assert np.array_equal(x, y)
+    assert waits.last_selection(0)[0].size > 0
+    waits.destroy()
+    alone.destroy()
+
+
 def test_budget_below_two_frames_keeps_first_and_current():
     spec = CONFIGS[0].with_(name="k0", budget=100)
     run_stream(spec, 4)
