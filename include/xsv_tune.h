@@ -15,7 +15,7 @@ extern "C" {
 #endif
 
 /* Tuning: number of equal key ranges every (head, block of query rows) is cut into by the attention
- * kernel (partial results are merged by a second kernel), 1..16.  0 (default) = one workgroup per
+ * kernel (partial results are merged by a second kernel, or by the workgroup that ends last), 1..16.  0 (default) = one workgroup per
  * slot of the chip, the key tiles of all (head, query block) pairs dealt out evenly among them. */
 int xsv_set_attend_splits(xsv_ctx* ctx, int per_layer_calls, int batched_calls);
 /* Tuning: compute units the attention launch of xsv_step / xsv_step_all_layers leaves free for the
@@ -40,7 +40,7 @@ int xsv_set_pool_polls(xsv_ctx* ctx, int polls);
  * xsv_attend_times waits for the stream, returns the number of launches recorded since the last call (or
  * since enabling), the average span of each of the two kernels in milliseconds and (event_ms, may be NULL)
  * the average span of the last two events, which have nothing between them: what an event pair itself adds
- * to a span.  It then starts a new series.  Enabling or disabling discards the series.  The events cost a
+ * to a span (merge_ms is no more than that where the attention kernel merges by itself).  It then starts a new series.  Enabling or disabling discards the series.  The events cost a
  * few microseconds per launch; leave this off in production. */
 int xsv_set_attend_timing(xsv_ctx* ctx, int enabled);
 int xsv_attend_times(xsv_ctx* ctx, int32_t* launches, float* attend_ms, float* merge_ms, float* event_ms);

@@ -29,7 +29,7 @@
 //   number of workgroups gets the same amount of work; a piece may end one unit and begin the
 //   next, and the workgroup handles them one after the other.  In both forms a unit covered by one
 //   workgroup is normalized and written directly; otherwise each workgroup writes an unnormalized
-//   partial that combine_kernel merges.
+//   partial, and the workgroup that finishes the unit merges them, or combine_kernel does (AttendArgs::merge_inside).
 //   Softmax.  No row maximum and no rescaling on the common path: the reference of the exponent is the row maximum
 //   of a range's first 32 tokens plus 8 powers of two, and probabilities may grow above 1 - they are as exact there, in bf16 as
 //   in fp32.  Only when a tile's row sum passes 2^24 - looked at once per tile - are the references moved, which rescales sums and
@@ -356,6 +356,21 @@ __device__ __forceinline__ void store_frame_tile(const FrameRegs<NH>& st, uint16
   }
 }
 
+// Partials of cut units pass between workgroups on different dies, whose caches do not see each other: agent-scope accesses go
+// past them.  (With plain stores a workgroup would have to write its die's whole L2 back before it could say that it is done.)
+constexpr int kAgentScope = 16;  // the sc1 bit of a buffer instruction
+// A (piece, layer, head)'s partial rows, see Workspace
+struct PartialRows {
+  __amdgpu_buffer_rsrc_t o, ml;
+};
+__device__ __forceinline__ PartialRows partial_rows(const AttendArgs& a, size_t piece_head) {
+  const uint32_t blocks = ((uint32_t)a.n + 31u) / 32u;
+  return PartialRows{__builtin_amdgcn_make_buffer_rsrc(a.attn_o + piece_head * blocks * 2048, 0, (int)(blocks * 4096u), 0x00020000),
+                     __builtin_amdgcn_make_buffer_rsrc(a.attn_ml + piece_head * (uint32_t)a.n * 4, 0, (int)((uint32_t)a.n * 16u), 0x00020000)};
+}
+// This wave's partials have reached memory (its count of outstanding accesses is zero).
+__device__ __forceinline__ void partials_written() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // "No vector-memory load is outstanding here" as an instruction (s_waitcnt vmcnt(0)).  A tile loop fetches the next
 // tile under a condition and consumes it under the same condition further down; the compiler does not connect the
 // two, assumes that fetched registers may still be in flight on the path that skips the consumer, and would then
@@ -406,7 +421,8 @@ struct Partition {
 // ONE_LAYER: the launch works on a single layer (the per-layer calls).  The layer index is then a constant, so every
 // pointer of the launch can be fetched from the kernel arguments right at the start, in one round trip, instead of
 // after the workgroup has worked out which layer its piece belongs to.
-template <int BITS, int G, int NW, int QB, bool ONE_LAYER>
+// INSIDE: AttendArgs::merge_inside.  (A kernel of its own: as a branch it cost the other form 1.4 % of a frame-wise attention.)
+template <int BITS, int G, int NW, int QB, bool ONE_LAYER, bool INSIDE>
 __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   constexpr int NT = NW * 64, NH = NT / 2;
   constexpr int kRowsWG = 32 * QB * NW;  // query rows per workgroup
@@ -429,6 +445,7 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   constexpr int kPrmBlock = BITS == 16 ? 1 : 2 * Stage<BITS, G, NH>::kPrm;  // one tile's scales and zero points of one role
   __shared__ __attribute__((aligned(16))) float lds_prm[2][2][kPrmBlock];    // [role][buffer]
   __shared__ int careful_pass[2];  // some wave asks for it (by the parity of the unit's number in this workgroup)
+  __shared__ int finishes;         // this workgroup's piece was the last of its unit to be done
 
   const int H = a.H, n = a.n, Tc = a.Tc;
   const int nqb = (n + kRowsWG - 1) / kRowsWG;
@@ -981,13 +998,74 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
           hw[r >> 1] = pack_f16(__builtin_amdgcn_ldexpf(o0[cb][r], -e), __builtin_amdgcn_ldexpf(o0[cb][r + 1], -e));
           hw[8 + (r >> 1)] = pack_f16(__builtin_amdgcn_ldexpf(o1[cb][r], -e), __builtin_amdgcn_ldexpf(o1[cb][r + 1], -e));
         }
-        uint4* op = reinterpret_cast<uint4*>(a.attn_o) + blk * 256 + hh * 32 + j;
+        if constexpr (INSIDE) {
+          const PartialRows to = partial_rows(a, ((size_t)piece * a.n_layers + lb) * H + h);
+          const uint32_t at = (uint32_t)(q_row >> 5) * 4096u + (uint32_t)(hh * 32 + j) * 16u;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) op[i * 64] = make_uint4(hw[4 * i], hw[4 * i + 1], hw[4 * i + 2], hw[4 * i + 3]);
-        if (hh == 0)
-          *reinterpret_cast<float4*>(a.attn_ml + row * 4) = make_float4(-mc[cb], lsum, __builtin_amdgcn_ldexpf(1.0f, e), 0.f);
+          for (int i = 0; i < 4; ++i)
+            __builtin_amdgcn_raw_buffer_store_b128(u32x4{hw[4 * i], hw[4 * i + 1], hw[4 * i + 2], hw[4 * i + 3]}, to.o, at + i * 1024u, 0, kAgentScope);
+          if (hh == 0) {
+            const u32x4 ml = {__float_as_uint(-mc[cb]), __float_as_uint(lsum), __float_as_uint(__builtin_amdgcn_ldexpf(1.0f, e)), 0u};
+            __builtin_amdgcn_raw_buffer_store_b128(ml, to.ml, (uint32_t)q_row * 16u, 0, kAgentScope);
+          }
+        } else {
+          uint4* op = reinterpret_cast<uint4*>(a.attn_o) + blk * 256 + hh * 32 + j;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) op[i * 64] = make_uint4(hw[4 * i], hw[4 * i + 1], hw[4 * i + 2], hw[4 * i + 3]);
+          if (hh == 0)
+            *reinterpret_cast<float4*>(a.attn_ml + row * 4) = make_float4(-mc[cb], lsum, __builtin_amdgcn_ldexpf(1.0f, e), 0.f);
+        }
       }
     }
+  };
+
+  // Merge of a unit's S <= kMergeInside pieces in the order of the pieces, whoever does it; the arithmetic is combine_kernel's.
+  // A lane takes the values it would have held of an uncut row, all pieces of a block of rows at once.  (Compact code, one block
+  // after the other: it is cold when a workgroup comes to it.)
+  auto merge = [&](int S) XSV_INLINE {
+    __builtin_amdgcn_s_setprio(3);
+#pragma unroll 1
+    for (int row0 = q_row0; row0 < min(n, q_row0 + 32 * QB); row0 += 32) {
+      const uint32_t at = (uint32_t)(row0 >> 5) * 4096u + (uint32_t)(hh * 32 + j) * 16u, at_ml = (uint32_t)(row0 + j) * 16u;
+      u32x4 ml[kMergeInside], o[kMergeInside][4];
+#pragma unroll
+      for (int s = 0; s < kMergeInside; ++s)
+        if (s < S) {  // (rows past the frame read as zeros: never stored)
+          const PartialRows from = partial_rows(a, ((size_t)s * a.n_layers + lb) * H + h);
+          ml[s] = __builtin_amdgcn_raw_buffer_load_b128(from.ml, at_ml, 0, kAgentScope);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) o[s][q] = __builtin_amdgcn_raw_buffer_load_b128(from.o, at + q * 1024u, 0, kAgentScope);
+        }
+      float M = kNegBig, L = 0.f, acc[32];
+#pragma unroll
+      for (int r = 0; r < 32; ++r) acc[r] = 0.f;
+#pragma unroll
+      for (int s = 0; s < kMergeInside; ++s)
+        if (s < S) M = fmaxf(M, __uint_as_float(ml[s][0]));
+#pragma unroll
+      for (int s = 0; s < kMergeInside; ++s) {
+        if (s < S) {
+          const float wgt = __builtin_amdgcn_exp2f(__uint_as_float(ml[s][0]) - M);
+          L += wgt * __uint_as_float(ml[s][1]);
+          const float ws = wgt * __uint_as_float(ml[s][2]);
+#pragma unroll
+          for (int r = 0; r < 32; r += 2) {
+            const f16x2 v = __builtin_bit_cast(f16x2, (uint32_t)o[s][r >> 3][(r >> 1) & 3]);
+            acc[r] += ws * (float)v[0];
+            acc[r + 1] += ws * (float)v[1];
+          }
+        }
+      }
+      const int q_row = row0 + j;
+      const float inv = 1.0f / L;
+      if (q_row < n) {
+        uint16_t* op = ly.out + ((size_t)h * n + q_row) * kD + 4 * hh;
+#pragma unroll
+        for (int r = 0; r < 32; r += 4)  // (channels as in write_rows)
+          *reinterpret_cast<uint2*>(op + 2 * r) = make_uint2(pack_bf16(acc[r] * inv, acc[r + 1] * inv), pack_bf16(acc[r + 2] * inv, acc[r + 3] * inv));
+      }
+    }
+    __builtin_amdgcn_s_setprio(0);
   };
 
   if (tid == 0) careful_pass[parity] = 0;  // (barriers of the walk lie between this and anybody's setting it)
@@ -1022,6 +1100,8 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   }
   if (n_cb > 0 && lost && lane == 0) careful_pass[parity] = 1;
   write_rows();
+  const bool finish = INSIDE && !whole;
+  if (finish) partials_written();
   __syncthreads();
   if (__builtin_expect(__builtin_amdgcn_readfirstlane(careful_pass[parity]) != 0, 0)) {
     clear();
@@ -1041,6 +1121,21 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
       __syncthreads();
     }
     write_rows();
+    if (finish) {
+      partials_written();
+      __syncthreads();
+    }
+  }
+  if (finish) {
+    const int w0 = a.equal_ranges > 0 ? 0 : part.first_wg(unit);
+    const int pieces = a.equal_ranges > 0 ? a.equal_ranges : part.last_wg(unit) - w0 + 1;
+    if (tid == 0) {
+      uint32_t* const done = a.unit_done + unit;
+      finishes = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)pieces - 1u;
+      if (finishes) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // as the next launch wants it
+    }
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(finishes)) merge(pieces);
   }
   parity ^= 1;
   }  // units of this workgroup's piece
@@ -1048,8 +1143,8 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
 }
 
 // Merge of the pieces of every unit that was cut:  out = sum_p 2^(m_p - M) O_p / sum_p 2^(m_p - M) l_p.
-// (A separate launch on purpose: a device-wide release/acquire inside the attention kernel costs an
-// L2 write-back per workgroup on this multi-die part, far more than a second small kernel.)
+// (A launch of its own where nothing runs beside attention: it spreads over the whole chip, and its partials need no agent-scope
+// stores; see AttendArgs::merge_inside.)
 // Grid: y = chunk of 32 query rows of a unit; x = the unit when all units are cut alike, else a boundary
 // between workgroups w-1 | w of the attention grid (w = blockIdx.x + 1), standing for the unit it falls
 // into: a unit with several boundaries is handled at its first one, and a boundary that coincides with
@@ -1124,12 +1219,21 @@ __global__ __launch_bounds__(256) void combine_kernel(const AttendArgs a) {
 
 template <int BITS, int G, int NW, int QB>
 static hipError_t launch_attend_t(const AttendArgs& a, hipStream_t stream, hipEvent_t between) {
-  if (a.n_layers == 1) hipLaunchKernelGGL((attend_kernel<BITS, G, NW, QB, true>), dim3(a.n_wgs), dim3(NW * 64), 0, stream, a);
-  else hipLaunchKernelGGL((attend_kernel<BITS, G, NW, QB, false>), dim3(a.n_wgs), dim3(NW * 64), 0, stream, a);
+  auto launch = [&](auto one_layer, auto inside) {
+    hipLaunchKernelGGL((attend_kernel<BITS, G, NW, QB, decltype(one_layer)::value, decltype(inside)::value>), dim3(a.n_wgs), dim3(NW * 64), 0, stream, a);
+  };
+  using std::true_type;
+  using std::false_type;
+  bool inside = false;
+  if constexpr (NW == 8) {  // (the shapes that the library chooses by itself)
+    inside = a.merge_inside;
+    if (inside) a.n_layers == 1 ? launch(true_type{}, true_type{}) : launch(false_type{}, true_type{});
+  }
+  if (!inside) a.n_layers == 1 ? launch(true_type{}, false_type{}) : launch(false_type{}, false_type{});
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (between && (e = hipEventRecord(between, stream)) != hipSuccess) return e;
-  if (a.cut) {
+  if (a.cut && !inside) {
     const int n_units = a.n_layers * a.H * ((a.n + a.rows_wg - 1) / a.rows_wg);
     hipLaunchKernelGGL(combine_kernel, dim3(a.equal_ranges > 0 ? n_units : a.n_wgs - 1, (a.rows_wg + 31) / 32), dim3(256), 0,
                        stream, a);

@@ -269,9 +269,10 @@ void range_starts(int n_ct, int n_ft, int R, int last_pct, int frame_cost, int32
 }
 
 // The three stages for layers [layer0, layer0 + n_layers), which must be in step with each other.
+// beside_chain: pooling, score, select and re-quantization of the same layers are on the other stream.
 // frame_only: the frame's own tokens are the only keys (no cache tiles, no change of state).
 int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const xsv_tensor* k, const xsv_tensor* v,
-              void* const* out, int splits_req, int spare_cus, bool frame_only = false) {
+              void* const* out, int splits_req, int spare_cus, bool beside_chain = false, bool frame_only = false) {
   AttendArgs a{};
   {
     Batch b;
@@ -290,7 +291,7 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
     a.kparam_head = (uint32_t)((size_t)(p.Tcap / p.G) * kD);
     a.vparam_head = (uint32_t)((size_t)p.Tcap * (kD / p.G));
     a.q_sh = b.q_sh; a.q_st = b.q_st; a.k_sh = b.k_sh; a.k_st = b.k_st; a.v_sh = b.v_sh; a.v_st = b.v_st;
-    a.attn_o = ctx->ws.attn_o; a.attn_ml = ctx->ws.attn_ml;
+    a.attn_o = ctx->ws.attn_o; a.attn_ml = ctx->ws.attn_ml; a.unit_done = ctx->ws.unit_done;
   }
   a.Tc = frame_only ? 0 : ctx->layers[layer0].T;
   a.n = ctx->cfg.tokens_per_frame;
@@ -317,6 +318,7 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
   a.n_wgs = plan.n_wgs;
   a.rows_wg = plan.rows_wg;
   a.cut = plan.max_pieces > 1;
+  a.merge_inside = a.cut && beside_chain && plan.max_pieces <= kMergeInside;
   {
     const int n_units = ((a.n + plan.rows_wg - 1) / plan.rows_wg) * ctx->cfg.n_heads * n_layers;
     const int ranges = plan.n_wgs % n_units == 0 ? plan.n_wgs / n_units : 0;
@@ -551,6 +553,7 @@ int xsv_create(const xsv_config* cfg, void* hip_stream, xsv_ctx** out) {
   ctx->part_rows = part_rows;
   A(&w.attn_o, part_rows * kD, false);
   A(&w.attn_ml, part_rows * 4, false);
+  A(&w.unit_done, (size_t)std::min(c.n_layers, kMaxBatch) * c.n_heads * ((n + 127) / 128), true);  // (128 rows: the smallest workgroup)
   if (rc == XSV_OK && hipStreamSynchronize(ctx->stream) != hipSuccess) rc = XSV_ERR_HIP;
   if (rc != XSV_OK) {
     free_all(ctx);
@@ -751,7 +754,7 @@ int xsv_frame_attend(xsv_ctx* ctx, xsv_tensor q, xsv_tensor k, xsv_tensor v, voi
   if (ctx->broken) return XSV_ERR_HIP;
   if (!tensor_ok(q) || !tensor_ok(k) || !tensor_ok(v) || !out) return XSV_ERR_ARG;
   void* outs[1] = {out};
-  return do_attend(ctx, 0, 1, &q, &k, &v, outs, ctx->splits_single, 0, true);
+  return do_attend(ctx, 0, 1, &q, &k, &v, outs, ctx->splits_single, 0, false, true);
 }
 
 int xsv_score_prune(xsv_ctx* ctx, int layer, xsv_tensor q) {
@@ -821,7 +824,7 @@ static int step_layers(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor*
         const long long wgs = (long long)per_cu * (ctx->n_cu - ctx->n_cu / 4);
         spare = units * tiles > 24 * wgs ? ctx->n_cu / 8 : ctx->n_cu / 4;
       }
-      rc = do_attend(ctx, layer0, n_layers, q, k, v, out, splits, spare);
+      rc = do_attend(ctx, layer0, n_layers, q, k, v, out, splits, spare, plan_for(ctx->cfg, ctx->layers[layer0]).score);
     }
     ctx->work = ctx->side;
     if (rc == XSV_OK) rc = do_quantize(ctx, layer0, n_layers, k, v);

@@ -102,6 +102,7 @@ struct Workspace {
   uint16_t* attn_o;   // [pieces][batch layers][H][ceil(n/32)] blocks of 32 rows x 64 fp16 mantissas of the unnormalized
                       // partial outputs, each block stored [16-byte piece 0..3][lane half][row] (4 KB)
   float* attn_ml;     // [pieces][batch layers][H][n][4]  softmax reference (log2 domain), row sum, row scale, -
+  uint32_t* unit_done;  // [units of an attention launch] pieces of a cut unit that are done, zero between launches
   int scores_stride;  // Tcap + n
   int sets;           // lists per layer (CachePool::sets)
 };
@@ -109,6 +110,7 @@ struct Workspace {
 // ---- launchers (defined in the .hip files; every one only enqueues on `stream`) -----------------
 
 constexpr int kMaxPieces = 16;  // workgroups that may share one unit
+constexpr int kMergeInside = 5;  // see AttendArgs::merge_inside
 // One layer of an attention launch: device pointers at head 0 of the buffer that holds the layer's cache, and of the
 // frame's tensors.  (Resolved on the host: a workgroup's first tile waits behind whatever address arithmetic the
 // kernel has to do, and the argument block stays small.)
@@ -131,11 +133,19 @@ struct AttendArgs {
   int64_t q_sh, q_st, k_sh, k_st, v_sh, v_st;    // strides of the frame tensors in elements
   uint16_t* attn_o;  // partial outputs of cut units, see Workspace
   float* attn_ml;
+  uint32_t* unit_done;  // see Workspace
   int Tc, n;
   int variant;   // waves x query rows per wave of a workgroup: 0: 4 x 64, 1: 4 x 32, 2: 8 x 32, 3: 8 x 64
   int n_wgs;     // workgroups the (unit, tile) line is cut into (from plan_attend)
   int rows_wg;   // query rows per workgroup of this variant
   int cut;       // some unit is shared by several workgroups: partials are written and merged
+  // The last workgroup of a cut unit merges it, instead of a second launch.  For steps with the chain beside attention, where a
+  // second launch waits for places among the chain's workgroups (us per pass, second launch and merge inside: 24 layers with
+  // deferred joins 1325 and 1312, joined 1529 and 1525, 24 layers of a 2-bit cache of 8192 tokens 2460 and 2405), and up to
+  // kMergeInside pieces: the last workgroup reads all of them (six 2-bit layers of 777 tokens and 9 pieces 287 and 315).  With
+  // nothing beside it the second launch is better, since it takes the whole chip: four ragged layers stage by stage 171 and 176,
+  // frame-wise attention 23.7 and 24.2; a chain without scores is over by then: one layer of that kind 50.5 and 51.1.
+  int merge_inside;
   int equal_ranges;  // > 0: every unit is cut into exactly this many key ranges, at the same tiles:
   // range p of a unit is its tiles [range_begin[p], range_begin[p + 1]); chosen on the host so that the ranges
   // COST the same (a tile of the frame's own bf16 rows takes longer to stage than a tile of packed codes), or

@@ -221,6 +221,33 @@ def test_score_workgroups_that_pool_by_themselves(mode, H, n, budget, bits, G):
     alone.destroy()
 
 
+@pytest.mark.parametrize("variant", [0, 1, 2, 3])
+@pytest.mark.parametrize("splits,n,budget", [(2, 600, 1900), (5, 600, 1900), (6, 257, 2000), (16, 300, 4300), (16, 130, 700)])
+def test_units_merged_by_their_last_workgroup_equal_the_second_launch(variant, splits, n, budget):
+    """With the chain beside attention the last workgroup of a cut unit merges it, without it a launch of its own does: the same
+    bits, over steps that reuse the counters, for fewer and more pieces than a lane holds at a time, for rows that are NaN and
+    go through the tiles twice, and (16 pieces of a short unit) for workgroups that end one unit and begin the next."""
+    outs, wgs = [], []
+    for overlap in (0, 1, 2):
+        ctx = xsv.Context(1, 3, 64, n, 5, budget, 4, 64)
+        ctx.set_attend_variant(variant)
+        ctx.set_attend_splits(splits, splits)
+        ctx.set_overlap(overlap)
+        g = torch.Generator().manual_seed(n)
+        frames = []
+        for f in range(-(-budget // n) + 3):
+            q, k, v = (torch.randn((3, n, 64), generator=g).to(torch.bfloat16).to(DEV) for _ in range(3))
+            q[1, n - 1] = float("nan") if f % 2 else 1.0
+            frames.append(ctx.step(0, q, k, v))
+        ctx.join()
+        torch.cuda.synchronize()
+        outs.append(torch.stack(frames).view(torch.int16))
+        wgs.append(ctx.last_attend_workgroups())
+        ctx.destroy()
+    assert wgs[0] == wgs[1] == wgs[2] > 3 * -(-n // (256, 128, 256, 512)[variant])   # more workgroups than units
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+
+
 def test_budget_below_two_frames_keeps_first_and_current():
     spec = CONFIGS[0].with_(name="k0", budget=100)
     run_stream(spec, 4)
