@@ -193,8 +193,8 @@ int xsv_quantize_k(void* hip_stream, const void* k_bf16, int H, int T, int d, in
                    float* scale, float* zero);
 int xsv_quantize_v(void* hip_stream, const void* v_bf16, int H, int T, int d, int bits, int G, void* codes_u8,
                    float* scale, float* zero);
-/* Sec. 3.2 importance of P keys k_mid (bf16 [H][P][64] contiguous) for the frame's queries q
- * (n rows, first n_s special, pooling size g).  scores: float [P]. */
+/* Sec. 3.2 importance of P keys k_mid (bf16 [H][P][64] contiguous, beginning at any element: no
+ * alignment beyond bf16's) for the frame's queries q (n rows, first n_s special, pooling size g).  scores: float [P]. */
 int xsv_score(void* hip_stream, xsv_tensor q, const void* k_mid_bf16, int H, int n, int n_s, int P, int d, int g,
               float* scores);
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving loops, harnesses

@@ -165,6 +165,8 @@ constexpr int score_lds() {
 // front (one memory round trip): the group parameters of all its items (staged in LDS, they are shared by a tile's tokens) and the
 // thread's codes of all items.  An item is a head's keys of the workgroup's tile, or a tile of the workgroup's head.
 // `lds`: score_lds(), and what pool_alone takes behind the first kD floats.
+// A caller's plain keys may begin at any bf16: their 16-byte loads promise no more than that (same instruction, same time).
+typedef __attribute__((ext_vector_type(4), aligned(2))) uint32_t KeyPiece;
 template <int BITS, int G, bool PER_HEAD, int THREADS, bool SYNC>
 __device__ __forceinline__ void score_part(const FrontLayer& ly, const FrontCommon& a, int list, int block, float* lds) {
   constexpr bool kQuant = BITS != 16;
@@ -236,7 +238,7 @@ __device__ __forceinline__ void score_part(const FrontLayer& ly, const FrontComm
       if constexpr (kQuant) {
         w[i][0] = valid ? *p : 0u;
       } else {
-        const uint4 v = valid ? *reinterpret_cast<const uint4*>(p) : make_uint4(0, 0, 0, 0);
+        const KeyPiece v = valid ? *reinterpret_cast<const KeyPiece*>(p) : KeyPiece{0, 0, 0, 0};
         w[i][0] = v.x; w[i][1] = v.y; w[i][2] = v.z; w[i][3] = v.w;
       }
     }

@@ -171,6 +171,23 @@ def test_score_matches_oracle(H, n, n_s, P, g):
     assert np.array_equal(s, s2)
 
 
+@pytest.mark.parametrize("offset", [1, 2, 3, 4, 7, 8])
+@pytest.mark.parametrize("H,n,P", [(3, 37, 70), (16, 64, 333)])
+def test_score_of_keys_that_begin_at_any_element(H, n, P, offset):
+    """Contiguous keys anywhere in a buffer (2 to 16 bytes past a 16-byte boundary): the bits of the same keys on one."""
+    print(f"score H={H} n={n} P={P} offset={offset}", flush=True)
+    q = randn_bf16((H, n, 64), n + P)
+    k = randn_bf16((H, P, 64), n + P + 1, outliers=(7, 21, 33))
+    moved = torch.zeros(offset + H * P * 64, dtype=torch.bfloat16, device=DEV)[offset:].view(H, P, 64)
+    moved.copy_(k)
+    assert k.data_ptr() % 16 == 0 and moved.data_ptr() % 16 == 2 * offset % 16
+    want = xsv.score(q, k, 5, 16)
+    assert torch.equal(xsv.score(q, moved, 5, 16), want)
+    out = torch.full_like(want, float("nan"))
+    xsv.score_noalloc(q, moved, 5, 16, out)
+    assert torch.equal(out, want)
+
+
 @pytest.mark.parametrize("P,k", [(1, 1), (50, 0), (50, 50), (257, 100), (2722, 1348), (7151, 6110), (40000, 12345)])
 def test_topk_keep_bit_exact_with_ties(P, k):
     print(f"topk P={P} k={k}", flush=True)
