@@ -51,6 +51,9 @@ int xsv_attend_times(xsv_ctx* ctx, int32_t* launches, float* attend_ms, float* m
 int xsv_chain_times(xsv_ctx* ctx, int32_t* steps, float* score_prune_ms, float* quantize_ms);
 /* Grid (workgroups) of the most recent attention launch of this context, 0 before the first. */
 int xsv_last_attend_workgroups(xsv_ctx* ctx, int32_t* workgroups);
+/* 1 if the last workgroup of each cut (head, query block) of that launch merges its partial results, 0 if a second kernel does
+ * or nothing was cut. */
+int xsv_last_attend_merge(xsv_ctx* ctx, int32_t* inside);
 /* Tuning: workgroup shape of the attention kernel (waves x query rows per wave).  3 = 8 x 64, 0 = 4 x 64,
  * 1 = 4 x 32, 2 = 8 x 32.  Default: 3, or 2 where blocks of 256 rows pad a frame's tokens less than blocks
  * of 512 (e.g. 1041 tokens).  Other values: XSV_ERR_ARG.  Results agree to rounding. */

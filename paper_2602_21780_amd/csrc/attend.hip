@@ -1224,16 +1224,14 @@ static hipError_t launch_attend_t(const AttendArgs& a, hipStream_t stream, hipEv
   };
   using std::true_type;
   using std::false_type;
-  bool inside = false;
-  if constexpr (NW == 8) {  // (the shapes that the library chooses by itself)
-    inside = a.merge_inside;
-    if (inside) a.n_layers == 1 ? launch(true_type{}, true_type{}) : launch(false_type{}, true_type{});
+  if constexpr (NW == 8) {  // (attend_merges_inside: nobody sets merge_inside for the other shapes)
+    if (a.merge_inside) a.n_layers == 1 ? launch(true_type{}, true_type{}) : launch(false_type{}, true_type{});
   }
-  if (!inside) a.n_layers == 1 ? launch(true_type{}, false_type{}) : launch(false_type{}, false_type{});
+  if (!a.merge_inside) a.n_layers == 1 ? launch(true_type{}, false_type{}) : launch(false_type{}, false_type{});
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (between && (e = hipEventRecord(between, stream)) != hipSuccess) return e;
-  if (a.cut && !inside) {
+  if (a.cut && !a.merge_inside) {
     const int n_units = a.n_layers * a.H * ((a.n + a.rows_wg - 1) / a.rows_wg);
     hipLaunchKernelGGL(combine_kernel, dim3(a.equal_ranges > 0 ? n_units : a.n_wgs - 1, (a.rows_wg + 31) / 32), dim3(256), 0,
                        stream, a);
@@ -1267,6 +1265,8 @@ void partition_unit_query(long long n_units, int n_tiles, int n_wgs, int unit, i
 int attend_rows_per_workgroup(int variant) {
   return variant == 1 ? 128 : (variant == 3 ? 512 : 256);
 }
+
+bool attend_merges_inside(int variant) { return variant >= 2; }  // 8 waves: what the library chooses by itself
 
 AttendPlan plan_attend(int variant, int n_layers, int H, int n, int Tc, int want_wgs, size_t part_rows) {
   const int rows_wg = attend_rows_per_workgroup(variant);

@@ -62,6 +62,7 @@ struct xsv_ctx {
   int splits_single = 0, splits_batched = 0;
   int attend_variant = 3;  // 8 waves x 64 query rows per workgroup (xsv_create picks 8 x 32 where that wastes fewer rows)
   int last_attend_wgs = 0;  // grid of the most recent attention launch
+  int last_attend_merge = 0;  // AttendArgs::merge_inside of it
   // optional timing of the attention launches: events before, between the two kernels, after, and one more
   // right behind (the span of the last two, with nothing between them, is what an event pair itself costs)
   bool timing = false;
@@ -318,7 +319,7 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
   a.n_wgs = plan.n_wgs;
   a.rows_wg = plan.rows_wg;
   a.cut = plan.max_pieces > 1;
-  a.merge_inside = a.cut && beside_chain && plan.max_pieces <= kMergeInside;
+  a.merge_inside = a.cut && beside_chain && plan.max_pieces <= kMergeInside && attend_merges_inside(a.variant);
   {
     const int n_units = ((a.n + plan.rows_wg - 1) / plan.rows_wg) * ctx->cfg.n_heads * n_layers;
     const int ranges = plan.n_wgs % n_units == 0 ? plan.n_wgs / n_units : 0;
@@ -331,6 +332,7 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
     if (a.equal_ranges > 0) range_starts(n_ct, n_ft, a.equal_ranges, short_last ? short_pct : 100, ctx->frame_tile_cost, a.range_begin);
   }
   ctx->last_attend_wgs = plan.n_wgs;
+  ctx->last_attend_merge = a.merge_inside;
   a.qscale = ctx->cfg.softmax_scale * 1.4426950408889634f;
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   if (ctx->timing) {
@@ -653,6 +655,12 @@ int xsv_chain_times(xsv_ctx* ctx, int32_t* steps, float* score_prune_ms, float* 
 int xsv_last_attend_workgroups(xsv_ctx* ctx, int32_t* workgroups) {
   if (!ctx || !workgroups) return XSV_ERR_ARG;
   *workgroups = ctx->last_attend_wgs;
+  return XSV_OK;
+}
+
+int xsv_last_attend_merge(xsv_ctx* ctx, int32_t* inside) {
+  if (!ctx || !inside) return XSV_ERR_ARG;
+  *inside = ctx->last_attend_merge;
   return XSV_OK;
 }
 

@@ -50,7 +50,7 @@ EXPORTS = (
 TUNE_EXPORTS = (
     "xsv_set_attend_splits", "xsv_set_attend_variant", "xsv_set_side_cus", "xsv_set_short_range", "xsv_set_frame_tile_cost",
     "xsv_set_pool_polls",
-    "xsv_last_attend_workgroups", "xsv_settled_blocks", "xsv_set_attend_timing", "xsv_attend_times", "xsv_chain_times", "xsv_measure_peaks",
+    "xsv_last_attend_workgroups", "xsv_last_attend_merge", "xsv_settled_blocks", "xsv_set_attend_timing", "xsv_attend_times", "xsv_chain_times", "xsv_measure_peaks",
     "xsv_key_ranges", "xsv_line_partition", "xsv_step_plan",
 )
 
@@ -85,6 +85,7 @@ def lib():
         L.xsv_set_pool_polls.argtypes = [vp, i32]
         L.xsv_set_frame_tile_cost.argtypes = [vp, i32]
         L.xsv_last_attend_workgroups.argtypes = [vp, C.POINTER(C.c_int32)]
+        L.xsv_last_attend_merge.argtypes = [vp, C.POINTER(C.c_int32)]
         L.xsv_set_attend_timing.argtypes = [vp, i32]
         L.xsv_settled_blocks.argtypes = [vp, i32, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
         L.xsv_chain_times.argtypes = [vp, C.POINTER(C.c_int32), C.POINTER(C.c_float), C.POINTER(C.c_float)]
@@ -212,6 +213,11 @@ class Context:
         w = C.c_int32()
         _check(lib().xsv_last_attend_workgroups(self._h, C.byref(w)), "xsv_last_attend_workgroups")
         return w.value
+
+    def last_attend_merges_inside(self) -> bool:
+        inside = C.c_int32()
+        _check(lib().xsv_last_attend_merge(self._h, C.byref(inside)), "xsv_last_attend_merge")
+        return bool(inside.value)
 
     def settled_blocks(self, layer=0):
         """((head, block) pairs the re-quantization no longer touches, (head, block) pairs in the layer's cache)."""

@@ -221,31 +221,66 @@ def test_score_workgroups_that_pool_by_themselves(mode, H, n, budget, bits, G):
     alone.destroy()
 
 
-@pytest.mark.parametrize("variant", [0, 1, 2, 3])
-@pytest.mark.parametrize("splits,n,budget", [(2, 600, 1900), (5, 600, 1900), (6, 257, 2000), (16, 300, 4300), (16, 130, 700)])
-def test_units_merged_by_their_last_workgroup_equal_the_second_launch(variant, splits, n, budget):
-    """With the chain beside attention the last workgroup of a cut unit merges it, without it a launch of its own does: the same
-    bits, over steps that reuse the counters, for fewer and more pieces than a lane holds at a time, for rows that are NaN and
-    go through the tiles twice, and (16 pieces of a short unit) for workgroups that end one unit and begin the next."""
-    outs, wgs = [], []
+def run_merge_forms(layers, H, n, budget, bits, G, variant, splits):
+    """The frames of a stream in the three overlap modes (the same grids in all of them): outputs, whether a launch of the pruning
+    steps merged inside, and the workgroups of the last launch."""
+    outs, inside, wgs = [], [], []
     for overlap in (0, 1, 2):
-        ctx = xsv.Context(1, 3, 64, n, 5, budget, 4, 64)
+        ctx = xsv.Context(layers, H, 64, n, 5, budget, bits, G)
         ctx.set_attend_variant(variant)
         ctx.set_attend_splits(splits, splits)
+        ctx.set_side_cus(0)
         ctx.set_overlap(overlap)
         g = torch.Generator().manual_seed(n)
-        frames = []
+        frames, merges = [], set()
         for f in range(-(-budget // n) + 3):
-            q, k, v = (torch.randn((3, n, 64), generator=g).to(torch.bfloat16).to(DEV) for _ in range(3))
-            q[1, n - 1] = float("nan") if f % 2 else 1.0
-            frames.append(ctx.step(0, q, k, v))
+            q, k, v = (torch.randn((layers, H, n, 64), generator=g).to(torch.bfloat16).to(DEV) for _ in range(3))
+            q[:, 1, n - 1] = float("nan") if f % 2 else 1.0
+            scored = f > 0 and ctx.cache_len(0) + n > budget
+            frames.append(ctx.step_all_layers(q, k, v) if layers > 1 else ctx.step(0, q[0], k[0], v[0]))
+            if scored:
+                merges.add(ctx.last_attend_merges_inside())
+            else:
+                assert not ctx.last_attend_merges_inside()
         ctx.join()
         torch.cuda.synchronize()
         outs.append(torch.stack(frames).view(torch.int16))
+        inside.append(merges)
         wgs.append(ctx.last_attend_workgroups())
         ctx.destroy()
-    assert wgs[0] == wgs[1] == wgs[2] > 3 * -(-n // (256, 128, 256, 512)[variant])   # more workgroups than units
+    assert wgs[0] == wgs[1] == wgs[2]
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    return inside, wgs[0]
+
+
+@pytest.mark.parametrize("bits,G", [(4, 64), (4, 32), (2, 64), (2, 32), (16, 64)])
+@pytest.mark.parametrize("variant", [2, 3])
+@pytest.mark.parametrize("layers,H,splits,n,budget", [(1, 3, 2, 600, 1900), (1, 3, 3, 257, 2000), (1, 3, 4, 300, 1300), (1, 3, 5, 600, 1900),
+                                                      (1, 3, 16, 130, 700), (3, 4, 2, 257, 2000), (3, 4, 0, 600, 1900)])
+def test_units_merged_by_their_last_workgroup_equal_the_second_launch(layers, H, splits, n, budget, variant, bits, G):
+    """With the chain beside attention the last workgroup of a cut unit merges it, without it a launch of its own does: the same
+    bits from every kernel that merges inside, over steps that reuse the counters, for two to five equal ranges, for one layer and
+    several, for rows that are NaN and go through the tiles twice, and (16 pieces asked of a short unit; several layers whose
+    partials have room for five) for workgroups that end one unit and begin the next."""
+    print(f"merge {bits} {G} {variant} {layers} {splits} {n}", flush=True)
+    inside, wgs = run_merge_forms(layers, H, n, budget, bits, G, variant, splits)
+    assert inside == [{False}, {True}, {True}]
+    units = layers * H * -(-n // (256, 128, 256, 512)[variant])
+    if splits in (2, 3, 4, 5):
+        assert wgs == units * splits
+    else:
+        assert wgs > units and wgs % units != 0
+
+
+FOUR_WAVES = [(v, *c) for v in (0, 1) for c in ((2, 600, 1900), (5, 600, 1900), (6, 257, 2000), (16, 300, 4300), (16, 130, 700))]
+
+
+@pytest.mark.parametrize("variant,splits,n,budget", FOUR_WAVES + [(v, *c) for v in (2, 3) for c in ((6, 257, 2000), (16, 300, 4300))])
+def test_shapes_and_cuts_that_the_second_launch_merges(variant, splits, n, budget):
+    """Four waves, and more pieces than a lane holds at a time: a second launch merges whatever runs beside attention."""
+    inside, wgs = run_merge_forms(1, 3, n, budget, 4, 64, variant, splits)
+    assert inside == [{False}, {False}, {False}]
+    assert wgs > 3 * -(-n // (256, 128, 256, 512)[variant])   # more workgroups than units
 
 
 def test_budget_below_two_frames_keeps_first_and_current():
