@@ -24,10 +24,24 @@ sys.path.insert(0, ROOT)
 PEAK_BF16_MFMA_TFLOPS = 2500.0   # MI355X dense bf16
 PEAK_HBM_GBS = 8000.0
 # Not measurable from inside this process: HBM bytes per attend_kernel launch of this workload from the two
-# rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE) summarized in profiles/attend_cfg2_hbm_traffic.md.  Reported under
-# "traffic_from_profile" with the profile's date and only for the grid it was measured on; "traffic" itself stays null.
-TRAFFIC_PROFILE = {"file": "profiles/attend_cfg2_hbm_traffic.md", "date": "2026-12-03", "workgroups": 240,
-                   "fetch_bytes": 13.4e6, "write_bytes": 15.8e6}
+# rocprofv3 --pmc runs (FETCH_SIZE, WRITE_SIZE) summarized in the file, by the grid and by who merges the key ranges (a launch
+# that merges inside also reads all partials back and writes the outputs).  Reported under "traffic_from_profile" and only for
+# a launch that was counted; "traffic" itself stays null.
+TRAFFIC_PROFILES = [
+    {"file": "profiles/attend_cfg2_hbm_traffic.md", "date": "2026-12-03", "workgroups": 240, "merges_inside": False,
+     "fetch_bytes": 13.4e6, "write_bytes": 15.8e6},
+    {"file": "profiles/attend_cfg2_hbm_traffic.md", "date": "2026-12-03", "workgroups": 240, "merges_inside": True,
+     "fetch_bytes": 29.874e6, "write_bytes": 18.652e6},
+]
+
+
+def traffic_from_profile(workgroups, merges_inside, algorithmic_bytes):
+    """The counted HBM bytes of an attention launch of this grid and merge form, None if it was not counted."""
+    for p in TRAFFIC_PROFILES:
+        if p["workgroups"] == workgroups and p["merges_inside"] == merges_inside:
+            total = p["fetch_bytes"] + p["write_bytes"]
+            return dict(p, bytes=total, ratio_to_algorithmic=round(total / algorithmic_bytes, 2))
+    return None
 
 
 def algorithmic_work(spec, Tc, Tn, P):
@@ -123,6 +137,7 @@ def main():
     ms_per_step = elapsed / K * 1e3
     value = K / elapsed
     step_wgs = ctx.last_attend_workgroups()   # attention grid of the timed steps
+    merges_inside = ctx.last_attend_merges_inside()   # and whether its launch includes the merge of the key ranges
     Tn = ctx.cache_len(0)
     P = Tc + n - 2 * n
     work = algorithmic_work(spec, Tc, Tn, P)
@@ -194,25 +209,24 @@ def main():
     iso_launches, iso_attend_span, iso_merge_span, iso_event = ctx.attend_times()
     ctx.set_attend_timing(False)
     iso_attend_ms = iso_attend_span - iso_event
-    traffic_from_profile = None
-    if TRAFFIC_PROFILE["fetch_bytes"] is not None and step_wgs == TRAFFIC_PROFILE["workgroups"]:
-        traffic_from_profile = dict(TRAFFIC_PROFILE, bytes=TRAFFIC_PROFILE["fetch_bytes"] + TRAFFIC_PROFILE["write_bytes"],
-                                    ratio_to_algorithmic=round((TRAFFIC_PROFILE["fetch_bytes"] + TRAFFIC_PROFILE["write_bytes"]) / work["attend_bytes"], 2))
+    iso_merges_inside = ctx.last_attend_merges_inside()
     roofline = {
         "kernel": "attend_kernel<4,64,8,2>",
         "bound": "mfma", "achieved": round(attend_tflops, 2), "peak": PEAK_BF16_MFMA_TFLOPS, "unit": "TFLOP/s",
         "frac": round(attend_tflops / PEAK_BF16_MFMA_TFLOPS, 4),
-        "traffic": None, "traffic_from_profile": traffic_from_profile,
+        "traffic": None, "traffic_from_profile": traffic_from_profile(step_wgs, merges_inside, work["attend_bytes"]),
         "measured_on": "the launches of a second pass over the timed frames in the timed configuration (chain beside "
                        "attention, deferred joins), events of the library on the launch stream around every launch",
         "algorithmic_bytes": work["attend_bytes"],
         "flop_per_launch": work["attend_flop"], "avg_launch_ms": round(attend_kernel_ms, 4), "launches_timed": n_timed_launches,
         "workgroups": step_wgs,
+        # True: avg_launch_ms and achieved include the merge, and merge_kernel_ms is the span of an event pair with nothing between
+        "merges_inside": merges_inside,
         "merge_kernel_ms": round(merge_kernel_ms, 4), "event_pair_ms": round(event_ms, 4),
         "attend_plus_merge_TFLOPs": round(work["attend_flop"] / ((attend_kernel_ms + merge_kernel_ms) * 1e-3) / 1e12, 2),
         "frames_per_s_with_events": round(K / elapsed_with_events, 2),
         "isolated": {   # attention launches alone, 24 back to back, nothing running beside them
-            "avg_launch_ms": round(iso_attend_ms, 4), "merge_kernel_ms": round(iso_merge_span - iso_event, 4),
+            "merges_inside": iso_merges_inside, "avg_launch_ms": round(iso_attend_ms, 4), "merge_kernel_ms": round(iso_merge_span - iso_event, 4),
             "launches_timed": iso_launches, "TFLOPs": round(work["attend_flop"] / (iso_attend_ms * 1e-3) / 1e12, 2),
             "attend_plus_merge_ms": round(stage_ms["attend"], 4),
         },
