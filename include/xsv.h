@@ -202,7 +202,7 @@ int xsv_score(void* hip_stream, xsv_tensor q, const void* k_mid_bf16, int H, int
  * a fixed device array of the library instead of a hipMalloc'ed buffer.  Same arguments, same kernels, same
  * scores as xsv_score.  Differences: it calls no hipMalloc / hipFree and does not wait - it only enqueues on
  * hip_stream, so `scores` is valid once the stream has passed the call; H is limited to
- * XSV_NOALLOC_MAX_HEADS (more: XSV_ERR_UNSUPPORTED, nothing launched); the array (16 KB) stays allocated on
+ * XSV_NOALLOC_MAX_HEADS (more: XSV_ERR_UNSUPPORTED, nothing launched); the array (64 KB) stays allocated on
  * every device the call ran on until the process ends.  All calls on one device share that array: calls
  * whose kernels could overlap on one device (different streams, no ordering between them) race; order them. */
 #define XSV_NOALLOC_MAX_HEADS 64

@@ -1103,7 +1103,7 @@ int xsv_score(void* hip_stream, xsv_tensor q, const void* k_mid_bf16, int H, int
 }
 
 // ---- the entry point that allocates nothing ---------------------------------------------------------
-// xsv_score needs one scratch buffer: the per-head partial sums of the pooled query that pool_query_kernel
+// xsv_score needs one scratch buffer: the per-head partial sums of the pooled query that pool_kernel
 // writes and score_kernel folds.  Here it lives in a file-scope device array instead of a hipMalloc'ed
 // temporary.  The array's name is only a host-side handle: its device address is looked up once per device
 // (each device holds its own copy) and that pointer is what the kernels get.

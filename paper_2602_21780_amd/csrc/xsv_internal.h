@@ -141,10 +141,16 @@ struct AttendArgs {
   int cut;       // some unit is shared by several workgroups: partials are written and merged
   // The last workgroup of a cut unit merges it, instead of a second launch.  For steps with the chain beside attention, where a
   // second launch waits for places among the chain's workgroups (us per pass, second launch and merge inside: 24 layers with
-  // deferred joins 1325 and 1312, joined 1529 and 1525, 24 layers of a 2-bit cache of 8192 tokens 2460 and 2405), and up to
-  // kMergeInside pieces: the last workgroup reads all of them (six 2-bit layers of 777 tokens and 9 pieces 287 and 315).  With
-  // nothing beside it the second launch is better, since it takes the whole chip: four ragged layers stage by stage 171 and 176,
-  // frame-wise attention 23.7 and 24.2; a chain without scores is over by then: one layer of that kind 50.5 and 51.1.
+  // deferred joins 1325 and 1312, 24 layers of a 2-bit cache of 8192 tokens 2460 and 2405; joined the 24 layers are level, 1529
+  // and 1525).  Up to kMergeInside pieces, which the last workgroup reads all by itself (six 2-bit layers of 777 tokens and 9
+  // pieces 287 and 315).  Below that the number of pieces decides little.  Eight layers with 16 x 1374 rows cut into 2 / 3 / 4 / 5:
+  // joined 740 571 486 623 and 741 571 486 616, deferred 704 535 446 552 and 708 536 451 554.  In the library's own cuts, joined
+  // and then deferred: 16 x 1041 of 2 bits 522 and 486, 486 and 450; 12 x 1041 415 and 408, 373 and 348; 14 x 1374 472 and 467,
+  // 423 and 431; 16 x 700 366 and 361, 299 and 308.
+  // With nothing beside it the second launch is better, since it takes the whole chip: four ragged layers stage by stage 171 and
+  // 176, frame-wise attention 23.7 and 24.2.  Beside a chain without scores, which is over by then, it is at the sizes that the
+  // line was drawn for (one layer of 16 x 1374 50.5 and 51.8, eight 402 and 407, 366 and 372); with fewer tokens merging inside would
+  // be faster there too (eight layers of 16 x 1041 381 and 360, 346 and 326, of 16 x 700 314 and 277, 268 and 217).
   int merge_inside;
   int equal_ranges;  // > 0: every unit is cut into exactly this many key ranges, at the same tiles:
   // range p of a unit is its tiles [range_begin[p], range_begin[p + 1]); chosen on the host so that the ranges
