@@ -149,7 +149,7 @@ struct AttendArgs {
   // 423 and 431; 16 x 700 366 and 361, 299 and 308.
   // With nothing beside it the second launch is better, since it takes the whole chip: four ragged layers stage by stage 171 and
   // 176, frame-wise attention 23.7 and 24.2.  Beside a chain without scores, which is over by then, it is at the sizes that the
-  // line was drawn for (one layer of 16 x 1374 50.5 and 51.8, eight 402 and 407, 366 and 372); with fewer tokens merging inside would
+  // line was drawn for (one layer of 16 x 1374 51 and 52, eight 402 and 407, 366 and 372); with fewer tokens merging inside would
   // be faster there too (eight layers of 16 x 1041 381 and 360, 346 and 326, of 16 x 700 314 and 277, 268 and 217).
   int merge_inside;
   int equal_ranges;  // > 0: every unit is cut into exactly this many key ranges, at the same tiles:
