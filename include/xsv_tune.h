@@ -15,7 +15,7 @@ extern "C" {
 #endif
 
 /* Tuning: number of equal key ranges every (head, block of query rows) is cut into by the attention
- * kernel (partial results are merged by a second kernel, or by the workgroup that ends last), 1..16.  0 (default) = one workgroup per
+ * kernel (partial results are merged by a second kernel, or by the workgroups themselves), 1..16.  0 (default) = one workgroup per
  * slot of the chip, the key tiles of all (head, query block) pairs dealt out evenly among them. */
 int xsv_set_attend_splits(xsv_ctx* ctx, int per_layer_calls, int batched_calls);
 /* Tuning: compute units the attention launch of xsv_step / xsv_step_all_layers leaves free for the
@@ -24,8 +24,8 @@ int xsv_set_attend_splits(xsv_ctx* ctx, int per_layer_calls, int batched_calls);
  * is long (more than about 24 key tiles per workgroup).  Ignored when overlap is off or splits are fixed. */
 int xsv_set_side_cus(xsv_ctx* ctx, int compute_units);
 /* Tuning: in xsv_step / xsv_step_all_layers with overlap, cut every (head, query block) into one more key
- * range than the spare units allow, the extra one `percent` of a full range long (1..100; 0 = off; -1 = default: 35): its
- * workgroups end early and hand their compute units to the chain for the rest of the attention launch. */
+ * range than the spare units allow, the extra one `percent` of a full range long (1..100; 0 = off; -1 = default: 35 where
+ * joins are deferred and ranges are long, else 0): its workgroups end early and hand their compute units to the chain for the rest of the attention launch. */
 int xsv_set_short_range(xsv_ctx* ctx, int percent);
 /* Tuning: what a key tile of the frame's own bf16 rows costs the attention kernel relative to a tile of the packed
  * cache, in percent (25..400, default 95: bf16 rows need no dequantization).  When every (head, query block) is cut into the same key ranges, the
@@ -51,7 +51,7 @@ int xsv_attend_times(xsv_ctx* ctx, int32_t* launches, float* attend_ms, float* m
 int xsv_chain_times(xsv_ctx* ctx, int32_t* steps, float* score_prune_ms, float* quantize_ms);
 /* Grid (workgroups) of the most recent attention launch of this context, 0 before the first. */
 int xsv_last_attend_workgroups(xsv_ctx* ctx, int32_t* workgroups);
-/* 1 if the last workgroup of each cut (head, query block) of that launch merges its partial results, 0 if a second kernel does
+/* 1 if the workgroups of each cut (head, query block) of that launch merge its partial results, 0 if a second kernel does
  * or nothing was cut. */
 int xsv_last_attend_merge(xsv_ctx* ctx, int32_t* inside);
 /* Tuning: workgroup shape of the attention kernel (waves x query rows per wave).  3 = 8 x 64, 0 = 4 x 64,

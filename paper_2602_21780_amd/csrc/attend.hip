@@ -29,7 +29,7 @@
 //   number of workgroups gets the same amount of work; a piece may end one unit and begin the
 //   next, and the workgroup handles them one after the other.  In both forms a unit covered by one
 //   workgroup is normalized and written directly; otherwise each workgroup writes an unnormalized
-//   partial, and the workgroup that finishes the unit merges them, or combine_kernel does (AttendArgs::merge_inside).
+//   partial, and the unit's workgroups merge them together, or combine_kernel does (AttendArgs::merge_inside).
 //   Softmax.  No row maximum and no rescaling on the common path: the reference of the exponent is the row maximum
 //   of a range's first 32 tokens plus 8 powers of two, and probabilities may grow above 1 - they are as exact there, in bf16 as
 //   in fp32.  Only when a tile's row sum passes 2^24 - looked at once per tile - are the references moved, which rescales sums and
@@ -359,17 +359,47 @@ __device__ __forceinline__ void store_frame_tile(const FrameRegs<NH>& st, uint16
 // Partials of cut units pass between workgroups on different dies, whose caches do not see each other: agent-scope accesses go
 // past them.  (With plain stores a workgroup would have to write its die's whole L2 back before it could say that it is done.)
 constexpr int kAgentScope = 16;  // the sc1 bit of a buffer instruction
-// A (piece, layer, head)'s partial rows, see Workspace
+// The partial rows from a (piece, layer, head)'s on, see Workspace.  Another piece's are a scalar offset away (the host sees to
+// it that all pieces of a launch lie within 2 GiB).
 struct PartialRows {
   __amdgpu_buffer_rsrc_t o, ml;
 };
 __device__ __forceinline__ PartialRows partial_rows(const AttendArgs& a, size_t piece_head) {
   const uint32_t blocks = ((uint32_t)a.n + 31u) / 32u;
-  return PartialRows{__builtin_amdgcn_make_buffer_rsrc(a.attn_o + piece_head * blocks * 2048, 0, (int)(blocks * 4096u), 0x00020000),
-                     __builtin_amdgcn_make_buffer_rsrc(a.attn_ml + piece_head * (uint32_t)a.n * 4, 0, (int)((uint32_t)a.n * 16u), 0x00020000)};
+  return PartialRows{__builtin_amdgcn_make_buffer_rsrc(a.attn_o + piece_head * blocks * 2048, 0, 0x7fffffff, 0x00020000),
+                     __builtin_amdgcn_make_buffer_rsrc(a.attn_ml + piece_head * (uint32_t)a.n * 4, 0, 0x7fffffff, 0x00020000)};
 }
 // This wave's partials have reached memory (its count of outstanding accesses is zero).
 __device__ __forceinline__ void partials_written() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// The workgroups of a cut unit meet at its counter (Workspace::unit_done), when their partials have reached memory, to share
+// the merge.  Who is not last waits for the others, but not for long: after `looks` looks at the counter it leaves, and the
+// others do its share.  One word says everything, so that everybody agrees on who is there: pieces that are done (bits 0..4, the
+// number before gives each its place), who of the others has seen that all are (bits 8..12), places that were left before all were
+// done (bits 16..31; none can be left after that).  Nobody depends on anybody's being resident: the last one to be done
+// never waits.  Where nobody waits at all (`waiting` false, the same for the whole launch) the last one is alone with the merge,
+// and the others need not say that they leave.
+// What bounds it: round trips to memory - the partials' way there, an atomic, a look or two, one trip for a sharer's part of all
+// pieces.  16 heads x 1374 rows in four long pieces and a short one: 1.7 us (median) from a partial's being written to the meeting's end, 2.0 us
+// of merging, where the last workgroup by itself took 0.8 and 6.1.
+constexpr uint32_t kMeetDone = 31u, kMeetAck = 1u << 8;
+struct Meeting {
+  int rank, sharers;  // this workgroup's number among those that share the merge (sharers = 0: it does not take part)
+};
+__device__ __forceinline__ Meeting meet(uint32_t* counter, int pieces, bool waiting, int looks) {
+  uint32_t v = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
+  const uint32_t place = (v & kMeetDone) - 1u, all = (uint32_t)pieces;
+  if (!waiting) return Meeting{0, (v & kMeetDone) == all ? 1 : 0};
+  for (int i = 0; i < looks && (v & kMeetDone) != all; ++i) {
+    __builtin_amdgcn_s_sleep(8);
+    v = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  while ((v & kMeetDone) != all)  // (fails, and goes on with the new value, only when somebody else has come or left)
+    if (__hip_atomic_compare_exchange_strong(counter, &v, v | (0x10000u << place), __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      return Meeting{0, 0};
+  const uint32_t left = v >> 16;
+  return Meeting{(int)(place - (uint32_t)__popc(left & ((1u << place) - 1u))), pieces - (int)__popc(left)};
+}
 
 // "No vector-memory load is outstanding here" as an instruction (s_waitcnt vmcnt(0)).  A tile loop fetches the next
 // tile under a condition and consumes it under the same condition further down; the compiler does not connect the
@@ -445,7 +475,7 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   constexpr int kPrmBlock = BITS == 16 ? 1 : 2 * Stage<BITS, G, NH>::kPrm;  // one tile's scales and zero points of one role
   __shared__ __attribute__((aligned(16))) float lds_prm[2][2][kPrmBlock];    // [role][buffer]
   __shared__ int careful_pass[2];  // some wave asks for it (by the parity of the unit's number in this workgroup)
-  __shared__ int finishes;         // this workgroup's piece was the last of its unit to be done
+  __shared__ int meeting[2];       // what thread 0 learned at a unit's meeting
 
   const int H = a.H, n = a.n, Tc = a.Tc;
   const int nqb = (n + kRowsWG - 1) / kRowsWG;
@@ -1019,37 +1049,46 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
     }
   };
 
-  // Merge of a unit's S <= kMergeInside pieces in the order of the pieces, whoever does it; the arithmetic is combine_kernel's.
-  // A lane takes the values it would have held of an uncut row, all pieces of a block of rows at once.  (Compact code, one block
-  // after the other: it is cold when a workgroup comes to it.)
-  auto merge = [&](int S) XSV_INLINE {
+  // Merge of a unit's S <= MOST pieces in the order of the pieces, whoever does it; the arithmetic is combine_kernel's.
+  // The unit's rows are dealt to `sharers` workgroups, this one is number `rank`: an item is a block of 32 rows and one of PARTS
+  // parts of the channels, a wave takes one after the other, and a lane the values it would have held of an uncut row, of all pieces
+  // at once.
+  auto merge = [&](auto parts, auto most, int S, int rank, int sharers) XSV_INLINE {
+    constexpr int PARTS = decltype(parts)::value, MOST = decltype(most)::value;
+    constexpr int kQuads = 4 / PARTS;  // 16-byte runs of a lane's 32 values
     __builtin_amdgcn_s_setprio(3);
+    const int row_first = qb * kRowsWG, items = PARTS * ((min(n - row_first, kRowsWG) + 31) / 32);
+    const int end = items * (rank + 1) / sharers;
+    const PartialRows from = partial_rows(a, (size_t)lb * H + h);
+    const uint32_t pieces_heads = (uint32_t)(a.n_layers * H);
+    const uint32_t o_piece = pieces_heads * (((uint32_t)n + 31u) / 32u) * 4096u, ml_piece = pieces_heads * (uint32_t)n * 16u;  // bytes
 #pragma unroll 1
-    for (int row0 = q_row0; row0 < min(n, q_row0 + 32 * QB); row0 += 32) {
-      const uint32_t at = (uint32_t)(row0 >> 5) * 4096u + (uint32_t)(hh * 32 + j) * 16u, at_ml = (uint32_t)(row0 + j) * 16u;
-      u32x4 ml[kMergeInside], o[kMergeInside][4];
+    for (int item = items * rank / sharers + wave; item < end; item += NW) {
+      const int row0 = row_first + 32 * (item / PARTS), part = item % PARTS;
+      const uint32_t at = (uint32_t)(row0 >> 5) * 4096u + (uint32_t)(part * kQuads) * 1024u + (uint32_t)(hh * 32 + j) * 16u;
+      const uint32_t at_ml = (uint32_t)min(row0 + j, n - 1) * 16u;
+      u32x4 ml[MOST], o[MOST][kQuads];
 #pragma unroll
-      for (int s = 0; s < kMergeInside; ++s)
-        if (s < S) {  // (rows past the frame read as zeros: never stored)
-          const PartialRows from = partial_rows(a, ((size_t)s * a.n_layers + lb) * H + h);
-          ml[s] = __builtin_amdgcn_raw_buffer_load_b128(from.ml, at_ml, 0, kAgentScope);
+      for (int s = 0; s < MOST; ++s)
+        if (s < S) {
+          ml[s] = __builtin_amdgcn_raw_buffer_load_b128(from.ml, at_ml, s * ml_piece, kAgentScope);
 #pragma unroll
-          for (int q = 0; q < 4; ++q) o[s][q] = __builtin_amdgcn_raw_buffer_load_b128(from.o, at + q * 1024u, 0, kAgentScope);
+          for (int q = 0; q < kQuads; ++q) o[s][q] = __builtin_amdgcn_raw_buffer_load_b128(from.o, at + q * 1024u, s * o_piece, kAgentScope);
         }
-      float M = kNegBig, L = 0.f, acc[32];
+      float M = kNegBig, L = 0.f, acc[8 * kQuads];
 #pragma unroll
-      for (int r = 0; r < 32; ++r) acc[r] = 0.f;
+      for (int r = 0; r < 8 * kQuads; ++r) acc[r] = 0.f;
 #pragma unroll
-      for (int s = 0; s < kMergeInside; ++s)
+      for (int s = 0; s < MOST; ++s)
         if (s < S) M = fmaxf(M, __uint_as_float(ml[s][0]));
 #pragma unroll
-      for (int s = 0; s < kMergeInside; ++s) {
+      for (int s = 0; s < MOST; ++s) {
         if (s < S) {
           const float wgt = __builtin_amdgcn_exp2f(__uint_as_float(ml[s][0]) - M);
           L += wgt * __uint_as_float(ml[s][1]);
           const float ws = wgt * __uint_as_float(ml[s][2]);
 #pragma unroll
-          for (int r = 0; r < 32; r += 2) {
+          for (int r = 0; r < 8 * kQuads; r += 2) {
             const f16x2 v = __builtin_bit_cast(f16x2, (uint32_t)o[s][r >> 3][(r >> 1) & 3]);
             acc[r] += ws * (float)v[0];
             acc[r + 1] += ws * (float)v[1];
@@ -1059,9 +1098,9 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
       const int q_row = row0 + j;
       const float inv = 1.0f / L;
       if (q_row < n) {
-        uint16_t* op = ly.out + ((size_t)h * n + q_row) * kD + 4 * hh;
+        uint16_t* op = ly.out + ((size_t)h * n + q_row) * kD + 16 * kQuads * part + 4 * hh;
 #pragma unroll
-        for (int r = 0; r < 32; r += 4)  // (channels as in write_rows)
+        for (int r = 0; r < 8 * kQuads; r += 4)  // (channels as in write_rows)
           *reinterpret_cast<uint2*>(op + 2 * r) = make_uint2(pack_bf16(acc[r] * inv, acc[r + 1] * inv), pack_bf16(acc[r + 2] * inv, acc[r + 3] * inv));
       }
     }
@@ -1129,13 +1168,27 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
   if (finish) {
     const int w0 = a.equal_ranges > 0 ? 0 : part.first_wg(unit);
     const int pieces = a.equal_ranges > 0 ? a.equal_ranges : part.last_wg(unit) - w0 + 1;
+    // (who still has a unit to work on, and a range that was made short so that its compute unit is free early, does not wait)
+    const bool waits = pos >= piece_end && !(a.short_last && my_range == pieces - 1);
+    uint32_t* const unit_done = a.unit_done + (size_t)unit * kMeetStride;
+    uint32_t acks = 0;
     if (tid == 0) {
-      uint32_t* const done = a.unit_done + unit;
-      finishes = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)pieces - 1u;
-      if (finishes) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // as the next launch wants it
+      const Meeting m = meet(unit_done, pieces, a.merge_looks > 0, waits ? a.merge_looks : 0);
+      meeting[0] = m.rank;
+      meeting[1] = m.sharers;
+      if (m.sharers > 0) acks = __hip_atomic_fetch_add(unit_done, kMeetAck, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(finishes)) merge(pieces);
+    const int rank = __builtin_amdgcn_readfirstlane(meeting[0]), sharers = __builtin_amdgcn_readfirstlane(meeting[1]);
+    if (sharers > 0) {
+      // (parts so small that a sharer's eight waves have an item each, and no smaller)
+      using std::integral_constant;
+      if (pieces <= (sharers == 1 ? 5 : 3)) merge(integral_constant<int, 1>{}, integral_constant<int, 5>{}, pieces, rank, sharers);
+      else if (pieces <= 8) merge(integral_constant<int, 2>{}, integral_constant<int, 8>{}, pieces, rank, sharers);
+      else merge(integral_constant<int, 4>{}, integral_constant<int, kMaxPieces>{}, pieces, rank, sharers);
+      // everybody who will look at the counter has looked: as the next launch wants it
+      if (tid == 0 && (acks / kMeetAck) % 32u == (uint32_t)sharers - 1u) __hip_atomic_store(unit_done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
   parity ^= 1;
   }  // units of this workgroup's piece
@@ -1224,7 +1277,7 @@ static hipError_t launch_attend_t(const AttendArgs& a, hipStream_t stream, hipEv
   };
   using std::true_type;
   using std::false_type;
-  if constexpr (NW == 8) {  // (attend_merges_inside: nobody sets merge_inside for the other shapes)
+  if constexpr (NW == 8 || QB == 2) {  // (attend_merges_inside: nobody sets merge_inside for the other shape)
     if (a.merge_inside) a.n_layers == 1 ? launch(true_type{}, true_type{}) : launch(false_type{}, true_type{});
   }
   if (!a.merge_inside) a.n_layers == 1 ? launch(true_type{}, false_type{}) : launch(false_type{}, false_type{});
@@ -1266,7 +1319,7 @@ int attend_rows_per_workgroup(int variant) {
   return variant == 1 ? 128 : (variant == 3 ? 512 : 256);
 }
 
-bool attend_merges_inside(int variant) { return variant >= 2; }  // 8 waves: what the library chooses by itself
+bool attend_merges_inside(int variant) { return variant != 1; }
 
 AttendPlan plan_attend(int variant, int n_layers, int H, int n, int Tc, int want_wgs, size_t part_rows) {
   const int rows_wg = attend_rows_per_workgroup(variant);

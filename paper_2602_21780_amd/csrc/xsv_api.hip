@@ -60,7 +60,7 @@ struct xsv_ctx {
   std::vector<LayerState> layers;
   std::vector<void*> allocs;
   int splits_single = 0, splits_batched = 0;
-  int attend_variant = 3;  // 8 waves x 64 query rows per workgroup (xsv_create picks 8 x 32 where that wastes fewer rows)
+  int attend_variant = -1;  // workgroup shape of the attention launches, -1: by attend_shape
   int last_attend_wgs = 0;  // grid of the most recent attention launch
   int last_attend_merge = 0;  // AttendArgs::merge_inside of it
   // optional timing of the attention launches: events before, between the two kernels, after, and one more
@@ -196,19 +196,34 @@ PrunePlan plan_for(const xsv_config& c, const LayerState& L) {
   return p;
 }
 
+int attend_units(const xsv_ctx* ctx, int variant, int n_layers) {
+  const int rows = attend_rows_per_workgroup(variant);
+  return ((ctx->cfg.tokens_per_frame + rows - 1) / rows) * ctx->cfg.n_heads * n_layers;
+}
+
+// Workgroup shape of an attention launch: 8 waves x 64 query rows, unless blocks of 256 rows leave fewer padding rows in a frame's
+// last block (1041 tokens: 1280 against 1536 rows).
+int attend_shape(const xsv_ctx* ctx) {
+  if (ctx->attend_variant >= 0) return ctx->attend_variant;
+  const int n = ctx->cfg.tokens_per_frame;
+  return round_up(n, 256) < round_up(n, 512) ? 2 : 3;
+}
+
 // Workgroups of one attention launch.  requested > 0: every unit is cut into that many equal key
 // ranges.  Otherwise one workgroup per slot of the chip (2 per compute unit for the 4-wave shapes, 1
 // for the 8-wave ones), minus the compute units left to kernels running beside it.
-AttendPlan choose_grid(const xsv_ctx* ctx, int n_layers, int Tc, int requested, int spare_cus) {
+AttendPlan choose_grid(const xsv_ctx* ctx, int variant, int n_layers, int Tc, int requested, int spare_cus) {
   const xsv_config& c = ctx->cfg;
-  const int rows = attend_rows_per_workgroup(ctx->attend_variant);
-  const int n_units = ((c.tokens_per_frame + rows - 1) / rows) * c.n_heads * n_layers;
-  const int per_cu = ctx->attend_variant >= 2 ? 1 : 2;
+  const int n_units = attend_units(ctx, variant, n_layers);
+  const int per_cu = variant >= 2 ? 1 : 2;
   int want = requested > 0 ? n_units * requested : per_cu * std::max(ctx->n_cu / 2, ctx->n_cu - spare_cus);
   // a grid that cuts every unit into the same number of ranges has no workgroup that ends one unit
-  // and begins another (two pipeline fills, two sets of partials); prefer it when it is nearly as large
+  // and begins another (two pipeline fills, two sets of partials), and its workgroups share the merge; prefer it when it is nearly
+  // as large (looked at behind plan_attend's limits of four tiles a piece and kMaxPieces pieces a unit)
+  const long long tiles = (Tc + kTile - 1) / kTile + (c.tokens_per_frame + kTile - 1) / kTile;
+  if (requested <= 0) want = (int)std::min<long long>(want, std::max<long long>(n_units, n_units * std::min<long long>(4 * kMaxPieces, tiles) / 4));
   if (requested <= 0 && want / n_units >= 1 && (want / n_units) * n_units * 8 >= want * 7) want = (want / n_units) * n_units;
-  return plan_attend(ctx->attend_variant, n_layers, c.n_heads, c.tokens_per_frame, Tc, want, ctx->part_rows);
+  return plan_attend(variant, n_layers, c.n_heads, c.tokens_per_frame, Tc, want, ctx->part_rows);
 }
 
 int fill_batch(xsv_ctx* ctx, Batch& b, int layer0, int n_layers, const xsv_tensor* q, const xsv_tensor* k,
@@ -269,6 +284,8 @@ void range_starts(int n_ct, int n_ft, int R, int last_pct, int frame_cost, int32
   begin[R] = n_tiles;
 }
 
+constexpr int kLongRange = 16;  // tiles of a key range that outlasts the chain (see do_attend)
+
 // The three stages for layers [layer0, layer0 + n_layers), which must be in step with each other.
 // beside_chain: pooling, score, select and re-quantization of the same layers are on the other stream.
 // frame_only: the frame's own tokens are the only keys (no cache tiles, no change of state).
@@ -296,20 +313,23 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
   }
   a.Tc = frame_only ? 0 : ctx->layers[layer0].T;
   a.n = ctx->cfg.tokens_per_frame;
-  a.variant = ctx->attend_variant;
-  AttendPlan plan = choose_grid(ctx, n_layers, a.Tc, splits_req, spare_cus);
+  a.variant = attend_shape(ctx);
+  AttendPlan plan = choose_grid(ctx, a.variant, n_layers, a.Tc, splits_req, spare_cus);
   const int n_ct = (a.Tc + kTile - 1) / kTile, n_ft = (a.n + kTile - 1) / kTile, n_tiles = n_ct + n_ft;
   bool short_last = false;
-  // (24 layers of 16 heads x 1374 tokens, 4-bit budget 4096, us per frame at 0 / 20 / 35 / 50 / 65 %: deferred joins
-  // 1315 / 1319 / 1282 / 1300 / 1343, a join per step 1498 / 1497 / 1487 / 1605 / 1638)
-  const int short_pct = ctx->short_pct >= 0 ? ctx->short_pct : 35;
+  // Beside a chain that nothing waits for, and if the other ranges are long enough to outlast it.  (While the short ranges run,
+  // their compute units are missing in some shader engines altogether, and the chain hardly starts.  24 layers of 16 x 1374
+  // tokens, us per frame at 0 / 20 / 35 / 50 %: deferred joins 1262 / 1244 / 1227 / 1240, joined by every step 1522 / 1621 / 1611 /
+  // 1620; of 16 x 700, long ranges of 12 tiles, 913 / 911 / 954 / 1220 deferred and 1212 / 1251 / 1313 / 1391 joined; six 2-bit layers
+  // of 12 x 777, 7 tiles, deferred 267 / 316 / 292.)
+  const int short_pct = ctx->short_pct >= 0 ? ctx->short_pct : (ctx->overlap == 2 ? 35 : 0);
   if (splits_req <= 0 && spare_cus > 0 && short_pct > 0) {
     // beside the overlapped chain: the equal cut that leaves spare units, plus one short range per unit
-    const int rows = attend_rows_per_workgroup(ctx->attend_variant);
-    const int n_units = ((a.n + rows - 1) / rows) * ctx->cfg.n_heads * n_layers;
+    const int n_units = attend_units(ctx, a.variant, n_layers);
     const int S = plan.n_wgs % n_units == 0 ? plan.n_wgs / n_units : 0;
-    if (S >= 1 && (S + 1) * n_units <= ctx->n_cu - 8 && S + 1 <= kMaxPieces && S + 1 <= n_tiles) {
-      const AttendPlan more = plan_attend(ctx->attend_variant, n_layers, ctx->cfg.n_heads, a.n, a.Tc, (S + 1) * n_units, ctx->part_rows);
+    const bool outlasts = 100 * n_tiles >= kLongRange * (100 * S + short_pct);
+    if (S >= 1 && (S + 1) * n_units <= ctx->n_cu - 8 && S + 1 <= kMaxPieces && S + 1 <= n_tiles && (ctx->short_pct >= 0 || outlasts)) {
+      const AttendPlan more = plan_attend(a.variant, n_layers, ctx->cfg.n_heads, a.n, a.Tc, (S + 1) * n_units, ctx->part_rows);
       if (more.n_wgs == (S + 1) * n_units) {
         plan = more;
         short_last = true;
@@ -319,7 +339,12 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
   a.n_wgs = plan.n_wgs;
   a.rows_wg = plan.rows_wg;
   a.cut = plan.max_pieces > 1;
-  a.merge_inside = a.cut && beside_chain && plan.max_pieces <= kMergeInside && attend_merges_inside(a.variant);
+  const bool own_cut = splits_req <= 0 && n_layers == 1 && plan.n_wgs % attend_units(ctx, a.variant, 1) == 0 && plan.max_pieces > 2;
+  // (the merge finds all pieces with 32-bit offsets)
+  const unsigned long long partial_bytes = 4096ull * plan.max_pieces * n_layers * ctx->cfg.n_heads * ((a.n + 31) / 32);
+  a.merge_inside = a.cut && attend_merges_inside(a.variant) && partial_bytes < (1ull << 31) &&
+                   (own_cut || (beside_chain && a.variant >= 2 && plan.max_pieces <= kMergeInside));
+  a.short_last = short_last;
   {
     const int n_units = ((a.n + plan.rows_wg - 1) / plan.rows_wg) * ctx->cfg.n_heads * n_layers;
     const int ranges = plan.n_wgs % n_units == 0 ? plan.n_wgs / n_units : 0;
@@ -331,6 +356,7 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
     a.xcd_heads = a.xcd_ranges > 0 && a.equal_ranges > 0 && (ctx->cfg.n_heads * n_layers) % 8 == 0;
     if (a.equal_ranges > 0) range_starts(n_ct, n_ft, a.equal_ranges, short_last ? short_pct : 100, ctx->frame_tile_cost, a.range_begin);
   }
+  a.merge_looks = a.equal_ranges > 0 ? kMergeLooks : 0;
   ctx->last_attend_wgs = plan.n_wgs;
   ctx->last_attend_merge = a.merge_inside;
   a.qscale = ctx->cfg.softmax_scale * 1.4426950408889634f;
@@ -502,9 +528,6 @@ int xsv_create(const xsv_config* cfg, void* hip_stream, xsv_ctx** out) {
     delete ctx;
     return XSV_ERR_HIP;
   }
-  // workgroups of 512 query rows unless blocks of 256 leave fewer padding rows in a frame's last block
-  // (1041 tokens: 1280 against 1536 rows)
-  ctx->attend_variant = round_up(c.tokens_per_frame, 256) < round_up(c.tokens_per_frame, 512) ? 2 : 3;
   ctx->pending.assign(c.n_layers, -1);
   ctx->seq.assign(c.n_layers, 0);
   for (int l = 0; l < c.n_layers; ++l) {
@@ -555,7 +578,7 @@ int xsv_create(const xsv_config* cfg, void* hip_stream, xsv_ctx** out) {
   ctx->part_rows = part_rows;
   A(&w.attn_o, part_rows * kD, false);
   A(&w.attn_ml, part_rows * 4, false);
-  A(&w.unit_done, (size_t)std::min(c.n_layers, kMaxBatch) * c.n_heads * ((n + 127) / 128), true);  // (128 rows: the smallest workgroup)
+  A(&w.unit_done, (size_t)std::min(c.n_layers, kMaxBatch) * c.n_heads * ((n + 127) / 128) * kMeetStride, true);  // (128 rows: the smallest workgroup)
   if (rc == XSV_OK && hipStreamSynchronize(ctx->stream) != hipSuccess) rc = XSV_ERR_HIP;
   if (rc != XSV_OK) {
     free_all(ctx);
@@ -825,10 +848,10 @@ static int step_layers(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor*
       int spare = ctx->side_cus;
       if (spare < 0) {
         const xsv_config& c = ctx->cfg;
-        const int rows = attend_rows_per_workgroup(ctx->attend_variant);
-        const long long units = (long long)((c.tokens_per_frame + rows - 1) / rows) * c.n_heads * n_layers;
+        const int variant = attend_shape(ctx);
+        const long long units = attend_units(ctx, variant, n_layers);
         const long long tiles = (ctx->layers[layer0].T + kTile - 1) / kTile + (c.tokens_per_frame + kTile - 1) / kTile;
-        const int per_cu = ctx->attend_variant >= 2 ? 1 : 2;
+        const int per_cu = variant >= 2 ? 1 : 2;
         const long long wgs = (long long)per_cu * (ctx->n_cu - ctx->n_cu / 4);
         spare = units * tiles > 24 * wgs ? ctx->n_cu / 8 : ctx->n_cu / 4;
       }

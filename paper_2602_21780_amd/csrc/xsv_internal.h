@@ -102,7 +102,7 @@ struct Workspace {
   uint16_t* attn_o;   // [pieces][batch layers][H][ceil(n/32)] blocks of 32 rows x 64 fp16 mantissas of the unnormalized
                       // partial outputs, each block stored [16-byte piece 0..3][lane half][row] (4 KB)
   float* attn_ml;     // [pieces][batch layers][H][n][4]  softmax reference (log2 domain), row sum, row scale, -
-  uint32_t* unit_done;  // [units of an attention launch] pieces of a cut unit that are done, zero between launches
+  uint32_t* unit_done;  // [units of an attention launch] where the workgroups of a cut unit meet (attend.hip), zero between launches
   int scores_stride;  // Tcap + n
   int sets;           // lists per layer (CachePool::sets)
 };
@@ -110,7 +110,11 @@ struct Workspace {
 // ---- launchers (defined in the .hip files; every one only enqueues on `stream`) -----------------
 
 constexpr int kMaxPieces = 16;  // workgroups that may share one unit
+// Words between the counters of two units: many workgroups look at them at the same time, and side by side in a few lines they
+// held up each other and the partials' stores (24 layers with deferred joins: 1406 us, 1214 apart).
+constexpr int kMeetStride = 64;
 constexpr int kMergeInside = 5;  // see AttendArgs::merge_inside
+constexpr int kMergeLooks = 32;  // see AttendArgs::merge_looks
 // One layer of an attention launch: device pointers at head 0 of the buffer that holds the layer's cache, and of the
 // frame's tensors.  (Resolved on the host: a workgroup's first tile waits behind whatever address arithmetic the
 // kernel has to do, and the argument block stays small.)
@@ -139,18 +143,13 @@ struct AttendArgs {
   int n_wgs;     // workgroups the (unit, tile) line is cut into (from plan_attend)
   int rows_wg;   // query rows per workgroup of this variant
   int cut;       // some unit is shared by several workgroups: partials are written and merged
-  // The last workgroup of a cut unit merges it, instead of a second launch.  For steps with the chain beside attention, where a
-  // second launch waits for places among the chain's workgroups (us per pass, second launch and merge inside: 24 layers with
-  // deferred joins 1325 and 1312, 24 layers of a 2-bit cache of 8192 tokens 2460 and 2405; joined the 24 layers are level, 1529
-  // and 1525).  Up to kMergeInside pieces, which the last workgroup reads all by itself (six 2-bit layers of 777 tokens and 9
-  // pieces 287 and 315).  Below that the number of pieces decides little.  Eight layers with 16 x 1374 rows cut into 2 / 3 / 4 / 5:
-  // joined 740 571 486 623 and 741 571 486 616, deferred 704 535 446 552 and 708 536 451 554.  In the library's own cuts, joined
-  // and then deferred: 16 x 1041 of 2 bits 522 and 486, 486 and 450; 12 x 1041 415 and 408, 373 and 348; 14 x 1374 472 and 467,
-  // 423 and 431; 16 x 700 366 and 361, 299 and 308.
-  // With nothing beside it the second launch is better, since it takes the whole chip: four ragged layers stage by stage 171 and
-  // 176, frame-wise attention 23.7 and 24.2.  Beside a chain without scores, which is over by then, it is at the sizes that the
-  // line was drawn for (one layer of 16 x 1374 51 and 52, eight 402 and 407, 366 and 372); with fewer tokens merging inside would
-  // be faster there too (eight layers of 16 x 1041 381 and 360, 346 and 326, of 16 x 700 314 and 277, 268 and 217).
+  // The workgroups of a cut unit merge it, each a share of its rows (see meet in attend.hip), instead of a second launch: where the
+  // library cuts one layer's units into three and more equal pieces, whatever runs beside it, and with other cuts of up to kMergeInside pieces
+  // beside a chain with scores, where a second launch waits for places among the chain's workgroups.  us per pass, second launch
+  // and inside: frame-wise attention of 16 x 1374 (5 pieces) 23.4 and 19.3, a bf16 cache grown by 16 frames, four layers, 5700
+  // and 5440, one layer of 16 x 1374 without scores 50.5 and 46.6, one of 5 x 539 in 11 pieces 41 and 33, six 2-bit layers of 12 x 777 in
+  // 8 281 and 267; two pieces of 9 x 501 17.8 and 18.4.  (With the last workgroup merging all by itself, 6 us for five
+  // pieces of 512 rows where four that share it take 2, 24 layers with deferred joins took 1305 and not 1212.)
   int merge_inside;
   int equal_ranges;  // > 0: every unit is cut into exactly this many key ranges, at the same tiles:
   // range p of a unit is its tiles [range_begin[p], range_begin[p + 1]); chosen on the host so that the ranges
@@ -159,6 +158,11 @@ struct AttendArgs {
   int32_t range_begin[17];
   int xcd_ranges;  // > 0: every unit is cut into this many key ranges and the grid is permuted for L2 sharing
   int xcd_heads;   // with xcd_ranges: (layer, head) pairs rather than (layer, head, range) triples are dealt to the XCDs
+  int short_last;   // the last of a unit's equal_ranges was made short (see range_begin)
+  // How often a workgroup that merges inside looks for the others of its unit before it leaves them its share (a look takes about
+  // 0.7 us; 24 layers with deferred joins at 0 / 4 / 16 / 32 looks: 1340 / 1249 / 1229 / 1228 us).  Only where all units are cut
+  // alike, so that its workgroups end together: a 2-bit stack on a line partition is 1 % slower with it.
+  int merge_looks;
   float qscale;  // softmax scale * log2(e)
 };
 struct AttendPlan {

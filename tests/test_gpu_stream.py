@@ -283,6 +283,38 @@ def test_shapes_and_cuts_that_the_second_launch_merges(variant, splits, n, budge
     assert wgs > 3 * -(-n // (256, 128, 256, 512)[variant])   # more workgroups than units
 
 
+@pytest.mark.parametrize("H,n,budget,bits,variant", [(3, 300, 4300, 4, 3), (3, 130, 700, 4, 3), (16, 1374, 0, 16, 3), (12, 777, 3000, 2, 3), (5, 282, 700, 4, 2),
+                                                     (8, 257, 2000, 2, 2)])
+def test_cuts_of_the_library_are_merged_by_all_workgroups_of_a_unit(H, n, budget, bits, variant):
+    """Without requested splits one layer's units of three and more equal pieces are merged inside whatever runs beside attention;
+    the same cut asked for is merged by a second launch.  The same bits from both: 3 to 16 pieces (whose items are whole, half and
+    quarter rows), rows that are NaN and go through the tiles twice, and the frame's own tokens only."""
+    print(f"own cut {H} {n} {budget} {bits} {variant}", flush=True)
+    own, asked = (xsv.Context(1, H, 64, n, 5, budget, bits, 64, max_frames=3) for _ in range(2))
+    g = torch.Generator().manual_seed(n)
+    for ctx in (own, asked):
+        ctx.set_overlap(0)
+        ctx.set_attend_variant(variant)
+    units = H * -(-n // (256, 128, 256, 512)[variant])
+    for f in range(-(-budget // n) + 3 if budget else 3):
+        q, k, v = (torch.randn((H, n, 64), generator=g).to(torch.bfloat16).to(DEV) for _ in range(3))
+        q[1, n - 1] = float("nan") if f % 2 else 1.0
+        for run in (lambda c: c.frame_attend(q, k, v), lambda c: c.step(0, q, k, v)):
+            a = run(own)
+            wgs = own.last_attend_workgroups()
+            assert own.last_attend_merges_inside() == (wgs > 2 * units and wgs % units == 0)
+            if wgs % units:      # (a line partition: not to be had by asking)
+                run(asked)
+                continue
+            asked.set_attend_splits(wgs // units, 0)
+            b = run(asked)
+            assert asked.last_attend_workgroups() == wgs and not asked.last_attend_merges_inside()
+            assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+            asked.set_attend_splits(0, 0)
+    own.destroy()
+    asked.destroy()
+
+
 def test_budget_below_two_frames_keeps_first_and_current():
     spec = CONFIGS[0].with_(name="k0", budget=100)
     run_stream(spec, 4)
