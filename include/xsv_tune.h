@@ -55,8 +55,8 @@ int xsv_last_attend_workgroups(xsv_ctx* ctx, int32_t* workgroups);
  * or nothing was cut. */
 int xsv_last_attend_merge(xsv_ctx* ctx, int32_t* inside);
 /* Tuning: workgroup shape of the attention kernel (waves x query rows per wave).  3 = 8 x 64, 0 = 4 x 64,
- * 1 = 4 x 32, 2 = 8 x 32.  Default: 3, or 2 where blocks of 256 rows pad a frame's tokens less than blocks
- * of 512 (e.g. 1041 tokens).  Other values: XSV_ERR_ARG.  Results agree to rounding. */
+ * 1 = 4 x 32, 2 = 8 x 32.  Default: 3, or where blocks of 256 rows pad a frame's tokens less than blocks
+ * of 512 (e.g. 1041 tokens) 2 for short launches and 0 for long ones.  Other values: XSV_ERR_ARG.  Results agree to rounding. */
 int xsv_set_attend_variant(xsv_ctx* ctx, int variant);
 
 /* Host only (no GPU call): where the attention launch of a step cuts a (head, query block)'s key tiles - `cache_tiles`

@@ -201,12 +201,21 @@ int attend_units(const xsv_ctx* ctx, int variant, int n_layers) {
   return ((ctx->cfg.tokens_per_frame + rows - 1) / rows) * ctx->cfg.n_heads * n_layers;
 }
 
-// Workgroup shape of an attention launch: 8 waves x 64 query rows, unless blocks of 256 rows leave fewer padding rows in a frame's
-// last block (1041 tokens: 1280 against 1536 rows).
-int attend_shape(const xsv_ctx* ctx) {
+// Workgroup shape of an attention launch.  8 waves x 64 query rows, unless blocks of 256 rows leave fewer padding rows in a frame's
+// last block (1041 tokens: 1280 against 1536 rows).  Of the two shapes of 256 rows, 8 waves x 32 have a compute unit to themselves
+// and read every key and value for 32 rows; 4 waves x 64 read them for 64 and share the compute unit with a second workgroup,
+// which is faster in the loop and slower in everything around it: for launches of 40 tiles and more per compute unit, 80 where
+// the layers' units follow each other on a line.  us per step, 8 x 32 and 4 x 64, 2 bits: one layer of 16 x 1041 and 4096 / 6000 /
+// 8192 / 10000 tokens (26 / 35 / 46 / 54 tiles) 66 and 69, 84 and 86, 98 and 91, 116 and 108; of 16 x 1270 / 9500 (46) 107 and
+// 101; several layers at a time, 2 of 16 x 1041 / 8192 (92) 169 and 152, 24 (1100) 1671 and 1348, 24 of 16 x 600 / 2400 (216) 350
+// and 305, but 6 of 16 x 600 / 3000 (64) 138 and 145.
+int attend_shape(const xsv_ctx* ctx, int n_layers, int Tc) {
   if (ctx->attend_variant >= 0) return ctx->attend_variant;
   const int n = ctx->cfg.tokens_per_frame;
-  return round_up(n, 256) < round_up(n, 512) ? 2 : 3;
+  if (round_up(n, 256) >= round_up(n, 512)) return 3;
+  if (ctx->cfg.group_size != 64) return 2;  // (4 x 64 takes more registers there than two workgroups of a compute unit have)
+  const long long tiles = (Tc + kTile - 1) / kTile + (n + kTile - 1) / kTile;
+  return attend_units(ctx, 2, n_layers) * tiles >= (n_layers > 1 ? 80 : 40) * (long long)ctx->n_cu ? 0 : 2;
 }
 
 // Workgroups of one attention launch.  requested > 0: every unit is cut into that many equal key
@@ -313,7 +322,7 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
   }
   a.Tc = frame_only ? 0 : ctx->layers[layer0].T;
   a.n = ctx->cfg.tokens_per_frame;
-  a.variant = attend_shape(ctx);
+  a.variant = attend_shape(ctx, n_layers, a.Tc);
   AttendPlan plan = choose_grid(ctx, a.variant, n_layers, a.Tc, splits_req, spare_cus);
   const int n_ct = (a.Tc + kTile - 1) / kTile, n_ft = (a.n + kTile - 1) / kTile, n_tiles = n_ct + n_ft;
   bool short_last = false;
@@ -848,7 +857,7 @@ static int step_layers(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor*
       int spare = ctx->side_cus;
       if (spare < 0) {
         const xsv_config& c = ctx->cfg;
-        const int variant = attend_shape(ctx);
+        const int variant = attend_shape(ctx, n_layers, ctx->layers[layer0].T);
         const long long units = attend_units(ctx, variant, n_layers);
         const long long tiles = (ctx->layers[layer0].T + kTile - 1) / kTile + (c.tokens_per_frame + kTile - 1) / kTile;
         const int per_cu = variant >= 2 ? 1 : 2;
