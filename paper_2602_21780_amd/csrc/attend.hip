@@ -1176,7 +1176,8 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
       const Meeting m = meet(unit_done, pieces, a.merge_looks > 0, waits ? a.merge_looks : 0);
       meeting[0] = m.rank;
       meeting[1] = m.sharers;
-      if (m.sharers > 0) acks = __hip_atomic_fetch_add(unit_done, kMeetAck, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      // (alone, it need not say that it has looked)
+      if (m.sharers > 1) acks = __hip_atomic_fetch_add(unit_done, kMeetAck, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
     const int rank = __builtin_amdgcn_readfirstlane(meeting[0]), sharers = __builtin_amdgcn_readfirstlane(meeting[1]);
