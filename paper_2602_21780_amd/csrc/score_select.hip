@@ -16,7 +16,8 @@
 // positions took 21.2 us as three kernels with nothing beside them, and takes 13.8 as one.  Beside attention, as a step runs it,
 // the kernel is no shorter than the three were together (7.9 + 8.9 + 10.2 before, 29.2 us now, medians of a trace): few compute
 // units are free then, its workgroups take turns on them, and all of them have the registers and the LDS of the score part.  What a
-// step gains there are two launches and the gaps between them.
+// step gains there are two launches and the gaps between them.  (61 registers, four workgroups to a compute unit; with the pool
+// of last resort unrolled like the first, 120 to 139, and steps that wait for the chain are 1 to 2 % slower.)
 // Nothing in it waits without end, whatever else is on the chip.  The workgroup that completes a list's scores goes on to select
 // it.  A score workgroup does wait for the pool (only at the end, with the key means in registers), which has smaller indices and
 // as a rule has been started before it; but launches of several streams may hold the places each other's pools need, so the wait
@@ -79,6 +80,7 @@ __device__ __forceinline__ uint64_t all_of(const FrontCommon& a, bool per_head) 
 constexpr int kPoolLds = (kThreads / 8) * (kD + 1);
 // Thread = (row lane, channel run).  A head has 128 row lanes (lane i: rows i, i + 128, ..), 64 to each of its two workgroups,
 // and each 32 lanes' sum is a partial: returned by threads tid < 128 for partial 2 * half + tid / 64, channel tid % 64.
+template <int ROWS>
 __device__ __forceinline__ float pool_partial(const FrontLayer& ly, const FrontCommon& a, int h, int half, float* lds) {
   float(*red)[kD + 1] = reinterpret_cast<float(*)[kD + 1]>(lds);
   const int H = a.H, n = a.n, n_s = a.n_special, g = a.pool_size;
@@ -90,15 +92,25 @@ __device__ __forceinline__ float pool_partial(const FrontLayer& ly, const FrontC
   const int last = n_s + (n_groups - 1) * g;  // its first row
   const float w_special = 1.0f / base, w_whole = 1.0f / (base * (float)min(g, n - n_s)), w_last = 1.0f / (base * (float)(n - last));
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll 6
-  for (int r = half * 64 + rl; r < n; r += 128) {
-    const float w = r < n_s ? w_special : (r < last ? w_whole : w_last);
-    const uint4 v = *reinterpret_cast<const uint4*>(qh + (size_t)r * a.q_st);
-    const uint32_t ww[4] = {v.x, v.y, v.z, v.w};
+  // ROWS rows of a row lane are in flight together (rows past the frame: weight 0); with six, 1374 rows take two trips to
+  // memory (an unrolled loop and its rest took two and one for every row of the rest: 4.8 us alone, 4.0 like this)
+  for (int r0 = half * 64 + rl; r0 < n; r0 += 128 * ROWS) {
+    uint4 v[ROWS];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      acc[2 * e] += w * bf16_lo(ww[e]);
-      acc[2 * e + 1] += w * bf16_hi(ww[e]);
+    for (int i = 0; i < ROWS; ++i) {
+      const int r = r0 + 128 * i;
+      v[i] = r < n ? *reinterpret_cast<const uint4*>(qh + (size_t)r * a.q_st) : make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+      const int r = r0 + 128 * i;
+      const float w = r < n_s ? w_special : (r < last ? w_whole : (r < n ? w_last : 0.f));
+      const uint32_t ww[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        acc[2 * e] += w * bf16_lo(ww[e]);
+        acc[2 * e + 1] += w * bf16_hi(ww[e]);
+      }
     }
   }
 #pragma unroll
@@ -114,7 +126,7 @@ __device__ __forceinline__ float pool_partial(const FrontLayer& ly, const FrontC
 }
 template <bool SYNC>
 __device__ __forceinline__ void pool_part(const FrontLayer& ly, const FrontCommon& a, int h, int half, float* lds) {
-  const float s = pool_partial(ly, a, h, half, lds);
+  const float s = pool_partial<6>(ly, a, h, half, lds);
   const int tid = threadIdx.x;
   if (tid < 2 * kD) {
     float* out = ly.qpart + ((size_t)h * kPoolParts + half * 2) * kD + tid;
@@ -143,7 +155,7 @@ __device__ __forceinline__ void pool_alone(const FrontLayer& ly, const FrontComm
   float sum = 0.f;
   for (int h = h0; h < h1; ++h) {
     for (int half = 0; half < 2; ++half) {
-      const float s = pool_partial(ly, a, h, half, lds);
+      const float s = pool_partial<1>(ly, a, h, half, lds);  // (a score workgroup has its registers full of keys)
       if (tid < 2 * kD) parts[half * 2 * kD + tid] = s;
       __syncthreads();
     }
@@ -340,7 +352,7 @@ __device__ __forceinline__ uint32_t wave_prefix(uint32_t x) {
 
 constexpr int kBins = 2048, kBinsT = kBins / kThreads;  // bins, and bins per thread
 constexpr int kSelWaves = kThreads / 64;
-constexpr int kSelLds = kBins + 2 * kSelWaves + 2 + 2 * 64;
+constexpr int kSelLds = kBins + 2 * kSelWaves + 4 + 2 * 64;
 
 // One list.  A wave holds chunks of 64 consecutive scores, one per lane: chunk c belongs to wave c % kSelWaves.  KPT: scores per
 // thread; lists longer than KPT * kThreads are read again in every pass, a segment of so many at a time.
@@ -349,8 +361,8 @@ __device__ __forceinline__ void select_part(const SelectArgs& a, int list, uint3
   static_assert(KPT * kSelWaves <= 128, "two chunks per lane in the prefix sums of the compaction");
   uint32_t* hist = lds;
   uint32_t* wave_tot = hist + kBins;           // [2][kSelWaves]: by the parity of the pass
-  uint32_t* found = wave_tot + 2 * kSelWaves;  // digit, rank inside it
-  uint32_t* counts = found + 2;                // per chunk of a segment: kept | equal << 16
+  uint32_t* found = wave_tot + 2 * kSelWaves;  // digit, rank inside it, keys in it; keys put on the list of candidates
+  uint32_t* counts = found + 4;                // per chunk of a segment: kept | equal << 16
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float* scores = a.scores + (size_t)list * a.scores_stride;
   int32_t* keep = a.keep + (size_t)list * a.keep_stride;
@@ -368,6 +380,7 @@ __device__ __forceinline__ void select_part(const SelectArgs& a, int list, uint3
     }
   };
   load(0);
+  if (tid == 0) found[3] = 0;
   for (int i = tid; i < a.T_first; i += kThreads) keep[i] = i;
   for (int i = tid; i < a.T_cur; i += kThreads) keep[a.T_first + k + i] = a.T_first + P + i;
 
@@ -407,12 +420,36 @@ __device__ __forceinline__ void select_part(const SelectArgs& a, int list, uint3
       if (above < need && need <= above + h[b]) {
         found[0] = kBins - 1 - (tid * kBinsT + b);
         found[1] = need - above;
+        found[2] = h[b];
       }
       above += h[b];
     }
     __syncthreads();
     prefix |= found[0] << shift;
     need = found[1];
+    // What is left of the class, if it is little, is ranked by comparing all with all, instead of further passes: a pass of four
+    // barriers takes about 1.2 us, as long as this with 64 candidates in place of two passes, with 16 in place of one.  (Every wave does
+    // it, so that nobody waits for the result.)  2722 scores of which 1348 are kept,
+    // the kernel by itself: 7.9 and 6.6 us.
+    const uint32_t left = found[2];
+    if (pass < 2 && segments == 1 && left <= (pass == 0 ? 64u : 16u)) {
+#pragma unroll
+      for (int i = 0; i < KPT; ++i)
+        if (at(0, i) < P && (keys[i] & (hi_mask | digits << shift)) == prefix) hist[atomicAdd(&found[3], 1u)] = keys[i];
+      __syncthreads();
+      const uint32_t mine = lane < (int)left ? hist[lane] : 0u;
+      uint32_t gt = 0, ge = 0;
+      for (uint32_t i = 0; i < left; ++i) {
+        const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)i);
+        gt += x > mine;
+        ge += x >= mine;
+      }
+      const unsigned long long hit = __ballot(lane < (int)left && gt < need && need <= ge);
+      const int at_hit = __builtin_ctzll(hit);
+      prefix = (uint32_t)__builtin_amdgcn_readlane((int)mine, at_hit);
+      need -= (uint32_t)__builtin_amdgcn_readlane((int)gt, at_hit);
+      break;
+    }
   }
   const uint32_t thr = prefix;  // key of the k-th largest score; `need` of the scores equal to it are kept (smallest positions)
 

@@ -488,3 +488,25 @@ def test_measured_peaks_are_plausible():
     print(f"measured: MFMA loop {mfma:.0f} TFLOP/s, copy {copy:.0f} GB/s", flush=True)
     assert 800.0 < mfma < 2600.0
     assert 1500.0 < copy < 8200.0
+
+
+@pytest.mark.parametrize("first,second", [(1, 1), (63, 1), (64, 64), (65, 1), (65, 15), (65, 16), (65, 17), (400, 16), (400, 65), (200, 200)])
+@pytest.mark.parametrize("ties", [False, True])
+@pytest.mark.parametrize("P", [900, 4096, 4097, 9000])
+def test_topk_where_the_last_candidates_are_compared_with_each_other(first, second, ties, P):
+    """`first` scores share the threshold's first digit (11 bits), `second` of them its second: the edges at which the passes of the
+    radix select give way to a comparison of all candidates, for lists of one and of several segments and both register counts.  The
+    list is whole numbers: equal to that of a stable sort."""
+    g = torch.Generator().manual_seed(first * 1000 + second)
+    low = (P - first) // 2
+    near = (torch.arange(second) if not ties else torch.randint(0, 3, (second,), generator=g)).float() * 2.0 ** -23    # 22 bits alike
+    rest = torch.linspace(0.01, 0.2, first - second)                                                                # 11 bits alike
+    scores = torch.cat([torch.linspace(0.1, 0.9, low), 1.0 + near, 1.0 + rest, torch.linspace(2.0, 9.0, P - first - low)])
+    scores = scores[torch.randperm(P, generator=g)].contiguous()
+    order = torch.argsort(scores, descending=True, stable=True)
+    above = P - first - low + (first - second)
+    for k in sorted({above + 1, above + (second + 1) // 2, above + second}):
+        want = torch.sort(order[:k]).values + 7
+        keep = xsv.topk_keep(scores.to(DEV), k, 7, 5).cpu().long()
+        assert torch.equal(keep[:7], torch.arange(7)) and torch.equal(keep[7:7 + k], want), (first, second, ties, P, k)
+        assert torch.equal(keep[7 + k:], 7 + P + torch.arange(5))
