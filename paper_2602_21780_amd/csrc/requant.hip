@@ -500,10 +500,12 @@ __global__ __launch_bounds__(256) void requant_kernel(const RequantArgs a) {
 }
 
 // A 16-bit cache: the kept rows copied to their new places.  Thread = (token tid/4 of the block, channel quarter tid%4); a
-// value row is gathered from the transposed blocks and goes through LDS to come out transposed again.
+// value row is gathered from the transposed blocks and goes through LDS to come out transposed again.  In a cache that is never
+// pruned that is the frame's rows and the block they begin in; blocks that an earlier step has flagged are not launched at all
+// (four layers, 16 frames of 16 x 1374 tokens: up to 5504 workgroups of which 352 have something to do took 8.5 us a step, 704 take 5.8).
 __global__ __launch_bounds__(256) void move_kernel(const RequantArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t vt[kD][kTile + 8];  // [channel][token]
-  const int u = blockIdx.x, h = blockIdx.y, lb = blockIdx.z;
+  const int u = blockIdx.x + a.first_block, h = blockIdx.y, lb = blockIdx.z;
   const int tid = threadIdx.x, r = tid >> 2, cq = tid & 3;
   const int Tc = a.Tc, Tn = a.Tn, Tcap = a.pool.Tcap;
   const int layer = a.b.layer0 + lb;
@@ -515,6 +517,10 @@ __global__ __launch_bounds__(256) void move_kernel(const RequantArgs a) {
   const bool candidate = u < a.stable_blocks;  // (a copied block always reproduces itself: the flag is set by its first step)
   uint8_t* const stable = a.stable_flag + ((size_t)layer * a.pool.H + h) * (Tcap / kTile) + u;
   if (candidate && *stable) return;
+  if (candidate && a.pool.buffers == 1) {  // (its rows are where they belong)
+    if (tid == 0) *stable = 1;
+    return;
+  }
   const int pos = u * kTile + r;
   int s_row = -1;
   if (r < nv) s_row = pos < a.identity_end ? pos : (pos >= Tn - a.n ? pos - (Tn - a.n) + Tc : keep[pos]);
@@ -579,7 +585,7 @@ hipError_t launch_zero_bytes(uint8_t* p, size_t n, hipStream_t stream) {
 
 hipError_t launch_requant(const RequantArgs& a, hipStream_t stream) {
   if (a.Tn <= 0) return hipSuccess;
-  const dim3 grid((a.Tn + kTile - 1) / kTile, a.pool.H, a.b.n_layers);
+  const dim3 grid((a.Tn + kTile - 1) / kTile - a.first_block, a.pool.H, a.b.n_layers);
   const int bits = a.pool.bits, G = a.pool.G;
   const bool carry = a.carry_values != 0 && bits != 16;
   if (bits == 16) hipLaunchKernelGGL(move_kernel, grid, dim3(256), 0, stream, a);

@@ -34,6 +34,7 @@ struct LayerState {
   int last_P = 0;       // scores computed by the last score_prune (0 if none)
   int last_keep = 0;
   int last_cut = 0;     // tokens it left out
+  int flagged = 0;      // 16 bits, no budget: leading blocks whose flag is known to be set
 };
 
 }  // namespace
@@ -442,12 +443,17 @@ int do_quantize(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* k, con
     r.stable_blocks = r.identity_end / kTile;
     r.stable_flag = ctx->stable_flag;
     r.carry_values = ctx->cfg.value_mode == 1;
+    if (ctx->cfg.kv_bits == 16 && ctx->pool.buffers == 1) {
+      r.first_block = ctx->layers[layer0].flagged;
+      for (int i = 1; i < n_layers; ++i) r.first_block = std::min(r.first_block, ctx->layers[layer0 + i].flagged);
+    }
   }
   if (launch_requant(r, ctx->work) != hipSuccess) return hip_fail(ctx);
   for (int i = 0; i < n_layers; ++i) {
     LayerState& L = ctx->layers[layer0 + i];
     L.T = r.Tn;
     L.frames += 1;
+    L.flagged = r.stable_blocks;
     if (ctx->pool.buffers == 2) L.buf ^= 1;
     L.phase = kIdle;
   }
@@ -1048,6 +1054,7 @@ int xsv_cache_import(xsv_ctx* ctx, int layer, int32_t T, int32_t frames_seen, co
   if (!good) return hip_fail(ctx);
   L.T = T;
   L.frames = frames_seen;
+  L.flagged = 0;
   L.last_P = 0;
   L.last_keep = 0;
   return XSV_OK;

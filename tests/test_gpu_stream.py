@@ -367,6 +367,30 @@ def test_unpruned_cache_is_rewritten_in_place_and_settles(bits, G):
     ctx.destroy()
 
 
+def test_appended_bf16_cache_goes_on_after_reset_and_import():
+    """A 16-bit cache without a budget leaves out the blocks that earlier steps have flagged.  Reset and import forget them: a context
+    that was used before and then takes over another's cache goes on like that one, byte for byte, one layer or both at a time."""
+    g = torch.Generator().manual_seed(3)
+    frames = [[torch.randn((2, 3, 100, 64), generator=g).to(torch.bfloat16).to(DEV) for _ in range(3)] for _ in range(9)]
+    a, b = (xsv.Context(2, 3, 64, 100, 5, 0, 16, 64, max_frames=9) for _ in range(2))
+    for q, k, v in frames[:4]:
+        a.step_all_layers(q, k, v)
+    for q, k, v in frames[2:7]:
+        for l in range(2):
+            b.step(l, q[l], k[l], v[l])
+    b.reset()
+    for l in range(2):
+        b.cache_import(l, a.cache_export(l), 4)
+    for i, (q, k, v) in enumerate(frames[4:]):
+        step = lambda c: c.step_all_layers(q, k, v) if i % 2 else torch.stack([c.step(l, q[l], k[l], v[l]) for l in range(2)])
+        assert torch.equal(step(a), step(b))
+        for l in range(2):
+            x, y = a.cache_export(l), b.cache_export(l)
+            assert x.T == y.T and all(np.array_equal(getattr(x, f), getattr(y, f)) for f in ("k_bf16", "v_bf16", "token_frame", "token_index"))
+    a.destroy()
+    b.destroy()
+
+
 def test_blocks_settled_while_the_cache_grew_are_not_skipped_once_their_rows_move():
     """While a budgeted cache is still growing no row moves, and old blocks settle as they do without a budget;
     from the first pruning step on only the first frame's blocks keep their place.  The blocks beyond it lose their
