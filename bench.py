@@ -29,9 +29,9 @@ PEAK_HBM_GBS = 8000.0
 # a launch that was counted; "traffic" itself stays null.
 TRAFFIC_PROFILES = [
     {"file": "profiles/attend_cfg2_hbm_traffic.md", "date": "2026-12-03", "workgroups": 240, "merges_inside": False,
-     "fetch_bytes": 13.4e6, "write_bytes": 15.8e6},
+     "fetch_bytes": 14.106e6, "write_bytes": 15.829e6},
     {"file": "profiles/attend_cfg2_hbm_traffic.md", "date": "2026-12-03", "workgroups": 240, "merges_inside": True,
-     "fetch_bytes": 29.874e6, "write_bytes": 18.652e6},
+     "fetch_bytes": 30.080e6, "write_bytes": 18.661e6},
 ]
 
 

@@ -126,7 +126,8 @@ __device__ __forceinline__ float pool_partial(const FrontLayer& ly, const FrontC
 }
 template <bool SYNC>
 __device__ __forceinline__ void pool_part(const FrontLayer& ly, const FrontCommon& a, int h, int half, float* lds) {
-  const float s = pool_partial<6>(ly, a, h, half, lds);
+  // (rows that are not there cost arithmetic all the same: a step of 14 x 58 tokens 24.3 us with six, 23.8 with two)
+  const float s = a.n > 256 ? pool_partial<6>(ly, a, h, half, lds) : pool_partial<2>(ly, a, h, half, lds);
   const int tid = threadIdx.x;
   if (tid < 2 * kD) {
     float* out = ly.qpart + ((size_t)h * kPoolParts + half * 2) * kD + tid;
