@@ -366,7 +366,9 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
     a.xcd_heads = a.xcd_ranges > 0 && a.equal_ranges > 0 && (ctx->cfg.n_heads * n_layers) % 8 == 0;
     if (a.equal_ranges > 0) range_starts(n_ct, n_ft, a.equal_ranges, short_last ? short_pct : 100, ctx->frame_tile_cost, a.range_begin);
   }
-  a.merge_looks = a.equal_ranges > 0 ? kMergeLooks : 0;
+  // (a workgroup that waits for one that has no place yet would only keep it from getting one)
+  const bool all_resident = plan.n_wgs <= (a.variant >= 2 ? 1 : 2) * ctx->n_cu;
+  a.merge_looks = a.equal_ranges > 0 && all_resident ? kMergeLooks : 0;
   ctx->last_attend_wgs = plan.n_wgs;
   ctx->last_attend_merge = a.merge_inside;
   a.qscale = ctx->cfg.softmax_scale * 1.4426950408889634f;

@@ -161,7 +161,8 @@ struct AttendArgs {
   int short_last;   // the last of a unit's equal_ranges was made short (see range_begin)
   // How often a workgroup that merges inside looks for the others of its unit before it leaves them its share (a look takes about
   // 0.7 us; 24 layers with deferred joins at 0 / 4 / 16 / 32 looks: 1340 / 1249 / 1229 / 1228 us).  Only where all units are cut
-  // alike, so that its workgroups end together: a 2-bit stack on a line partition is 1 % slower with it.
+  // alike, so that its workgroups end together - a 2-bit stack on a line partition is 1 % slower with it - and all have a place
+  // at once (cuts of the library's own do; 0 otherwise).
   int merge_looks;
   float qscale;  // softmax scale * log2(e)
 };
