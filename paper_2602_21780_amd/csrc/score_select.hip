@@ -499,6 +499,7 @@ __global__ __launch_bounds__(kThreads) void front_kernel(const FrontArgsT<1> arg
   constexpr int kLds = max_of(max_of(kD + kPoolLds + kPoolParts * kD, score_lds<BITS, G, PER_HEAD>()), kSelLds);
   __shared__ __attribute__((aligned(16))) float lds[kLds];
   __shared__ int last;
+  static_assert(sizeof(lds) > kLdsBesideAttention, "it stays off the compute units of attention's 32-row shapes");
 #if defined(__HIP_DEVICE_COMPILE__)
   {
     // every field of the arguments that is read further down would wait for its own line of them: all lines at once
