@@ -1328,6 +1328,9 @@ int attend_rows_per_workgroup(int variant) {
   return variant == 1 ? 128 : (variant == 3 ? 512 : 256);
 }
 
+// (4 waves x 64 rows with groups of 32 take more than 256 registers: one wave to a SIMD)
+int attend_places_per_cu(int variant, int G) { return variant >= 2 || (variant == 0 && G == 32) ? 1 : 2; }
+
 bool attend_merges_inside(int variant) { return variant != 1; }
 
 AttendPlan plan_attend(int variant, int n_layers, int H, int n, int Tc, int want_wgs, size_t part_rows) {

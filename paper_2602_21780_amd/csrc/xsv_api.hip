@@ -220,12 +220,13 @@ int attend_shape(const xsv_ctx* ctx, int n_layers, int Tc) {
 }
 
 // Workgroups of one attention launch.  requested > 0: every unit is cut into that many equal key
-// ranges.  Otherwise one workgroup per slot of the chip (2 per compute unit for the 4-wave shapes, 1
-// for the 8-wave ones), minus the compute units left to kernels running beside it.
+// ranges.  Otherwise one workgroup per place on the chip, minus the compute units left to kernels running beside it.
+// (us per step of the 4 x 64 shape with groups of 32, two workgroups counted to a compute unit and the one it holds: 8 x 1374 over 4096
+// tokens 66 and 50, 16 x 1041 82 and 65, six layers of 12 x 777 over 3000 297 and 292; in one stream 79 and 60, 87 and 78, 393 and 334.)
 AttendPlan choose_grid(const xsv_ctx* ctx, int variant, int n_layers, int Tc, int requested, int spare_cus) {
   const xsv_config& c = ctx->cfg;
   const int n_units = attend_units(ctx, variant, n_layers);
-  const int per_cu = variant >= 2 ? 1 : 2;
+  const int per_cu = attend_places_per_cu(variant, c.group_size);
   int want = requested > 0 ? n_units * requested : per_cu * std::max(ctx->n_cu / 2, ctx->n_cu - spare_cus);
   // a grid that cuts every unit into the same number of ranges has no workgroup that ends one unit
   // and begins another (two pipeline fills, two sets of partials), and its workgroups share the merge; prefer it when it is nearly
@@ -367,7 +368,7 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
     if (a.equal_ranges > 0) range_starts(n_ct, n_ft, a.equal_ranges, short_last ? short_pct : 100, ctx->frame_tile_cost, a.range_begin);
   }
   // (a workgroup that waits for one that has no place yet would only keep it from getting one)
-  const bool all_resident = plan.n_wgs <= (a.variant >= 2 ? 1 : 2) * ctx->n_cu;
+  const bool all_resident = plan.n_wgs <= attend_places_per_cu(a.variant, a.G) * ctx->n_cu;
   a.merge_looks = a.equal_ranges > 0 && all_resident ? kMergeLooks : 0;
   ctx->last_attend_wgs = plan.n_wgs;
   ctx->last_attend_merge = a.merge_inside;
@@ -868,7 +869,7 @@ static int step_layers(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor*
         const int variant = attend_shape(ctx, n_layers, ctx->layers[layer0].T);
         const long long units = attend_units(ctx, variant, n_layers);
         const long long tiles = (ctx->layers[layer0].T + kTile - 1) / kTile + (c.tokens_per_frame + kTile - 1) / kTile;
-        const int per_cu = variant >= 2 ? 1 : 2;
+        const int per_cu = attend_places_per_cu(variant, c.group_size);
         const long long wgs = (long long)per_cu * (ctx->n_cu - ctx->n_cu / 4);
         spare = units * tiles > 24 * wgs ? ctx->n_cu / 8 : ctx->n_cu / 4;
       }

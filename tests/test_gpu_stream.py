@@ -315,6 +315,25 @@ def test_cuts_of_the_library_are_merged_by_all_workgroups_of_a_unit(H, n, budget
     asked.destroy()
 
 
+@pytest.mark.parametrize("variant,bits,G,places", [(0, 4, 32, 1), (0, 2, 32, 1), (0, 4, 64, 2), (0, 16, 64, 2), (1, 4, 32, 2), (2, 4, 32, 1), (3, 4, 64, 1)])
+def test_grids_of_the_library_have_a_place_for_every_workgroup(variant, bits, G, places):
+    """A compute unit holds two workgroups of the four-wave shapes, but one of 4 x 64 with groups of 32: a grid of the library's own
+    is no larger (its workgroups wait for each other), and nearly as large, in one stream and beside the chain."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    ctx = xsv.Context(1, 8, 64, 1374, 5, 4096, bits, G)
+    ctx.set_attend_variant(variant)
+    g = torch.Generator().manual_seed(variant)
+    q, k, v = (torch.randn((8, 1374, 64), generator=g).to(torch.bfloat16).to(DEV) for _ in range(3))
+    for f in range(5):
+        ctx.set_overlap(f % 2)
+        ctx.step(0, q, k, v)
+    for overlap in (0, 1):
+        ctx.set_overlap(overlap)
+        ctx.step(0, q, k, v)
+        assert places * cus * 2 // 3 <= ctx.last_attend_workgroups() <= places * cus
+    ctx.destroy()
+
+
 @pytest.mark.parametrize("bits", [4, 2, 16])
 def test_long_launches_of_small_blocks_take_the_shape_of_four_waves(bits):
     """150 tokens are one block of 256 rows: 8 waves x 32 rows while 24 layers' units hold fewer than 80 tiles per compute unit, 4
