@@ -34,6 +34,10 @@ int xsv_set_frame_tile_cost(xsv_ctx* ctx, int percent);
 /* Tuning: how often a workgroup of the score launch of a layer looks for the pooled query, which others of the launch are working
  * out, before it pools the queries by itself (0 .. 2^20, default 8192: some milliseconds).  Results are the same bit for bit. */
 int xsv_set_pool_polls(xsv_ctx* ctx, int polls);
+/* Tuning: how often a workgroup of the attention kernel that is done with its piece of a cut (head, query block) looks whether the
+ * others are, to share the merge with them, before it leaves its share to them (0 .. 1024, default 32; a look takes about 0.7 us).
+ * Several streams that use the chip at the same time may gain a few percent with fewer.  Results are the same bit for bit. */
+int xsv_set_merge_looks(xsv_ctx* ctx, int looks);
 /* Measurement aid.  While enabled, every attention launch of this context (xsv_dequant_attend, xsv_step,
  * xsv_step_all_layers) is bracketed by events on the context's stream: before the attention kernel,
  * between it and the kernel that merges key-range partials, after, and once more right behind.

@@ -1173,7 +1173,7 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
     uint32_t* const unit_done = a.unit_done + (size_t)unit * kMeetStride;
     uint32_t acks = 0;
     if (tid == 0) {
-      const Meeting m = meet(unit_done, pieces, a.merge_looks > 0, waits ? a.merge_looks : 0);
+      const Meeting m = meet(unit_done, pieces, a.merge_waits, waits ? a.merge_looks : 0);
       meeting[0] = m.rank;
       meeting[1] = m.sharers;
       // (alone, it need not say that it has looked)

@@ -75,6 +75,7 @@ struct xsv_ctx {
   int short_pct = -1; // xsv_step: length of one extra, short key range per unit, in percent of a long one (0 = none, -1 = default)
   int side_cus = -1;  // compute units xsv_step leaves to the prune chain while attention runs (-1: by launch size)
   int pool_polls = 1 << 13;  // a look takes half a microsecond or more: several times the longest launch it could wait behind
+  int merge_looks = kMergeLooks;
   size_t part_rows = 0;  // rows the partial-output workspace holds
   int n_cu = 256;
   bool broken = false;
@@ -369,7 +370,8 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
   }
   // (a workgroup that waits for one that has no place yet would only keep it from getting one)
   const bool all_resident = plan.n_wgs <= attend_places_per_cu(a.variant, a.G) * ctx->n_cu;
-  a.merge_looks = a.equal_ranges > 0 && all_resident ? kMergeLooks : 0;
+  a.merge_waits = a.equal_ranges > 0 && all_resident;
+  a.merge_looks = ctx->merge_looks;
   ctx->last_attend_wgs = plan.n_wgs;
   ctx->last_attend_merge = a.merge_inside;
   a.qscale = ctx->cfg.softmax_scale * 1.4426950408889634f;
@@ -743,6 +745,12 @@ int xsv_set_side_cus(xsv_ctx* ctx, int compute_units) {
 int xsv_set_pool_polls(xsv_ctx* ctx, int polls) {
   if (!ctx || polls < 0 || polls > (1 << 20)) return XSV_ERR_ARG;
   ctx->pool_polls = polls;
+  return XSV_OK;
+}
+
+int xsv_set_merge_looks(xsv_ctx* ctx, int looks) {
+  if (!ctx || looks < 0 || looks > 1024) return XSV_ERR_ARG;
+  ctx->merge_looks = looks;
   return XSV_OK;
 }
 

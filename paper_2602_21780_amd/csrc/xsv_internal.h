@@ -162,10 +162,13 @@ struct AttendArgs {
   int xcd_ranges;  // > 0: every unit is cut into this many key ranges and the grid is permuted for L2 sharing
   int xcd_heads;   // with xcd_ranges: (layer, head) pairs rather than (layer, head, range) triples are dealt to the XCDs
   int short_last;   // the last of a unit's equal_ranges was made short (see range_begin)
-  // How often a workgroup that merges inside looks for the others of its unit before it leaves them its share (a look takes about
-  // 0.7 us; 24 layers with deferred joins at 0 / 4 / 16 / 32 looks: 1340 / 1249 / 1229 / 1228 us).  Only where all units are cut
-  // alike, so that its workgroups end together - a 2-bit stack on a line partition is 1 % slower with it - and all have a place
-  // at once (cuts of the library's own do; 0 otherwise).
+  // Workgroups that merge inside wait for the others of their unit: only where all units are cut alike, so that its workgroups end
+  // together - a 2-bit stack on a line partition is 1 % slower with it - and no more of them than have a place at once.
+  int merge_waits;
+  // How often such a workgroup looks for the others before it leaves them its share (a look takes about 0.7 us).  Long enough for
+  // those that started late because a chain still held their compute units.  us at 0 / 4 / 8 / 16 / 32 / 64 looks: 24 layers with
+  // deferred joins 1283 / 1238 / 1224 / 1212 / 1214 / 1215, six 2-bit layers of 12 x 777, deferred, 310 / 310 / 308 / 296 / 258 / 253.
+  // Two streams of 16 x 1374 at a time, whose grids do not fit the chip together, would rather not wait: 340 / 350 / 360 / - / 361.
   int merge_looks;
   float qscale;  // softmax scale * log2(e)
 };

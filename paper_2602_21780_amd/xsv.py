@@ -49,7 +49,7 @@ EXPORTS = (
 # every symbol include/xsv_tune.h declares (launch tuning and measurement aids)
 TUNE_EXPORTS = (
     "xsv_set_attend_splits", "xsv_set_attend_variant", "xsv_set_side_cus", "xsv_set_short_range", "xsv_set_frame_tile_cost",
-    "xsv_set_pool_polls",
+    "xsv_set_pool_polls", "xsv_set_merge_looks",
     "xsv_last_attend_workgroups", "xsv_last_attend_merge", "xsv_settled_blocks", "xsv_set_attend_timing", "xsv_attend_times", "xsv_chain_times", "xsv_measure_peaks",
     "xsv_key_ranges", "xsv_line_partition", "xsv_step_plan",
 )
@@ -83,6 +83,7 @@ def lib():
         L.xsv_set_side_cus.argtypes = [vp, i32]
         L.xsv_set_short_range.argtypes = [vp, i32]
         L.xsv_set_pool_polls.argtypes = [vp, i32]
+        L.xsv_set_merge_looks.argtypes = [vp, i32]
         L.xsv_set_frame_tile_cost.argtypes = [vp, i32]
         L.xsv_last_attend_workgroups.argtypes = [vp, C.POINTER(C.c_int32)]
         L.xsv_last_attend_merge.argtypes = [vp, C.POINTER(C.c_int32)]
@@ -239,6 +240,9 @@ class Context:
 
     def set_pool_polls(self, polls):
         _check(lib().xsv_set_pool_polls(self._h, int(polls)), "xsv_set_pool_polls")
+
+    def set_merge_looks(self, looks):
+        _check(lib().xsv_set_merge_looks(self._h, int(looks)), "xsv_set_merge_looks")
 
     def _out(self, q, out):
         if out is None:

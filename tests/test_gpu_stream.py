@@ -315,6 +315,42 @@ def test_cuts_of_the_library_are_merged_by_all_workgroups_of_a_unit(H, n, budget
     asked.destroy()
 
 
+@pytest.mark.parametrize("pieces,H,n,budget,bits,variant", [(3, 3, 130, 700, 4, 3), (5, 16, 1374, 0, 16, 3), (5, 16, 1374, 4096, 4, 3), (8, 4, 500, 1600, 4, 3),
+                                                            (16, 3, 300, 4300, 4, 2), (6, 16, 1041, 4000, 2, 0), (16, 4, 200, 5000, 16, 0)])
+def test_any_number_of_workgroups_may_share_a_merge(pieces, H, n, budget, bits, variant):
+    """Who waits at a unit's counter, and for how long, decides who merges which rows and not what comes out: with no look at all
+    the last workgroup is alone with the merge, with one or two some leave and the others take new numbers, with very many all
+    stay (but a range that was made short, with deferred joins).  The same bits from all of them, over launches that use the
+    same counters one after the other, in one stream (frames by themselves and steps) and beside the chain."""
+    print(f"looks {pieces} {H} {n} {bits} {variant}", flush=True)
+    looks = (0, 1, 2, 32, 1024)
+    ctxs = [xsv.Context(1, H, 64, n, 5, budget, bits, 64, max_frames=8) for _ in looks]
+    for ctx, x in zip(ctxs, looks):
+        ctx.set_attend_variant(variant)
+        ctx.set_merge_looks(x)
+    units = H * -(-n // (256, 128, 256, 512)[variant])
+    g = torch.Generator().manual_seed(n)
+    seen = set()
+    for f in range(-(-budget // n) + 6 if budget else 4):
+        q, k, v = (torch.randn((H, n, 64), generator=g).to(torch.bfloat16).to(DEV) for _ in range(3))
+        q[1, n - 1] = float("nan") if f % 2 else 1.0
+        runs = [lambda c: c.step(0, q, k, v)] + [lambda c: c.frame_attend(q, k, v)] * 3
+        for run in runs:
+            outs = []
+            for ctx in ctxs:
+                ctx.set_overlap(f % 3)
+                outs.append(run(ctx))
+                if ctx.last_attend_merges_inside():
+                    seen.add(ctx.last_attend_workgroups() / units)
+            ctxs[0].join()
+            torch.cuda.synchronize()
+            for out in outs[1:]:
+                assert torch.equal(outs[0].view(torch.int16), out.view(torch.int16))
+    assert pieces in seen, seen
+    for ctx in ctxs:
+        ctx.destroy()
+
+
 @pytest.mark.parametrize("variant,bits,G,places", [(0, 4, 32, 1), (0, 2, 32, 1), (0, 4, 64, 2), (0, 16, 64, 2), (1, 4, 32, 2), (2, 4, 32, 1), (3, 4, 64, 1)])
 def test_grids_of_the_library_have_a_place_for_every_workgroup(variant, bits, G, places):
     """A compute unit holds two workgroups of the four-wave shapes, but one of 4 x 64 with groups of 32: a grid of the library's own
