@@ -429,11 +429,11 @@ __device__ __forceinline__ void select_part(const SelectArgs& a, int list, uint3
     prefix |= found[0] << shift;
     need = found[1];
     // What is left of the class, if it is little, is ranked by comparing all with all, instead of further passes: a pass of four
-    // barriers takes about 1.2 us, as long as this with 64 candidates in place of two passes, with 16 in place of one.  (Every wave does
-    // it, so that nobody waits for the result.)  2722 scores of which 1348 are kept,
-    // the kernel by itself: 7.9 and 6.6 us.
+    // barriers takes about 0.65 us, a candidate 0.04.  (Every wave does it, so that nobody waits for the result.)  2722 scores
+    // around zero of which 1348 are kept, 9 candidates, the kernel by itself: 7.9 and 6.6 us; around a third of their spread, 56
+    // candidates, 6.7 with passes and 7.7 by comparing.
     const uint32_t left = found[2];
-    if (pass < 2 && segments == 1 && left <= (pass == 0 ? 64u : 16u)) {
+    if (pass < 2 && segments == 1 && left <= (pass == 0 ? 32u : 16u)) {
 #pragma unroll
       for (int i = 0; i < KPT; ++i)
         if (at(0, i) < P && (keys[i] & (hi_mask | digits << shift)) == prefix) hist[atomicAdd(&found[3], 1u)] = keys[i];

@@ -490,7 +490,7 @@ def test_measured_peaks_are_plausible():
     assert 1500.0 < copy < 8200.0
 
 
-@pytest.mark.parametrize("first,second", [(1, 1), (63, 1), (64, 64), (65, 1), (65, 15), (65, 16), (65, 17), (400, 16), (400, 65), (200, 200)])
+@pytest.mark.parametrize("first,second", [(1, 1), (63, 1), (64, 64), (65, 1), (65, 15), (65, 16), (65, 17), (31, 31), (32, 1), (32, 32), (33, 1), (33, 16), (33, 17), (400, 16), (400, 65), (200, 200)])
 @pytest.mark.parametrize("ties", [False, True])
 @pytest.mark.parametrize("P", [900, 4096, 4097, 9000])
 def test_topk_where_the_last_candidates_are_compared_with_each_other(first, second, ties, P):
