@@ -206,18 +206,31 @@ int attend_units(const xsv_ctx* ctx, int variant, int n_layers) {
 // Workgroup shape of an attention launch.  8 waves x 64 query rows, unless blocks of 256 rows leave fewer padding rows in a frame's
 // last block (1041 tokens: 1280 against 1536 rows).  Of the two shapes of 256 rows, 8 waves x 32 have a compute unit to themselves
 // and read every key and value for 32 rows; 4 waves x 64 read them for 64 and share the compute unit with a second workgroup,
-// which is faster in the loop and slower in everything around it: for launches of 40 tiles and more per compute unit, 80 where
-// the layers' units follow each other on a line.  us per step, 8 x 32 and 4 x 64, 2 bits: one layer of 16 x 1041 and 4096 / 6000 /
-// 8192 / 10000 tokens (26 / 35 / 46 / 54 tiles) 66 and 69, 84 and 86, 98 and 91, 116 and 108; of 16 x 1270 / 9500 (46) 107 and
-// 101; several layers at a time, 2 of 16 x 1041 / 8192 (92) 169 and 152, 24 (1100) 1671 and 1348, 24 of 16 x 600 / 2400 (216) 350
-// and 305, but 6 of 16 x 600 / 3000 (64) 138 and 145.
-int attend_shape(const xsv_ctx* ctx, int n_layers, int Tc) {
+// which is faster in the loop and slower in everything around it, and leaves a chain beside it nothing of its compute units.  So the
+// latter for long launches only, by key tiles per compute unit.  us per step, 8 x 32 and 4 x 64, one layer of
+//   - 16 x 1041 over 4096 / 7200 / 9200 / 12000 tokens (25 / 41 / 50 / 64 tiles), 4 bits: 55 and 58, 76 and 75, 90 and 87, 113 and 106; 2 bits
+//     over 4096 / 6000 / 8192 / 10000: 66 and 69, 84 and 86, 98 and 91, 116 and 108.  From 40 on.
+//   - 24 x 600 over 10000 / 12500 / 16000 (47 / 58 / 73), 4 bits: 1.06, 0.99, 0.99 of the time; 14 x 600 / 16000 (43) 1.07, 16 x 750 / 16000
+//     (49) 1.06.  The chain's work grows with heads and cache, attention's with the blocks of a frame too: with few blocks from 56 on.
+//   - 12 x 1200 over 10000 / 16000 (41 / 63), 16 bits: 81 and 92, 1.08 of the time, 16 x 1041 over 8192 / 10000 0.97 and 1.01: a chain that
+//     moves 16-bit rows ends last.  Not beside one; with nothing beside it 4 x 64 takes 0.79 to 0.95 of attention's time (15 to 83 tiles).
+// Several layers at a time: from 80 on, and if the workspace has room to cut their units for all places (two pieces of every
+// row from eight layers on).  2 of 16 x 1041 / 8192 (91) 147 and 133 with 4 bits, 134 and 119 with 16, 24 of 16 x 600 / 2400 (216) 319 and
+// 303, 2 bits 350 and 305; 6 of 16 x 600 / 4200, 288 units that stay whole, 143 and 157.
+int attend_shape(const xsv_ctx* ctx, int n_layers, int Tc, bool beside) {
   if (ctx->attend_variant >= 0) return ctx->attend_variant;
-  const int n = ctx->cfg.tokens_per_frame;
+  const xsv_config& c = ctx->cfg;
+  const int n = c.tokens_per_frame;
   if (round_up(n, 256) >= round_up(n, 512)) return 3;
-  if (ctx->cfg.group_size != 64) return 2;  // (4 x 64 takes more registers there than two workgroups of a compute unit have)
+  if (c.group_size != 64) return 2;  // (4 x 64 takes more registers there than two workgroups of a compute unit have)
+  if (n_layers == 1 && beside && c.kv_bits == 16) return 2;
+  const int least = n_layers > 1 ? 80 : (beside && n <= 4 * 256 ? 56 : 40);
   const long long tiles = (Tc + kTile - 1) / kTile + (n + kTile - 1) / kTile;
-  return attend_units(ctx, 2, n_layers) * tiles >= (n_layers > 1 ? 80 : 40) * (long long)ctx->n_cu ? 0 : 2;
+  const int units = attend_units(ctx, 0, n_layers);
+  if (units * tiles < least * (long long)ctx->n_cu) return 2;
+  const int want = 2 * (ctx->n_cu - ctx->n_cu / 8);
+  if (n_layers > 1 && units < want && 8 * plan_attend(0, n_layers, c.n_heads, n, Tc, want, ctx->part_rows).n_wgs < 7 * want) return 2;
+  return 0;
 }
 
 // Workgroups of one attention launch.  requested > 0: every unit is cut into that many equal key
@@ -325,7 +338,7 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
   }
   a.Tc = frame_only ? 0 : ctx->layers[layer0].T;
   a.n = ctx->cfg.tokens_per_frame;
-  a.variant = attend_shape(ctx, n_layers, a.Tc);
+  a.variant = attend_shape(ctx, n_layers, a.Tc, beside_chain || spare_cus > 0);
   AttendPlan plan = choose_grid(ctx, a.variant, n_layers, a.Tc, splits_req, spare_cus);
   const int n_ct = (a.Tc + kTile - 1) / kTile, n_ft = (a.n + kTile - 1) / kTile, n_tiles = n_ct + n_ft;
   bool short_last = false;
@@ -874,7 +887,7 @@ static int step_layers(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor*
       int spare = ctx->side_cus;
       if (spare < 0) {
         const xsv_config& c = ctx->cfg;
-        const int variant = attend_shape(ctx, n_layers, ctx->layers[layer0].T);
+        const int variant = attend_shape(ctx, n_layers, ctx->layers[layer0].T, true);
         const long long units = attend_units(ctx, variant, n_layers);
         const long long tiles = (ctx->layers[layer0].T + kTile - 1) / kTile + (c.tokens_per_frame + kTile - 1) / kTile;
         const int per_cu = attend_places_per_cu(variant, c.group_size);

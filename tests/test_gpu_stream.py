@@ -389,6 +389,35 @@ def test_long_launches_of_small_blocks_take_the_shape_of_four_waves(bits):
         c.destroy()
 
 
+@pytest.mark.parametrize("layers,H,n,budget,bits,overlap,four_waves", [
+    (1, 16, 1041, 7400, 4, 1, True), (1, 16, 1041, 6600, 4, 1, False), (1, 16, 1041, 7400, 16, 1, False), (1, 16, 1041, 7400, 16, 0, True),
+    (1, 24, 600, 10000, 4, 1, False), (1, 24, 600, 12300, 2, 2, True), (1, 24, 600, 10000, 4, 0, True), (6, 16, 600, 4200, 4, 1, False),
+    (8, 16, 600, 4200, 4, 1, True), (1, 12, 600, 21000, 16, 0, True)])
+def test_the_shape_of_four_waves_is_taken_by_length_and_room(layers, H, n, budget, bits, overlap, four_waves):
+    """Which of the two shapes of 256 rows a launch takes (told by its grid), at either side of the rules' edges: key tiles per compute unit,
+    a chain of 16-bit rows beside it, few blocks of query rows, several layers whose units the workspace has no room to cut.  And the
+    outputs of either, head by head, within the rounding of probabilities and outputs to bf16 and of partials to fp16."""
+    ctxs = [xsv.Context(layers, H, 64, n, 5, budget, bits, 64) for _ in range(3)]
+    for ctx, variant in zip(ctxs[1:], (2, 0)):
+        ctx.set_attend_variant(variant)
+    for ctx in ctxs:
+        ctx.set_overlap(overlap)
+    g = torch.Generator(device=DEV).manual_seed(n)
+    for f in range(-(-budget // n) + 1):
+        q, k, v = (torch.randn((layers, H, n, 64), generator=g, device=DEV).to(torch.bfloat16) for _ in range(3))
+        outs = [(c.step_all_layers(q, k, v) if layers > 1 else c.step(0, q[0], k[0], v[0])).float() for c in ctxs]
+        ctxs[0].join()
+        for ctx in ctxs[1:]:
+            ctx.join()
+        for out in outs[1:]:
+            assert ((outs[0] - out).norm(dim=(-2, -1)) <= 1e-2 * out.norm(dim=(-2, -1))).all()
+    own, eight, four = (c.last_attend_workgroups() for c in ctxs)
+    assert eight != four and own == (four if four_waves else eight)
+    assert torch.equal(outs[0], outs[2 if four_waves else 1])
+    for ctx in ctxs:
+        ctx.destroy()
+
+
 def test_budget_below_two_frames_keeps_first_and_current():
     spec = CONFIGS[0].with_(name="k0", budget=100)
     run_stream(spec, 4)
