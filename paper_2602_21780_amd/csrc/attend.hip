@@ -1277,10 +1277,13 @@ static hipError_t launch_attend_t(const AttendArgs& a, hipStream_t stream, hipEv
   // that works on both ends last: the launch keeps the LDS that front_kernel would need.  us per step with and without front_kernel
   // on its compute units, 4 bits, 8 x 32: one layer of 16 x 1041 over 4096 tokens 60.4 and 55.1, 10 x 1188 / 4956 57.3 and 52.7, six
   // layers of 16 x 600 / 3000 joined by every step 280 and 248, two such streams at a time 382 and 335.
+  // Not with a short range, whose grid leaves so few compute units at first that the chain needs these too (deferred joins, 8 x 600 over
+  // 16000 tokens 92 and 102, 16 x 200 / 24000 137 and 158), and not for 16 bits: front_kernel has 115 registers there and finds no
+  // place anyway, move_kernel has 9 KB of LDS and should find more than one (10 x 1200 / 8000 56 and 60).
   // (Launches of several layers have the chain's parts beside them one by one, which share as they always did.)
-  constexpr int kStatic = 4 * kLdsTile * (int)sizeof(uint16_t) + (BITS == 16 ? 0 : 8 * Stage<BITS, G, NW * 32>::kPrm * (int)sizeof(float));
-  constexpr int kKeep = QB == 1 ? (kLdsOfComputeUnit - kLdsBesideAttention) / (NW == 8 ? 1 : 2) - kStatic : 0;
-  const int keep = a.n_layers == 1 ? kKeep : 0;
+  constexpr int kStatic = 4 * kLdsTile * (int)sizeof(uint16_t) + 8 * Stage<BITS, G, NW * 32>::kPrm * (int)sizeof(float);
+  constexpr int kKeep = QB == 1 && BITS != 16 ? (kLdsOfComputeUnit - kLdsBesideAttention) / (NW == 8 ? 1 : 2) - kStatic : 0;
+  const int keep = a.n_layers == 1 && !a.short_last ? kKeep : 0;
   auto launch = [&](auto one_layer, auto inside) {
     hipLaunchKernelGGL((attend_kernel<BITS, G, NW, QB, decltype(one_layer)::value, decltype(inside)::value>), dim3(a.n_wgs), dim3(NW * 64), keep, stream, a);
   };

@@ -113,8 +113,8 @@ constexpr int kMaxPieces = 16;  // workgroups that may share one unit
 // Words between the counters of two units: many workgroups look at them at the same time, and side by side in a few lines they
 // held up each other and the partials' stores (24 layers with deferred joins: 1406 us, 1214 apart).
 constexpr int kMeetStride = 64;
-// LDS of a compute unit, and what one-layer attention launches whose waves hold 32 query rows leave of it: too little for front_kernel
-// (a static_assert there), enough for three workgroups of requant_kernel.
+// LDS of a compute unit, and what attention launches that want none of front_kernel's workgroups beside them leave of it (launch_attend_t):
+// too little for one (a static_assert there), enough for three of requant_kernel.
 constexpr int kLdsOfComputeUnit = 160 * 1024, kLdsBesideAttention = 16 * 1024;
 constexpr int kMergeInside = 5;  // see AttendArgs::merge_inside
 constexpr int kMergeLooks = 32;  // see AttendArgs::merge_looks
