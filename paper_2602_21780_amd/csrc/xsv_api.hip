@@ -212,8 +212,11 @@ int attend_units(const xsv_ctx* ctx, int variant, int n_layers) {
 //     over 4096 / 6000 / 8192 / 10000: 66 and 69, 84 and 86, 98 and 91, 116 and 108.  From 40 on.
 //   - 24 x 600 over 10000 / 12500 / 16000 (47 / 58 / 73), 4 bits: 1.06, 0.99, 0.99 of the time; 14 x 600 / 16000 (43) 1.07, 16 x 750 / 16000
 //     (49) 1.06.  The chain's work grows with heads and cache, attention's with the blocks of a frame too: with few blocks from 56 on.
-//   - 12 x 1200 over 10000 / 16000 (41 / 63), 16 bits: 81 and 92, 1.08 of the time, 16 x 1041 over 8192 / 10000 0.97 and 1.01: a chain that
-//     moves 16-bit rows ends last.  Not beside one; with nothing beside it 4 x 64 takes 0.79 to 0.95 of attention's time (15 to 83 tiles).
+//   - 12 x 1200 over 10000 / 16000 (41 / 63), 16 bits: 81 and 92, 110 and 119: a chain that moves 16-bit rows ends last if attention
+//     leaves it few places or writes many pieces of every row.  24 x 1041 over 8000 / 12000, three pieces, 0.93 and 1.00 of the time,
+//     20 x 1200, four equal ones, 0.95 and 0.98, 16 x 1041, five that leave a fifth of the places, 0.95 and 1.01; 17 x 1041, five that
+//     do not, 0.97 and 1.09, 18 x 1041, more than four on a line, 0.99 and 1.11.  Few blocks: 1.05 and more at any number of heads.
+//     (With nothing beside it 4 x 64 takes 0.79 to 0.95 of attention's time, 15 to 83 tiles.)
 // Several layers at a time: from 80 on, and if the workspace has room to cut their units for all places (two pieces of every
 // row from eight layers on).  2 of 16 x 1041 / 8192 (91) 147 and 133 with 4 bits, 134 and 119 with 16, 24 of 16 x 600 / 2400 (216) 319 and
 // 303, 2 bits 350 and 305; 6 of 16 x 600 / 4200, 288 units that stay whole, 143 and 157.
@@ -223,12 +226,17 @@ int attend_shape(const xsv_ctx* ctx, int n_layers, int Tc, bool beside) {
   const int n = c.tokens_per_frame;
   if (round_up(n, 256) >= round_up(n, 512)) return 3;
   if (c.group_size != 64) return 2;  // (4 x 64 takes more registers there than two workgroups of a compute unit have)
-  if (n_layers == 1 && beside && c.kv_bits == 16) return 2;
-  const int least = n_layers > 1 ? 80 : (beside && n <= 4 * 256 ? 56 : 40);
+  const bool few_blocks = n <= 4 * 256;
+  const int least = n_layers > 1 ? 80 : (beside && few_blocks ? 56 : 40);
   const long long tiles = (Tc + kTile - 1) / kTile + (n + kTile - 1) / kTile;
   const int units = attend_units(ctx, 0, n_layers);
   if (units * tiles < least * (long long)ctx->n_cu) return 2;
-  const int want = 2 * (ctx->n_cu - ctx->n_cu / 8);
+  const int places = 2 * ctx->n_cu, want = places - places / 8;
+  if (n_layers == 1 && beside && c.kv_bits == 16) {
+    const int ranges = want / units, grid = ranges * units;
+    const bool equal = 8 * grid >= 7 * want;  // (see choose_grid)
+    if (few_blocks || ranges > 5 || (ranges > 3 && !equal) || (ranges == 5 && 5 * grid > 4 * places)) return 2;
+  }
   if (n_layers > 1 && units < want && 8 * plan_attend(0, n_layers, c.n_heads, n, Tc, want, ctx->part_rows).n_wgs < 7 * want) return 2;
   return 0;
 }

@@ -390,7 +390,7 @@ def test_long_launches_of_small_blocks_take_the_shape_of_four_waves(bits):
 
 
 @pytest.mark.parametrize("layers,H,n,budget,bits,overlap,four_waves", [
-    (1, 16, 1041, 7400, 4, 1, True), (1, 16, 1041, 6600, 4, 1, False), (1, 16, 1041, 7400, 16, 1, False), (1, 16, 1041, 7400, 16, 0, True),
+    (1, 16, 1041, 7400, 4, 1, True), (1, 16, 1041, 6600, 4, 1, False), (1, 16, 1041, 7400, 16, 1, True), (1, 14, 1041, 9000, 16, 1, False), (1, 14, 1041, 9000, 16, 0, True),
     (1, 24, 600, 10000, 4, 1, False), (1, 24, 600, 12300, 2, 2, True), (1, 24, 600, 10000, 4, 0, True), (6, 16, 600, 4200, 4, 1, False),
     (8, 16, 600, 4200, 4, 1, True), (1, 12, 600, 21000, 16, 0, True)])
 def test_the_shape_of_four_waves_is_taken_by_length_and_room(layers, H, n, budget, bits, overlap, four_waves):
