@@ -25,7 +25,7 @@ int xsv_set_attend_splits(xsv_ctx* ctx, int per_layer_calls, int batched_calls);
 int xsv_set_side_cus(xsv_ctx* ctx, int compute_units);
 /* Tuning: in xsv_step / xsv_step_all_layers with overlap, cut every (head, query block) into one more key
  * range than the spare units allow, the extra one `percent` of a full range long (1..100; 0 = off; -1 = default: 35 where
- * joins are deferred and ranges are long, else 0): its workgroups end early and hand their compute units to the chain for the rest of the attention launch. */
+ * joins are deferred, ranges are long and a workgroup has its compute unit to itself, else 0): its workgroups end early and hand their compute units to the chain for the rest of the attention launch. */
 int xsv_set_short_range(xsv_ctx* ctx, int percent);
 /* Tuning: what a key tile of the frame's own bf16 rows costs the attention kernel relative to a tile of the packed
  * cache, in percent (25..400, default 95: bf16 rows need no dequantization).  When every (head, query block) is cut into the same key ranges, the
@@ -59,7 +59,7 @@ int xsv_last_attend_workgroups(xsv_ctx* ctx, int32_t* workgroups);
  * or nothing was cut. */
 int xsv_last_attend_merge(xsv_ctx* ctx, int32_t* inside);
 /* Tuning: workgroup shape of the attention kernel (waves x query rows per wave).  3 = 8 x 64, 0 = 4 x 64,
- * 1 = 4 x 32, 2 = 8 x 32.  Default: 3, or where blocks of 256 rows pad a frame's tokens less than blocks
+ * 1 = 4 x 32, 2 = 8 x 32, -1 (default) = by the launch: 3, or where blocks of 256 rows pad a frame's tokens less than blocks
  * of 512 (e.g. 1041 tokens) 2 for short launches and 0 for long ones.  Other values: XSV_ERR_ARG.  Results agree to rounding. */
 int xsv_set_attend_variant(xsv_ctx* ctx, int variant);
 

@@ -354,14 +354,17 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
   // their compute units are missing in some shader engines altogether, and the chain hardly starts.  24 layers of 16 x 1374
   // tokens, us per frame at 0 / 20 / 35 / 50 %: deferred joins 1262 / 1244 / 1227 / 1240, joined by every step 1522 / 1621 / 1611 /
   // 1620; of 16 x 700, long ranges of 12 tiles, 913 / 911 / 954 / 1220 deferred and 1212 / 1251 / 1313 / 1391 joined; six 2-bit layers
-  // of 12 x 777, 7 tiles, deferred 267 / 316 / 292.)
+  // of 12 x 777, 7 tiles, deferred 267 / 316 / 292.)  Where two workgroups share a compute unit one is rarely free of both: eight layers of
+  // 16 x 1041 over 8192, 4 x 64, deferred, 4 bits 556 / 555 / 561 / 571, 2 bits 713 / 805 / 778 / 747; such shapes only when asked.
   const int short_pct = ctx->short_pct >= 0 ? ctx->short_pct : (ctx->overlap == 2 ? 35 : 0);
   if (splits_req <= 0 && spare_cus > 0 && short_pct > 0) {
     // beside the overlapped chain: the equal cut that leaves spare units, plus one short range per unit
     const int n_units = attend_units(ctx, a.variant, n_layers);
     const int S = plan.n_wgs % n_units == 0 ? plan.n_wgs / n_units : 0;
     const bool outlasts = 100 * n_tiles >= kLongRange * (100 * S + short_pct);
-    if (S >= 1 && (S + 1) * n_units <= ctx->n_cu - 8 && S + 1 <= kMaxPieces && S + 1 <= n_tiles && (ctx->short_pct >= 0 || outlasts)) {
+    const int per_cu = attend_places_per_cu(a.variant, a.G);
+    if (S >= 1 && (S + 1) * n_units <= per_cu * (ctx->n_cu - 8) && S + 1 <= kMaxPieces && S + 1 <= n_tiles &&
+        (ctx->short_pct >= 0 || (outlasts && per_cu == 1))) {
       const AttendPlan more = plan_attend(a.variant, n_layers, ctx->cfg.n_heads, a.n, a.Tc, (S + 1) * n_units, ctx->part_rows);
       if (more.n_wgs == (S + 1) * n_units) {
         plan = more;
@@ -812,7 +815,7 @@ int xsv_line_partition(int64_t units, int tiles, int workgroups, int workgroup, 
 }
 
 int xsv_set_attend_variant(xsv_ctx* ctx, int variant) {
-  if (!ctx || variant < 0 || variant > 3) return XSV_ERR_ARG;
+  if (!ctx || variant < -1 || variant > 3) return XSV_ERR_ARG;
   ctx->attend_variant = variant;
   return XSV_OK;
 }

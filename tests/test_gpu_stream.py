@@ -418,6 +418,35 @@ def test_the_shape_of_four_waves_is_taken_by_length_and_room(layers, H, n, budge
         ctx.destroy()
 
 
+def test_short_range_and_automatic_shape_can_be_asked_for():
+    """A short range is left out where two workgroups share a compute unit, unless asked for; a shape once set can be given back."""
+    ctx = xsv.Context(1, 16, 64, 1041, 5, 7400, 4, 64)
+    ctx.set_overlap(2)
+    q, k, v = (torch.randn((16, 1041, 64), device=DEV).to(torch.bfloat16) for _ in range(3))
+
+    def grid():
+        ctx.step(0, q, k, v)
+        ctx.join()
+        return ctx.last_attend_workgroups()
+
+    for _ in range(9):
+        own = grid()
+    ctx.set_attend_variant(0)
+    assert grid() == own == 5 * 80                 # five ranges of each of 16 x 5 blocks
+    ctx.set_short_range(35)
+    assert grid() == 6 * 80
+    ctx.set_attend_variant(2)
+    eight = grid()
+    ctx.set_short_range(-1)
+    assert grid() == eight != own
+    ctx.set_attend_variant(-1)
+    assert grid() == own
+    for bad in (-2, 4):
+        with pytest.raises(xsv.XsvError):
+            ctx.set_attend_variant(bad)
+    ctx.destroy()
+
+
 def test_budget_below_two_frames_keeps_first_and_current():
     spec = CONFIGS[0].with_(name="k0", budget=100)
     run_stream(spec, 4)
