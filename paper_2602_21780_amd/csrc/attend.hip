@@ -1182,11 +1182,17 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
     __syncthreads();
     const int rank = __builtin_amdgcn_readfirstlane(meeting[0]), sharers = __builtin_amdgcn_readfirstlane(meeting[1]);
     if (sharers > 0) {
-      // (parts so small that a sharer's eight waves have an item each, and no smaller)
+      // (parts so small that most waves of a sharer have an item, and no smaller; several layers never have more than kMergeInside
+      // pieces here)
       using std::integral_constant;
-      if (pieces <= (sharers == 1 ? 5 : 3)) merge(integral_constant<int, 1>{}, integral_constant<int, 5>{}, pieces, rank, sharers);
-      else if (pieces <= 8) merge(integral_constant<int, 2>{}, integral_constant<int, 8>{}, pieces, rank, sharers);
-      else merge(integral_constant<int, 4>{}, integral_constant<int, kMaxPieces>{}, pieces, rank, sharers);
+      if (pieces <= (sharers == 1 ? kMergeInside : 3)) {
+        merge(integral_constant<int, 1>{}, integral_constant<int, kMergeInside>{}, pieces, rank, sharers);
+      } else if constexpr (ONE_LAYER) {
+        if (pieces <= 8) merge(integral_constant<int, 2>{}, integral_constant<int, 8>{}, pieces, rank, sharers);
+        else merge(integral_constant<int, 4>{}, integral_constant<int, kMaxPieces>{}, pieces, rank, sharers);
+      } else {
+        merge(integral_constant<int, 2>{}, integral_constant<int, kMergeInside>{}, pieces, rank, sharers);
+      }
       // everybody who will look at the counter has looked: as the next launch wants it
       if (tid == 0 && (acks / kMeetAck) % 32u == (uint32_t)sharers - 1u) __hip_atomic_store(unit_done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -1289,8 +1295,12 @@ static hipError_t launch_attend_t(const AttendArgs& a, hipStream_t stream, hipEv
   };
   using std::true_type;
   using std::false_type;
-  if constexpr (NW == 8 || QB == 2) {  // (attend_merges_inside: nobody sets merge_inside for the other shape)
-    if (a.merge_inside) a.n_layers == 1 ? launch(true_type{}, true_type{}) : launch(false_type{}, true_type{});
+  if (a.merge_inside) {  // (attend_merges_inside)
+    if (a.n_layers == 1) {
+      if constexpr (NW == 8 || QB == 2) launch(true_type{}, true_type{});
+    } else {
+      if constexpr (NW == 8) launch(false_type{}, true_type{});
+    }
   }
   if (!a.merge_inside) a.n_layers == 1 ? launch(true_type{}, false_type{}) : launch(false_type{}, false_type{});
   hipError_t e = hipGetLastError();
@@ -1334,7 +1344,7 @@ int attend_rows_per_workgroup(int variant) {
 // (4 waves x 64 rows with groups of 32 take more than 256 registers: one wave to a SIMD)
 int attend_places_per_cu(int variant, int G) { return variant >= 2 || (variant == 0 && G == 32) ? 1 : 2; }
 
-bool attend_merges_inside(int variant) { return variant != 1; }
+bool attend_merges_inside(int variant, int n_layers) { return variant >= 2 || (variant == 0 && n_layers == 1); }
 
 AttendPlan plan_attend(int variant, int n_layers, int H, int n, int Tc, int want_wgs, size_t part_rows) {
   const int rows_wg = attend_rows_per_workgroup(variant);

@@ -378,7 +378,7 @@ int do_attend(xsv_ctx* ctx, int layer0, int n_layers, const xsv_tensor* q, const
   const bool own_cut = splits_req <= 0 && n_layers == 1 && plan.n_wgs % attend_units(ctx, a.variant, 1) == 0 && plan.max_pieces > 2;
   // (the merge finds all pieces with 32-bit offsets)
   const unsigned long long partial_bytes = 4096ull * plan.max_pieces * n_layers * ctx->cfg.n_heads * ((a.n + 31) / 32);
-  a.merge_inside = a.cut && attend_merges_inside(a.variant) && partial_bytes < (1ull << 31) &&
+  a.merge_inside = a.cut && attend_merges_inside(a.variant, n_layers) && partial_bytes < (1ull << 31) &&
                    (own_cut || (beside_chain && a.variant >= 2 && plan.max_pieces <= kMergeInside));
   a.short_last = short_last;
   {

@@ -184,7 +184,7 @@ void partition_unit_query(long long n_units, int n_tiles, int n_wgs, int unit, i
 hipError_t launch_attend(const AttendArgs& a, hipStream_t stream, hipEvent_t between = nullptr);
 int attend_rows_per_workgroup(int variant);
 int attend_places_per_cu(int variant, int G);  // workgroups that a compute unit holds at once
-bool attend_merges_inside(int variant);  // the shape has kernels that can (see AttendArgs::merge_inside)
+bool attend_merges_inside(int variant, int n_layers);  // the shape has kernels that can (see AttendArgs::merge_inside)
 
 // Pool, score and select (score_select.hip).  One layer: device pointers, resolved on the host.
 struct FrontLayer {
