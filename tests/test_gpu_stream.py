@@ -256,18 +256,19 @@ def run_merge_forms(layers, H, n, budget, bits, G, variant, splits):
 @pytest.mark.parametrize("bits,G", [(4, 64), (4, 32), (2, 64), (2, 32), (16, 64)])
 @pytest.mark.parametrize("variant", [2, 3])
 @pytest.mark.parametrize("layers,H,splits,n,budget", [(1, 3, 2, 600, 1900), (1, 3, 3, 257, 2000), (1, 3, 4, 300, 1300), (1, 3, 5, 600, 1900),
-                                                      (1, 3, 16, 130, 700), (3, 4, 2, 257, 2000), (3, 4, 0, 600, 1900)])
-def test_units_merged_by_their_last_workgroup_equal_the_second_launch(layers, H, splits, n, budget, variant, bits, G):
-    """With the chain beside attention the last workgroup of a cut unit merges it, without it a launch of its own does: the same
-    bits from every kernel that merges inside, over steps that reuse the counters, for two to five equal ranges, for one layer and
-    several, for rows that are NaN and go through the tiles twice, and (16 pieces asked of a short unit; several layers whose
-    partials have room for five) for workgroups that end one unit and begin the next."""
+                                                      (1, 3, 16, 130, 700), (3, 4, 2, 257, 2000), (3, 4, 0, 600, 1900), (1, 30, 5, 520, 1700)])
+def test_units_merged_inside_equal_the_second_launch(layers, H, splits, n, budget, variant, bits, G):
+    """With the chain beside attention the workgroups of a cut unit merge it, without it (a cut that was asked for) a launch of its own
+    does: the same bits from the 8-wave kernels that merge inside, over steps that reuse the counters.  Two to five equal ranges, whose
+    workgroups share the merge; 30 heads in five ranges, more workgroups than places, and (16 pieces asked of a short unit; several
+    layers whose partials have room for five) workgroups that end one unit and begin the next: there the last one merges alone.
+    One layer and several; rows that are NaN and go through the tiles twice."""
     print(f"merge {bits} {G} {variant} {layers} {splits} {n}", flush=True)
     inside, wgs = run_merge_forms(layers, H, n, budget, bits, G, variant, splits)
     assert inside == [{False}, {True}, {True}]
     units = layers * H * -(-n // (256, 128, 256, 512)[variant])
     if splits in (2, 3, 4, 5):
-        assert wgs == units * splits
+        assert wgs == units * splits and (H < 30 or wgs > torch.cuda.get_device_properties(0).multi_processor_count)
     else:
         assert wgs > units and wgs % units != 0
 
@@ -277,14 +278,15 @@ FOUR_WAVES = [(v, *c) for v in (0, 1) for c in ((2, 600, 1900), (5, 600, 1900), 
 
 @pytest.mark.parametrize("variant,splits,n,budget", FOUR_WAVES + [(v, *c) for v in (2, 3) for c in ((6, 257, 2000), (16, 300, 4300))])
 def test_shapes_and_cuts_that_the_second_launch_merges(variant, splits, n, budget):
-    """Four waves, and more pieces than a lane holds at a time: a second launch merges whatever runs beside attention."""
+    """Cuts that were asked for, of the four-wave shapes or into more than five pieces: a second launch merges whatever runs beside
+    attention."""
     inside, wgs = run_merge_forms(1, 3, n, budget, 4, 64, variant, splits)
     assert inside == [{False}, {False}, {False}]
     assert wgs > 3 * -(-n // (256, 128, 256, 512)[variant])   # more workgroups than units
 
 
 @pytest.mark.parametrize("H,n,budget,bits,variant", [(3, 300, 4300, 4, 3), (3, 130, 700, 4, 3), (16, 1374, 0, 16, 3), (12, 777, 3000, 2, 3), (5, 282, 700, 4, 2),
-                                                     (8, 257, 2000, 2, 2)])
+                                                     (8, 257, 2000, 2, 2), (16, 1041, 4000, 4, 0), (4, 200, 5000, 2, 0), (5, 513, 3000, 16, 0)])
 def test_cuts_of_the_library_are_merged_by_all_workgroups_of_a_unit(H, n, budget, bits, variant):
     """Without requested splits one layer's units of three and more equal pieces are merged inside whatever runs beside attention;
     the same cut asked for is merged by a second launch.  The same bits from both: 3 to 16 pieces (whose items are whole, half and
@@ -373,8 +375,9 @@ def test_grids_of_the_library_have_a_place_for_every_workgroup(variant, bits, G,
 @pytest.mark.parametrize("bits", [4, 2, 16])
 def test_long_launches_of_small_blocks_take_the_shape_of_four_waves(bits):
     """150 tokens are one block of 256 rows: 8 waves x 32 rows while 24 layers' units hold fewer than 80 tiles per compute unit, 4
-    waves x 64 from there on.  Against the first shape throughout, within the rounding of probabilities and outputs to bf16 and of
-    partials to fp16 (the bounds of the comparison with the oracle; the two differ by a fifth of them)."""
+    waves x 64 from there on.  Against the first shape throughout, each head of each layer by itself (what is lost at a piece's edge
+    is lost in one of them), within the rounding of probabilities and outputs to bf16 and of partials to fp16: the bound of the
+    comparison with the oracle, of which the two differ by a fifth, and for single values 20 times that of their head's rms."""
     ctxs = [xsv.Context(24, 16, 64, 150, 5, 3800, bits, 64) for _ in range(2)]
     ctxs[1].set_attend_variant(2)
     g = torch.Generator().manual_seed(bits)
@@ -383,7 +386,9 @@ def test_long_launches_of_small_blocks_take_the_shape_of_four_waves(bits):
         q, k, v = (torch.randn((24, 16, 150, 64), generator=g).to(torch.bfloat16).to(DEV) for _ in range(3))
         a, b = (c.step_all_layers(q, k, v).float() for c in ctxs)
         grids.append([c.last_attend_workgroups() for c in ctxs])
-        assert (a - b).abs().max() <= 2e-2 and (a - b).norm() <= 1e-2 * b.norm()
+        norms = b.norm(dim=(-2, -1))
+        assert ((a - b).norm(dim=(-2, -1)) <= 1e-2 * norms).all()
+        assert ((a - b).abs().amax(dim=(-2, -1)) <= 0.2 * norms / (150 * 64) ** 0.5).all()
     assert grids[1][0] == grids[1][1] and grids[-1][0] != grids[-1][1]
     for c in ctxs:
         c.destroy()
