@@ -38,14 +38,16 @@
 //   each row on its own (the careful pass).
 //   The headroom is small on purpose.  Products of probability and value are accumulated at the probabilities' scale: at 2^-60
 //   values below 2^-66 lose bits and below 2^-89 vanish.  At 2^-8 they keep what bf16 holds down to its smallest numbers.
-//   What bounds the loop: vector issue.  Per wave and tile 64 multiply-adds, 64 exponentials, 32 conversions, some 70 plain
+//   What the loop's time goes to: vector issue first.  Per wave and tile 64 multiply-adds, 64 exponentials, 32 conversions, some 70 plain
 //   instructions of dequantizing and of looking at the sums, and 40 MFMAs.  At the rates measured on this part (a plain instruction
 //   4.9 cycles of a wave's issue, an exponential 8.6, an MFMA 7 beside the other wave's arithmetic) the two waves of a SIMD need
-//   some 3290 cycles for that, against 2340 of the matrix pipe; the loop takes 3320.  v_dot2c_f32_bf16 must stay out of it: it
-//   executes on the matrix pipe (beside a wave that issues MFMAs back to back it makes no progress at all), so row sums taken
-//   with it serialize MFMAs and softmax; they are MFMAs of their own here (sum_step).  At 16 heads, 1374 rows, 5470 keys, one
-//   key range per 512 rows: 1.88 -> 1.66 us per tile of a workgroup on the 4-bit cache; a bf16 cache grown by 16 frames of 1374
-//   tokens, four layers: 7220 -> 5780 us.
+//   some 3290 cycles for that, against 2340 of the matrix pipe.  A 4-bit tile takes 3900 (a bf16 one 3400, where the same count
+//   gives some 2750): 600 more, which no count here explains - the barrier of a tile, reads and writes of LDS, the prefetch.
+//   v_dot2c_f32_bf16 must stay out of it: it executes on the matrix pipe (beside a wave that issues MFMAs back to back it makes no
+//   progress at all), so row sums taken with it serialize MFMAs and softmax; they are MFMAs of their own here (sum_step).  At 16
+//   heads, 1374 rows, 5470 keys, one key range per 512 rows: 1.88 -> 1.66 us per tile of a workgroup on the 4-bit cache (at 2.4 GHz; the
+//   part grants 2.15 beside a chain and 2.0 with 24 layers per launch); a bf16 cache grown by 16 frames of 1374 tokens, four layers: 7220
+//   -> 5780 us.
 #include <cstddef>
 #include <type_traits>
 
@@ -1203,8 +1205,8 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const AttendArgs a) {
 }
 
 // Merge of the pieces of every unit that was cut:  out = sum_p 2^(m_p - M) O_p / sum_p 2^(m_p - M) l_p.
-// (A launch of its own where nothing runs beside attention: it spreads over the whole chip, and its partials need no agent-scope
-// stores; see AttendArgs::merge_inside.)
+// (A launch of its own for cuts that were asked for and line partitions with nothing beside them, for units in two pieces, and for
+// shapes and numbers of pieces that have no kernel that merges inside; see AttendArgs::merge_inside.)
 // Grid: y = chunk of 32 query rows of a unit; x = the unit when all units are cut alike, else a boundary
 // between workgroups w-1 | w of the attention grid (w = blockIdx.x + 1), standing for the unit it falls
 // into: a unit with several boundaries is handled at its first one, and a boundary that coincides with

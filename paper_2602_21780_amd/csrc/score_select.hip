@@ -14,10 +14,9 @@
 // front_kernel is all three in one launch for one layer, a role per workgroup.  Each part takes a few microseconds, most of it the latency of
 // a kernel's start, of its arguments and of one or two trips to memory: one layer of 16 heads x 1374 tokens with 2722 middle
 // positions took 21.2 us as three kernels with nothing beside them, and takes 13.8 as one.  Beside attention, as a step runs it,
-// the kernel is no shorter than the three were together (7.9 + 8.9 + 10.2 before, 29.2 us now, medians of a trace): few compute
-// units are free then, its workgroups take turns on them, and all of them have the registers and the LDS of the score part.  What a
-// step gains there are two launches and the gaps between them.  (61 registers, four workgroups to a compute unit; with the pool
-// of last resort unrolled like the first, 120 to 139, and steps that wait for the chain are 1 to 2 % slower.)
+// the kernel takes 17.2 us where 64 compute units are free, the three took 7.9 + 8.9 + 10.2 (medians of traces).  (61 registers, three
+// workgroups to a compute unit; with the pool of last resort unrolled like the first, 120 to 139, and steps that wait for the chain are 1
+// to 2 % slower.  So few registers that a workgroup fits beside attention's 32-row shapes, which does harm: launch_attend_t.)
 // Nothing in it waits without end, whatever else is on the chip.  The workgroup that completes a list's scores goes on to select
 // it.  A score workgroup does wait for the pool (only at the end, with the key means in registers), which has smaller indices and
 // as a rule has been started before it; but launches of several streams may hold the places each other's pools need, so the wait

@@ -151,7 +151,7 @@ struct AttendArgs {
   // beside a chain with scores, where a second launch waits for places among the chain's workgroups.  us per pass, second launch
   // and inside: frame-wise attention of 16 x 1374 (5 pieces) 23.4 and 19.3, a bf16 cache grown by 16 frames, four layers, 5700
   // and 5440, one layer of 16 x 1374 without scores 50.5 and 46.6, one of 5 x 539 in 11 pieces 41 and 33, six 2-bit layers of 12 x 777 in
-  // 8 281 and 267; two pieces of 9 x 501 17.8 and 18.4.  (With the last workgroup merging all by itself, 6 us for five
+  // 8 282 and 272 (within what that case's runs differ by); two pieces of 9 x 501 17.8 and 18.4.  (With the last workgroup merging all by itself, 6 us for five
   // pieces of 512 rows where four that share it take 2, 24 layers with deferred joins took 1305 and not 1212.)
   int merge_inside;
   int equal_ranges;  // > 0: every unit is cut into exactly this many key ranges, at the same tiles:
@@ -163,7 +163,9 @@ struct AttendArgs {
   int xcd_heads;   // with xcd_ranges: (layer, head) pairs rather than (layer, head, range) triples are dealt to the XCDs
   int short_last;   // the last of a unit's equal_ranges was made short (see range_begin)
   // Workgroups that merge inside wait for the others of their unit: only where all units are cut alike, so that its workgroups end
-  // together - a 2-bit stack on a line partition is 1 % slower with it - and no more of them than have a place at once.
+  // together - a 2-bit stack on a line partition is 1 % slower with it - and no more of them than have a place at once.  (Another
+  // stream's work, or a chain that deferred joins left running, may hold places all the same: then the number of looks bounds the wait.
+  // Frame-wise attention behind deferred steps of 16 x 1374 / 16 x 700: 315 and 301, 222 and 206 us with the second launch and inside.)
   int merge_waits;
   // How often such a workgroup looks for the others before it leaves them its share (a look takes about 0.7 us).  Long enough for
   // those that started late because a chain still held their compute units.  us at 0 / 4 / 8 / 16 / 32 / 64 looks: 24 layers with
