@@ -92,7 +92,7 @@ __device__ __forceinline__ float pool_partial(const FrontLayer& ly, const FrontC
   const float w_special = 1.0f / base, w_whole = 1.0f / (base * (float)min(g, n - n_s)), w_last = 1.0f / (base * (float)(n - last));
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   // ROWS rows of a row lane are in flight together (rows past the frame: weight 0); with six, 1374 rows take two trips to
-  // memory (an unrolled loop and its rest took two and one for every row of the rest: 4.8 us alone, 4.0 like this)
+  // memory (an unrolled loop and its rest took two and one for every row of the rest: 4.8 us alone, 4.2 like this)
   for (int r0 = half * 64 + rl; r0 < n; r0 += 128 * ROWS) {
     uint4 v[ROWS];
 #pragma unroll
